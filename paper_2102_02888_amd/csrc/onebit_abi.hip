@@ -8,6 +8,7 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <memory>
 #include <new>
@@ -210,101 +211,108 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
         return fail(ONEBIT_EINVAL, "%lld tiles: plans are limited to 2^25 tiles of %d elements",
                     (long long)tile_count, kTileElems);
 
-    // Tiles in address order (segment by segment), so that passes over all
-    // of d stream through memory; the tiles of chunk owner j are listed
-    // separately, chunk-major, as one contiguous range of chunk_tiles.
-    std::vector<Tile> tiles;
-    tiles.reserve(tile_count);
-    p->seg_tile_begin.assign(p->S, 0);
-    p->seg_tile_end.assign(p->S, 0);
+    // Every segment's range of the tile list, and the number of the chunk
+    // owners' shared-table workgroups (up to kWavesPerBlock consecutive tiles
+    // of one segment each), which fix the sizes of the device tables.
+    p->seg_tile_begin.resize(p->S);
+    p->seg_tile_end.resize(p->S);
     p->chunk_tile_begin.assign(n + 1, 0);
+    p->chunk_block_begin.assign(n + 1, 0);
     p->chunk_word_lo.assign(n, INT64_MAX);
     p->chunk_word_hi.assign(n, -1);
-    std::vector<int64_t> seg_len(p->S);
+    int64_t at = 0, server_block_count = 0;
     for (int64_t q = 0; q < p->S; ++q) {
-        const int64_t b = p->seg_begin[q], en = p->seg_end[q];
-        seg_len[q] = en - b;
-        p->seg_tile_begin[q] = (int64_t)tiles.size();
-        for (int64_t s = b; s < en;) {
+        const int64_t cnt = tiles_of(p->seg_begin[q], p->seg_end[q]);
+        p->seg_tile_begin[q] = at;
+        p->seg_tile_end[q] = at += cnt;
+        p->max_seg_tiles = std::max(p->max_seg_tiles, cnt);
+        server_block_count += onebit::server_blocks_of(cnt);
+    }
+    p->T = tile_count;
+    const int64_t num_blocks = (p->D + kTileElems - 1) / kTileElems;
+
+    // The tables are built in place in one host buffer, in the layout of the
+    // device allocation.
+    const size_t tiles_bytes = round_up((size_t)p->T * sizeof(Tile) + 1, 256);
+    const size_t order_bytes = round_up((size_t)p->T * sizeof(int32_t) + 1, 256);
+    const size_t seg_bytes = round_up((size_t)p->S * sizeof(int64_t), 256);
+    const size_t sblock_bytes = round_up((size_t)server_block_count * sizeof(int32_t) + 1, 256);
+    const size_t seg0 = tiles_bytes + order_bytes;
+    const size_t sblocks0 = seg0 + 3 * seg_bytes;
+    const size_t blocks0 = sblocks0 + sblock_bytes;
+    const size_t total = blocks0 + round_up((size_t)num_blocks * sizeof(onebit::Block) + 1, 256);
+    std::unique_ptr<char, void (*)(void *)> host((char *)std::malloc(total), std::free);
+    if (!host) throw std::bad_alloc();
+
+    // Tiles in address order (segment by segment), so that passes over all
+    // of d stream through memory, and the blocks that hold them (every
+    // 1024-element block of the padded length holds a tile, as tensors follow
+    // one another at multiples of 64 elements with no gap).
+    Tile *tiles = (Tile *)host.get();
+    onebit::Block *blocks = (onebit::Block *)(host.get() + blocks0);
+    int64_t *seg_len = (int64_t *)(host.get() + seg0 + 2 * seg_bytes);
+    int64_t blk = -1;
+    for (int64_t q = 0, t = 0; q < p->S; ++q) {
+        const int64_t en = p->seg_end[q];
+        seg_len[q] = en - p->seg_begin[q];
+        for (int64_t s = p->seg_begin[q]; s < en; ++t) {
             const int64_t next = std::min<int64_t>(en, (s / kTileElems + 1) * kTileElems);
-            Tile t;
-            t.start = s;
-            t.len = (int32_t)(next - s);
-            t.seg = (int32_t)q;
-            tiles.push_back(t);
+            tiles[t].start = s;
+            tiles[t].len = (int32_t)(next - s);
+            tiles[t].seg = (int32_t)q;
+            if (s / kTileElems != blk) {
+                blk = s / kTileElems;
+                blocks[blk] = onebit::Block{(int32_t)t, (int32_t)q, 0, next - s == kTileElems};
+            }
+            blocks[blk].starts |= 1u << (s % kTileElems / 64);
             s = next;
         }
-        p->seg_tile_end[q] = (int64_t)tiles.size();
-        p->max_seg_tiles = std::max(p->max_seg_tiles, p->seg_tile_end[q] - p->seg_tile_begin[q]);
     }
-    std::vector<int32_t> chunk_tiles;
-    chunk_tiles.reserve(tiles.size());
-    // the chunk owners' shared-table workgroups: up to kWavesPerBlock
-    // consecutive tiles of one segment each, in the same chunk-major order
-    std::vector<int32_t> server_blocks;
-    p->chunk_block_begin.assign(n + 1, 0);
+    // the tiles of chunk owner j, chunk-major, as one contiguous range of
+    // chunk_tiles, and its shared-table workgroups in the same order
+    int32_t *chunk_tiles = (int32_t *)(host.get() + tiles_bytes);
+    int32_t *server_blocks = (int32_t *)(host.get() + sblocks0);
+    int64_t pos = 0, sb = 0;
     for (int32_t j = 0; j < n; ++j) {
-        p->chunk_tile_begin[j] = (int64_t)chunk_tiles.size();
-        p->chunk_block_begin[j] = (int64_t)server_blocks.size();
+        p->chunk_tile_begin[j] = pos;
+        p->chunk_block_begin[j] = sb;
         for (int32_t k = 0; k < K; ++k) {
             const int64_t q = (int64_t)k * n + j;
-            const int64_t pos = (int64_t)chunk_tiles.size();
+            const int64_t b = p->seg_begin[q], en = p->seg_end[q];
+            if (en <= b) continue;
             const int64_t cnt = p->seg_tile_end[q] - p->seg_tile_begin[q];
             for (int64_t i = 0; i < onebit::server_blocks_of(cnt); ++i)
-                server_blocks.push_back(onebit::server_block_entry(pos, cnt, i));
+                server_blocks[sb++] = onebit::server_block_entry(pos, cnt, i);
             for (int64_t t = p->seg_tile_begin[q]; t < p->seg_tile_end[q]; ++t)
-                chunk_tiles.push_back((int32_t)t);
-            const int64_t b = p->seg_begin[q], en = p->seg_end[q];
-            if (en > b) {
-                p->chunk_word_lo[j] = std::min(p->chunk_word_lo[j], b / 64);
-                p->chunk_word_hi[j] = std::max(p->chunk_word_hi[j], (en - 1) / 64);
-            }
+                chunk_tiles[pos++] = (int32_t)t;
+            p->chunk_word_lo[j] = std::min(p->chunk_word_lo[j], b / 64);
+            p->chunk_word_hi[j] = std::max(p->chunk_word_hi[j], (en - 1) / 64);
         }
     }
-    p->chunk_tile_begin[n] = (int64_t)chunk_tiles.size();
-    p->chunk_block_begin[n] = (int64_t)server_blocks.size();
-    p->T = (int64_t)tiles.size();
-
-    const size_t tiles_bytes = round_up(tiles.size() * sizeof(Tile) + 1, 256);
-    const size_t order_bytes = round_up(chunk_tiles.size() * sizeof(int32_t) + 1, 256);
-    const size_t seg_bytes = round_up((size_t)p->S * sizeof(int64_t), 256);
-    const size_t block_bytes = round_up(server_blocks.size() * sizeof(int32_t) + 1, 256);
-    const size_t seg0 = tiles_bytes + order_bytes;
-    const size_t blocks0 = seg0 + 3 * seg_bytes;
-    const size_t total = blocks0 + block_bytes;
-    std::vector<char> host(total, 0);
-    if (!tiles.empty()) {
-        std::memcpy(host.data(), tiles.data(), tiles.size() * sizeof(Tile));
-        std::memcpy(host.data() + tiles_bytes, chunk_tiles.data(),
-                    chunk_tiles.size() * sizeof(int32_t));
-        std::memcpy(host.data() + blocks0, server_blocks.data(),
-                    server_blocks.size() * sizeof(int32_t));
-    }
-    std::memcpy(host.data() + seg0, p->seg_tile_begin.data(), p->S * sizeof(int64_t));
-    std::memcpy(host.data() + seg0 + seg_bytes, p->seg_tile_end.data(), p->S * sizeof(int64_t));
-    std::memcpy(host.data() + seg0 + 2 * seg_bytes, seg_len.data(), p->S * sizeof(int64_t));
+    p->chunk_tile_begin[n] = pos;
+    p->chunk_block_begin[n] = sb;
+    std::memcpy(host.get() + seg0, p->seg_tile_begin.data(), p->S * sizeof(int64_t));
+    std::memcpy(host.get() + seg0 + seg_bytes, p->seg_tile_end.data(), p->S * sizeof(int64_t));
     // Every host allocation is done; from here on nothing throws.
     e = hipMalloc(&p->dev_mem, total);
     if (e != hipSuccess)
         return fail(ONEBIT_ENOMEM, "hipMalloc of %zu bytes of plan tables: %s", total,
                     hipGetErrorString(e));
-    e = hipMemcpy(p->dev_mem, host.data(), total, hipMemcpyHostToDevice);
+    e = hipMemcpy(p->dev_mem, host.get(), total, hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         (void)hipFree(p->dev_mem);
         return hip_fail(e, "hipMemcpy of plan tables");
     }
     char *base = (char *)p->dev_mem;
-    Tile *d_tiles = (Tile *)base;
-    int32_t *d_order = (int32_t *)(base + tiles_bytes);
-    int64_t *d_stb = (int64_t *)(base + seg0);
-    int64_t *d_ste = (int64_t *)(base + seg0 + seg_bytes);
-    int64_t *d_sl = (int64_t *)(base + seg0 + 2 * seg_bytes);
-    p->tb.tiles = d_tiles;
-    p->tb.chunk_tiles = d_order;
-    p->tb.seg_tile_begin = d_stb;
-    p->tb.seg_tile_end = d_ste;
-    p->tb.seg_len = d_sl;
-    p->tb.server_blocks = (const int32_t *)(base + blocks0);
+    p->tb.tiles = (const Tile *)base;
+    p->tb.chunk_tiles = (const int32_t *)(base + tiles_bytes);
+    p->tb.seg_tile_begin = (const int64_t *)(base + seg0);
+    p->tb.seg_tile_end = (const int64_t *)(base + seg0 + seg_bytes);
+    p->tb.seg_len = (const int64_t *)(base + seg0 + 2 * seg_bytes);
+    p->tb.server_blocks = (const int32_t *)(base + sblocks0);
+    p->tb.blocks = (const onebit::Block *)(base + blocks0);
+    p->tb.num_blocks = num_blocks;
+    p->tb.padded_len = p->D;
     const size_t seg_tables = onebit::server_table_bytes(p->n, 1);
     p->table_bytes = (size_t)p->S <= kServerTableBudget / seg_tables
                          ? onebit::server_table_bytes(p->n, p->S)

@@ -23,9 +23,25 @@ constexpr int kTileElems = kWave * 4 * kSubBlocks;  // 1024 elements = 16 sign w
 constexpr int kTileWords = kTileElems / 64;
 constexpr int kServerRowBatch = 32;                 // worker rows staged in LDS at a time
 
+// The streaming passes walk the flat buffer in blocks: block b is elements
+// [b * kTileElems, (b + 1) * kTileElems) of the padded length (only the last
+// one can be short).  Tiles are cut at block boundaries, so a block holds
+// whole tiles: one full tile (`whole`), or up to 16 short ones whose sign
+// words fill it from its first word on.  Word w of a block belongs to tile
+// `tile` + (number of bits of `starts` at or below w) - 1.
+struct Block {
+    int32_t tile;     // the block's first tile
+    int32_t seg;      // that tile's segment
+    uint32_t starts;  // bit w: a tile starts at the block's word w
+    int32_t whole;    // 1: one tile of kTileElems elements
+};
+
 // Device-side layout tables owned by a plan.
 struct DeviceTables {
     const Tile *tiles;             // [T], in address (segment) order
+    const Block *blocks;           // [num_blocks], every block of the padded length
+    int64_t num_blocks;            // ceil(D / kTileElems)
+    int64_t padded_len;            // D
     const int32_t *chunk_tiles;    // [T], tile ids in chunk-major order
     const int64_t *seg_tile_begin; // [S]
     const int64_t *seg_tile_end;   // [S]
@@ -33,6 +49,23 @@ struct DeviceTables {
     const int32_t *server_blocks;  // chunk owners' shared-table workgroups, chunk-major
                                    // (entries of onebit_grid.h's server_block_entry)
 };
+
+// Exact quotient of an item number below 2^31 by a fixed divisor d < 2^31:
+// (item * mul) >> shift with mul = ceil(2^(31+s) / d), s = ceil(log2 d),
+// shift = 31 + s.  mul * d exceeds 2^(31+s) by less than d <= 2^s, so the
+// error item * (mul * d - 2^(31+s)) / (d * 2^(31+s)) stays below 1/d.
+struct FastDiv {
+    uint64_t mul;
+    uint32_t shift;
+};
+
+inline FastDiv fast_div(int64_t d)
+{
+    uint32_t s = 0;
+    while (((int64_t)1 << s) < d) ++s;
+    const uint64_t one = (uint64_t)1 << (31 + s);
+    return {(one + (uint64_t)d - 1) / (uint64_t)d, 31 + s};
+}
 
 // Gradient element types (the values of the ONEBIT_GRAD_* constants).
 constexpr int kGradF32 = 0;

@@ -216,6 +216,97 @@ __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane
 __device__ __forceinline__ float error_of(float z, float s) { return z >= 0.f ? z - s : z + s; }
 
 // ---------------------------------------------------------------------------
+// Blocks (the streaming passes).  A wave's loads of a block need its number
+// only, so they are issued before the block's record, and the scales that
+// hang on it, have arrived.  A whole block is one full tile of one segment.
+// A mixed block (short tiles, several segments, padding) is streamed the same
+// way; each 16-lane row holds one sign word, which lies in one tile, so the
+// lanes look up their row's tile and store only their real elements.
+// ---------------------------------------------------------------------------
+
+// The record of block b (wave-uniform), in one 128-bit load.
+__device__ __forceinline__ Block load_block(const Block *__restrict__ blocks, int64_t b)
+{
+    const int4 r = ((const int4 *)blocks)[b];
+    return Block{r.x, r.y, (uint32_t)r.z, r.w};
+}
+
+// Loads elements li..li+3 of the block at p; lim = elements of the block
+// inside the padded length (a multiple of 64).  INSIDE: the whole block is.
+template <bool INSIDE>
+__device__ __forceinline__ v4f ldb4(const float *__restrict__ p, int li, int lim)
+{
+    if (INSIDE || li < lim)
+        return __builtin_bit_cast(
+            v4f, __builtin_amdgcn_raw_buffer_load_b128(stream_rsrc(p), li * 4, 0, kStreamLoad));
+    return v4f{0.f, 0.f, 0.f, 0.f};
+}
+
+template <bool INSIDE, class G>
+__device__ __forceinline__ v4f ldgb4(const typename G::T *__restrict__ p, int li, int lim)
+{
+    if constexpr (sizeof(typename G::T) == 4) {
+        return ldb4<INSIDE>((const float *)p, li, lim);
+    } else {
+        if (INSIDE || li < lim) return ldg4<true, G>(p, li, 0);
+        return v4f{0.f, 0.f, 0.f, 0.f};
+    }
+}
+
+// The tile of word w of a mixed block (w inside the padded length).
+__device__ __forceinline__ Tile block_word_tile(const Tile *__restrict__ tiles, const Block &rec,
+                                                int w)
+{
+    return tiles[rec.tile + __popc(rec.starts & ((2u << w) - 1u)) - 1];
+}
+
+// How many of the 4 elements at flat index e the tile holds (0..4).
+__device__ __forceinline__ int tile_valid4(const Tile &t, int64_t e)
+{
+    const int64_t left = t.start + t.len - e;
+    return left >= 4 ? 4 : left > 0 ? (int)left : 0;
+}
+
+// Stores elements li..li+3 of the block at p, the first `valid` of them.
+template <bool WHOLE>
+__device__ __forceinline__ void stb4(float *__restrict__ p, int li, int valid, v4f v)
+{
+    if (WHOLE || valid == 4) {
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u32, v), stream_rsrc(p),
+                                               li * 4, 0, kStreamStore);
+        return;
+    }
+    if (valid > 0) p[li] = v.x;
+    if (valid > 1) p[li + 1] = v.y;
+    if (valid > 2) p[li + 2] = v.z;
+}
+
+// Sum over the 16 lanes of each row (every lane of the row gets it).
+__device__ __forceinline__ double row_sum(double a)
+{
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) a += __shfl_xor(a, off, kWave);
+    return a;
+}
+
+// Sum of tile j's words of a mixed block from the words' sums, in word order.
+__device__ __forceinline__ double block_tile_sum(const double *__restrict__ words, uint32_t starts,
+                                                 int j)
+{
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < kTileWords; ++w)
+        if (__popc(starts & ((2u << w) - 1u)) - 1 == j) s += words[w];
+    return s;
+}
+
+// The sign bit of +-a (bit set: +a), exact for any a.
+__device__ __forceinline__ float with_sign(float a, uint32_t nib, int c)
+{
+    return __uint_as_float(__float_as_uint(a) ^ (((~nib >> c) & 1u) << 31));
+}
+
+// ---------------------------------------------------------------------------
 // Warm-up Adam (eq. (alg:v)) on the average of n_grads gradient rows.
 //
 // The row-summing kernels (this one and the 32-bit comparison step) give the
@@ -537,23 +628,46 @@ __global__ __launch_bounds__(kRowBlock) void k_warmup(
 // sign words of z_i, per-tile partial sum of z_i^2, and z_i written back as the
 // new compensated error state.
 //
-// Packed momentum (every step after the first): a two-wave workgroup handles
-// one tile for a group of consecutive workers (one worker in practice), wave h
-// holding sub-blocks 2h and 2h+1, and the items run group-major, split into
-// one contiguous eighth per XCD: the waves in flight on an XCD work on the
-// same few worker rows, so each XCD streams through 2 x group rows of
-// (g, error state) at a time instead of all 2n.  Half a tile per wave keeps
-// fewer bytes in flight per wave at a higher occupancy (80 instead of ~120
-// VGPRs), which the mix of two read streams and one written stream favours.
-// The momentum of a tile is re-derived by every worker, 1/8 byte per element
-// per worker from a sign array small enough to stay in the last-level cache.
+// Packed momentum (every step after the first): a workgroup takes one item,
+// one block of one worker's row, and the items run row by row, split into one
+// contiguous eighth per XCD: the waves in flight on an XCD stream the same two
+// rows (g_i and the error state of worker i).  The momentum of a block is
+// re-derived by every worker, 1/8 byte per element per worker from a sign
+// array small enough to stay in the last-level cache.
+//
+// What bounds it is HBM, and how close it comes depends on the bytes of loads
+// that each SIMD keeps in flight: about 15 KB is best (fewer leave the memory
+// idle, more make its read and write streams interfere).  With every load
+// issued before the block's record arrives, a wave has its loads in flight
+// nearly all its life, so the parts of a block are sized for that: fp32
+// gradients take one sub-block per wave (2 KB of loads, 8 waves per SIMD),
+// 16-bit ones two (3 KB) at 5 waves per SIMD, held there by unused LDS.  Step
+// of the BERT-Base shape, n = 16, one process, same buffers, fp32 / bf16
+// gradients, in ms (two dependent loads before the rows' loads, before:
+// 3.641 / 3.124): one sub-block per wave at 8, 7, 6, 5 waves 3.531, 3.540,
+// 3.774, 4.663 / 3.171, 3.401, 3.717, 4.908; two at 8, 7, 6, 5, 4, 3 waves
+// 3.666, 3.645, 3.589, 3.556, 3.542, 3.781 / 3.128, 3.097, 3.041, 3.033,
+// 3.095, 3.704; four at 8, 3, 2 waves 3.727, 3.574, 3.541 / 3.222, 3.038,
+// 3.218.
 // An fp32 momentum (the first compression step) is read once per tile for all
 // local workers instead, by k_worker_rows.
 // ---------------------------------------------------------------------------
-// Sub-blocks per wave of the packed worker pass, and its waves per tile.
+// Sub-blocks per wave of the first compression step's row walk.
 constexpr int kWorkerSubBlocks = 2;
 static_assert(kSubBlocks / kWorkerSubBlocks == kWorkerWavesPerBlock,
-              "the packed worker pass gives each wave of a workgroup part of one tile");
+              "the row walk gives each wave of a pair part of one tile");
+
+// The packed pass: sub-blocks per wave, waves per workgroup (one block), and
+// the unused LDS that holds the occupancy at 5 waves per SIMD (160 KB of LDS
+// for 10 workgroups of two waves on a CU's four SIMDs), see above.
+template <class G>
+constexpr int kPassSubBlocks = sizeof(typename G::T) == 2 ? 2 : 1;
+template <class G>
+constexpr int kPassWaves = kSubBlocks / kPassSubBlocks<G>;
+// Items of one launch: at most 256 threads each, below 2^32 work-items.
+constexpr int64_t kMaxPassItems = (int64_t)3 << 22;
+template <class G>
+constexpr int kPassIdleLds = sizeof(typename G::T) == 2 ? 15872 : 0;
 
 // The shared momentum m_{t-1} of sub-blocks sb0 .. sb0+SB-1 of the tile times
 // beta1.  PACKED: m_{t-1} is the previous step's gathered server message,
@@ -656,83 +770,169 @@ __device__ __forceinline__ double worker_row_store(const Tile &tile, int lane, i
     return wave_sum(acc);
 }
 
-// The tile for workers [i0, i1), this wave's sub-blocks of the momentum term
-// loaded or decoded once.  The waves' sums of each row meet in red (two slots,
-// alternating by row: a wave can be at most one row ahead of the other, so
-// the slot it writes is never the one still being read) and wave 0 adds them
-// in wave order.  Every wave of the workgroup runs the same rows, so every
-// wave reaches every barrier.
-template <bool FULL, bool PACKED, class G>
-__device__ __forceinline__ void worker_tile(
-    double (&red)[2][kWorkerWavesPerBlock], int &slot, const Tile &tile, int64_t t, int lane,
-    int wv, int64_t num_tiles, const float *__restrict__ m, const uint64_t *__restrict__ m_bits,
-    const float *__restrict__ m_scales, const typename G::T *__restrict__ g, int64_t g_ld,
-    float *__restrict__ err, int64_t err_ld, const float *__restrict__ scales, int64_t scales_ld,
-    uint64_t *__restrict__ bits, int64_t bits_ld, double *__restrict__ partial, int i0, int i1,
-    float beta1, float omb1)
+// A wave's loads of its part of one block: the gradient row, the compensated
+// row and the momentum (sign words, or fp32 values).
+template <bool INSIDE, bool PACKED, class G, int SB>
+__device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&mv)[SB],
+                                            uint64_t (&word)[SB],
+                                            const typename G::T *__restrict__ gi,
+                                            const float *__restrict__ ei,
+                                            const float *__restrict__ m,
+                                            const uint64_t *__restrict__ m_bits, int sb0, int lane,
+                                            int lim)
 {
-    constexpr int SB = kWorkerSubBlocks;
-    const int sb0 = wv * SB;
-    v4f bm[SB];
-    beta1_momentum<FULL, PACKED, SB>(bm, tile, lane, sb0, m, m_bits, m_scales, beta1);
-    for (int i = i0; i < i1; ++i) {
-        v4f gv[SB], cv[SB];
-        float sp;
-        worker_row_load<FULL, G, SB>(tile, lane, sb0, i, g, g_ld, err, err_ld, scales, scales_ld,
-                                     gv, cv, sp);
-        const double acc = worker_row_store<FULL, SB>(tile, lane, sb0, bm, i, gv, cv, sp, err,
-                                                      err_ld, bits, bits_ld, omb1);
-        if (lane == 0) red[slot][wv] = acc;
-        __syncthreads();
-        if (wv == 0 && lane == 0) {
-            double sum = red[slot][0];
 #pragma unroll
-            for (int k = 1; k < kWorkerWavesPerBlock; ++k) sum += red[slot][k];
-            partial[(int64_t)i * num_tiles + t] = sum;
+    for (int b = 0; b < SB; ++b) {
+        const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
+        word[b] = 0;
+        if (PACKED) {
+            if (INSIDE || li < lim) word[b] = m_bits[li >> 6];
+        } else {
+            mv[b] = ldb4<INSIDE>(m, li, lim);
         }
-        slot ^= 1;
+        gv[b] = ldgb4<INSIDE, G>(gi, li, lim);
+        cv[b] = ldb4<INSIDE>(ei, li, lim);
     }
 }
 
-// Waves per SIMD of the worker pass.  With fp32 gradients the kernel's
-// register count sits at the six-wave limit (80 VGPRs; without the hint the
-// compiler settles on 85 and five waves).  A 16-bit gradient row needs half
-// the registers for its loads, and seven waves (72 VGPRs, no spills) ran the
-// bf16 and fp16 passes 0.5-0.8% faster than six on the BERT shapes and 2.2%
-// on the 5,000-tensor stress workload; eight spill.
-template <class G>
-constexpr int kWorkerWavesPerSimd = sizeof(typename G::T) == 2 ? 7 : 6;
+// One block of a worker's row (this wave's sub-blocks) from its loaded values:
+// scales, arithmetic and stores.  The waves' sums meet in red and are added in
+// wave or word order.  Both waves have the same block, so both reach the
+// barrier.
+template <bool WHOLE, bool PACKED, int SB>
+__device__ __forceinline__ void worker_block(
+    double (&red)[kTileWords], const Tile *__restrict__ tiles, const Block &rec, int64_t base,
+    int lim, int lane, int wv, const v4f (&mv)[SB], const uint64_t (&word)[SB], float s0,
+    float ms0, const float *__restrict__ m_scales, const v4f (&gv)[SB], const v4f (&cv)[SB],
+    const float *__restrict__ scales, float *__restrict__ ei, uint64_t *__restrict__ bi,
+    double *__restrict__ partial, float beta1, float omb1)
+{
+    const int sb0 = wv * SB;
+    // the scales of each sub-block's elements, one segment for a whole block
+    float sp[SB], bs[SB];
+    int valid[SB];
+    if (WHOLE) {
+        const float bms = PACKED ? beta1 * ms0 : 0.f;
+#pragma unroll
+        for (int b = 0; b < SB; ++b) {
+            sp[b] = s0;
+            bs[b] = bms;
+            valid[b] = 4;
+        }
+    } else {
+#pragma unroll
+        for (int b = 0; b < SB; ++b) {
+            const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
+            sp[b] = s0;
+            bs[b] = beta1 * ms0;
+            valid[b] = 0;
+            if (li < lim) {
+                const Tile t = block_word_tile(tiles, rec, li >> 6);
+                valid[b] = tile_valid4(t, base + li);
+                sp[b] = scales[t.seg];
+                if (PACKED) bs[b] = beta1 * m_scales[t.seg];
+            }
+        }
+    }
+    double acc = 0.0;
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+        const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
+        const uint32_t mnib = (uint32_t)(word[b] >> (4 * (lane & 15)));
+        v4f zv;
+        uint32_t nib = 0;
+        double sub = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float d = error_of(cv[b][c], sp[b]);
+            const float bm = PACKED ? with_sign(bs[b], mnib, c) : beta1 * mv[b][c];
+            float mi = omb1 * gv[b][c];
+            mi = bm + mi;
+            const float z = mi + d;
+            zv[c] = z;
+            const bool in = WHOLE || c < valid[b];
+            const double zd = in ? (double)z : 0.0;
+            sub += zd * zd;
+            nib |= (in && z >= 0.f) ? (1u << c) : 0u;
+        }
+        stb4<WHOLE>(ei, li, valid[b], zv);
+        const uint64_t out = row_sign_word(nib, lane);
+        const int w = 4 * (sb0 + b) + (lane >> 4);
+        if ((lane & 15) == 0 && (WHOLE || li < lim)) bi[w] = out;
+        if (WHOLE) {
+            acc += sub;
+        } else {
+            const double row = row_sum(sub);
+            if ((lane & 15) == 0) red[w] = row;
+        }
+    }
+    if (WHOLE) {
+        acc = wave_sum(acc);
+        if (lane == 0) red[wv] = acc;
+        __syncthreads();
+        if (wv == 0 && lane == 0) {
+            double sum = red[0];
+#pragma unroll
+            for (int k = 1; k < kSubBlocks / SB; ++k) sum += red[k];
+            partial[rec.tile] = sum;
+        }
+    } else {
+        __syncthreads();
+        if (wv == 0 && lane < __popc(rec.starts))
+            partial[rec.tile + lane] = block_tile_sum(red, rec.starts, lane);
+    }
+}
 
+// PACKED: m_{t-1} is the previous step's gathered server message, decoded
+// from its sign words and segment scale (+-scale, exactly the fp32 value the
+// update would have stored), so no fp32 momentum buffer is read.
 template <bool PACKED, class G>
-__global__ __launch_bounds__(kWorkerBlock) __attribute__((amdgpu_waves_per_eu(kWorkerWavesPerSimd<G>))) void k_worker_pass(
-    const Tile *__restrict__ tiles, int64_t num_tiles, const float *__restrict__ m,
+__global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t num_blocks,
+    FastDiv by_blocks, int64_t padded_len, int64_t num_tiles, const float *__restrict__ m,
     const uint64_t *__restrict__ m_bits, const float *__restrict__ m_scales,
     const typename G::T *__restrict__ g, int64_t g_ld, float *__restrict__ err, int64_t err_ld,
     const float *__restrict__ scales, int64_t scales_ld, uint64_t *__restrict__ bits,
-    int64_t bits_ld, double *__restrict__ partial, int n_local, int group, int64_t num_items,
+    int64_t bits_ld, double *__restrict__ partial, int64_t item_base, int64_t num_items,
     float beta1, float omb1)
 {
-    __shared__ double red[2][kWorkerWavesPerBlock];
+    constexpr int SB = kPassSubBlocks<G>;
+    __shared__ double red[kTileWords];
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x >> 6;
-    int slot = 0;
-    // each XCD walks one contiguous eighth of the items, one item per workgroup
+    // each XCD takes one contiguous eighth of the launch's items, one per workgroup
     const ItemWalk walk = xcd_item_walk(blockIdx.x, gridDim.x, num_items);
-    for (int64_t item = walk.first; item < walk.end; item += walk.stride) {
-        const int64_t grp = item / num_tiles;
-        const int64_t t = item - grp * num_tiles;
-        const int i0 = (int)grp * group;
-        const int i1 = min(n_local, i0 + group);
-        const Tile tile = tiles[t];
-        if (tile.len == kTileElems)
-            worker_tile<true, PACKED, G>(red, slot, tile, t, lane, wv, num_tiles, m, m_bits,
-                                         m_scales, g, g_ld, err, err_ld, scales, scales_ld, bits,
-                                         bits_ld, partial, i0, i1, beta1, omb1);
-        else
-            worker_tile<false, PACKED, G>(red, slot, tile, t, lane, wv, num_tiles, m, m_bits,
-                                          m_scales, g, g_ld, err, err_ld, scales, scales_ld, bits,
-                                          bits_ld, partial, i0, i1, beta1, omb1);
-    }
+    if (walk.first >= walk.end) return;  // the whole workgroup
+    const int64_t item = item_base + walk.first;
+    const int64_t i = (int64_t)(((uint64_t)item * by_blocks.mul) >> by_blocks.shift);
+    const int64_t blk = item - i * num_blocks;
+    const int64_t base = blk * kTileElems;
+    const int64_t room = padded_len - base;
+    const int lim = room < kTileElems ? (int)room : kTileElems;
+    const typename G::T *gi = g + i * g_ld + base;
+    float *ei = err + i * err_ld + base;
+    v4f gv[SB], cv[SB], mv[SB];
+    uint64_t word[SB];
+    if (lim == kTileElems)
+        worker_load<true, PACKED, G, SB>(gv, cv, mv, word, gi, ei, m + base, m_bits + (base >> 6),
+                                         wv * SB, lane, lim);
+    else
+        worker_load<false, PACKED, G, SB>(gv, cv, mv, word, gi, ei, m + base,
+                                          m_bits + (base >> 6), wv * SB, lane, lim);
+    const Block rec = load_block(blocks, blk);
+    scales += i * scales_ld;
+    // read here, before the branch, so that they travel with the rows
+    const float s0 = scales[rec.seg];
+    const float ms0 = PACKED ? m_scales[rec.seg] : 0.f;
+    uint64_t *bi = bits + i * bits_ld + (base >> 6);
+    if (rec.whole)
+        worker_block<true, PACKED, SB>(red, tiles, rec, base, lim, lane, wv, mv, word, s0, ms0,
+                                       m_scales, gv, cv, scales, ei, bi, partial + i * num_tiles,
+                                       beta1, omb1);
+    else
+        worker_block<false, PACKED, SB>(red, tiles, rec, base, lim, lane, wv, mv, word, s0, ms0,
+                                        m_scales, gv, cv, scales, ei, bi, partial + i * num_tiles,
+                                        beta1, omb1);
 }
 
 // ---------------------------------------------------------------------------
@@ -2067,13 +2267,16 @@ static void launch_worker_t(const DeviceTables &tb, int64_t num_tiles, const flo
 {
     const float omb1 = 1.0f - beta1;
     if constexpr (PACKED) {
-        const int64_t groups = (n_local + group - 1) / group;
-        const int64_t items = groups * num_tiles;
-        const int64_t blocks = worker_grid(items, kMaxWorkerGridBlocks);
-        hipLaunchKernelGGL((k_worker_pass<PACKED, G>), dim3((unsigned)blocks), dim3(kWorkerBlock),
-                           0, s, tb.tiles, num_tiles, m, m_bits, m_scales,
-                           (const typename G::T *)g, g_ld, err, err_ld, scales, scales_ld, bits,
-                           bits_ld, partial, n_local, group, items, beta1, omb1);
+        const int64_t items = (int64_t)n_local * tb.num_blocks;
+        for (int64_t base = 0; base < items; base += kMaxPassItems) {
+            const int64_t count = std::min(items - base, kMaxPassItems);
+            hipLaunchKernelGGL((k_worker_pass<PACKED, G>),
+                               dim3((unsigned)worker_grid(count, kMaxPassItems)),
+                               dim3(kWave * kPassWaves<G>), kPassIdleLds<G>, s, tb.tiles,
+                               tb.blocks, tb.num_blocks, fast_div(tb.num_blocks), tb.padded_len,
+                               num_tiles, m, m_bits, m_scales, (const typename G::T *)g, g_ld, err, err_ld, scales,
+                               scales_ld, bits, bits_ld, partial, base, count, beta1, omb1);
+        }
     } else {
         (void)m_bits;
         (void)m_scales;

@@ -1,0 +1,95 @@
+"""Layouts whose 1024-element blocks hold several short tiles: ragged and
+one-word tensors, chunks of one word, a last block that ends early, against
+the CPU oracle in a free run of every pass.  Padding elements hold values that
+would show in any sum or store that took them in (gradients: NaN)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from parity_util import check_bits, check_fp, check_scales, host
+
+pytestmark = pytest.mark.gpu
+
+PAD = 7.5
+
+
+def _sizes(seed, count, lo, hi):
+    rng = np.random.default_rng(seed)
+    return [int(a) for a in rng.integers(lo, hi, size=count)]
+
+
+CASES = [
+    ("one-word tensors", [64] * 16 + [1] * 20 + [63, 65, 127], 1),     # 16 tiles in a block
+    ("up to 200", _sizes(1, 90, 1, 200), 2),
+    ("up to 2500", _sizes(2, 40, 1, 2500), 3),
+    ("one-word chunks", [5000, 0, 1024, 3000, 64, 1], 40),             # n > 32
+    ("full blocks at the end of short ones", [64, 960, 1024, 4096, 1000, 24], 1),
+    ("one full block", [1024], 1),
+    ("short chunks, 32 workers", _sizes(3, 12, 500, 9000), 32),
+]
+
+
+@pytest.mark.parametrize("grad_dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("name,numel,n", CASES)
+def test_short_tiles_free_running(dev, name, numel, n, packed, grad_dtype):
+    import paper_2102_02888_amd as ob
+    wl = synth.Workload(name=name, numel=numel, n=n, warmup_steps=2, steps=3)
+    L = oracle.Layout(numel, n)
+    plan = ob.Plan(numel, n)
+    mask = L.real_mask()
+    pad = torch.from_numpy(~mask).to(dev)
+    st = ob.State(plan, dev, grad_dtype=grad_dtype, packed_momentum=packed)
+    x = synth.host_params(wl, L.D)
+    x[~mask] = 0
+    st.x.copy_(torch.from_numpy(x))
+    padded = (st.x, st.m, st.v, st.worker_err, st.server_err)
+    for t in padded:
+        t[..., pad] = PAD
+
+    def grads(t):
+        gt = torch.from_numpy(synth.host_grads(wl, L.D, L.tensor_off, t)).to(grad_dtype)
+        st.grads.copy_(gt.to(dev))
+        st.grads[:, pad] = float("nan")
+        return gt.float().numpy()
+
+    m, v = np.zeros(L.D, np.float32), np.zeros(L.D, np.float32)
+    for t in (1, 2):
+        g = grads(t)
+        oracle.warmup_step(L, x, m, v, g, n, wl.lr, wl.beta1, wl.beta2, wl.eps, 0, t)
+        st.warmup(wl.lr, wl.beta1, wl.beta2, wl.eps, t)
+    norm = st.variance_l1_norm()
+    assert abs(norm - oracle.l1_norm(L, host(st.v))) <= 1e-12 * norm
+    ref = oracle.State(L, x, m, v)
+    for t in (3, 4, 5):
+        g = grads(t)
+        ref.step(g, wl.lr, wl.beta1, wl.eps)
+        st.step(wl.lr, wl.beta1, wl.eps)
+        torch.cuda.synchronize()
+        check_bits("worker bits", host(st.worker_bits), ref.wbits)
+        check_bits("server bits", host(st.server_bits), ref.sbits)
+        check_scales("worker scales", host(st.worker_scales), ref.wscales)
+        check_scales("server scales", host(st.server_scales), ref.sscales)
+    for what, a, b in (("x", st.x, ref.x), ("m", st.momentum(), ref.m),
+                       ("worker delta", st.worker_delta(), ref.delta),
+                       ("server delta", st.server_delta(), ref.delta_bar)):
+        check_fp(what, host(a), b, mask=mask)
+    # the comparison steps on the same layout
+    m, v, x = host(st.momentum()).copy(), host(st.v).copy(), host(st.x).copy()
+    st.m.copy_(torch.from_numpy(m))
+    g = grads(6)
+    oracle.step_uncompressed(L, x, m, v, g, wl.lr, wl.beta1, wl.eps)
+    st.step_uncompressed(wl.lr, wl.beta1, wl.eps)
+    dec = oracle.decode_message(L, host(st.server_bits), host(st.server_scales))
+    oracle.warmup_step(L, x, m, v, dec[None, :].copy(), 1, wl.lr, wl.beta1, wl.beta2, wl.eps, 0, 7)
+    ob.onebit_adam_message_step(plan, st.x, st.m, st.v, st.server_bits, st.server_scales, wl.lr,
+                                wl.beta1, wl.beta2, wl.eps, 0, 7)
+    torch.cuda.synchronize()
+    check_fp("x", host(st.x), x, mask=mask)
+    check_fp("m", host(st.m), m, mask=mask)
+    check_fp("v", host(st.v), v, mask=mask)
+    for t in (st.x, st.v, st.worker_err, st.server_err):
+        assert bool((t[..., pad] == PAD).all()), "a padding element was written"
+    plan.close()
