@@ -235,10 +235,10 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
     // device allocation.
     const size_t tiles_bytes = round_up((size_t)p->T * sizeof(Tile) + 1, 256);
     const size_t order_bytes = round_up((size_t)p->T * sizeof(int32_t) + 1, 256);
-    const size_t seg_bytes = round_up((size_t)p->S * sizeof(int64_t), 256);
+    const size_t seg_bytes = round_up((size_t)p->S * sizeof(onebit::Segment), 256);
     const size_t sblock_bytes = round_up((size_t)server_block_count * sizeof(int32_t) + 1, 256);
     const size_t seg0 = tiles_bytes + order_bytes;
-    const size_t sblocks0 = seg0 + 3 * seg_bytes;
+    const size_t sblocks0 = seg0 + seg_bytes;
     const size_t blocks0 = sblocks0 + sblock_bytes;
     const size_t total = blocks0 + round_up((size_t)num_blocks * sizeof(onebit::Block) + 1, 256);
     std::unique_ptr<char, void (*)(void *)> host((char *)std::malloc(total), std::free);
@@ -250,11 +250,12 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
     // one another at multiples of 64 elements with no gap).
     Tile *tiles = (Tile *)host.get();
     onebit::Block *blocks = (onebit::Block *)(host.get() + blocks0);
-    int64_t *seg_len = (int64_t *)(host.get() + seg0 + 2 * seg_bytes);
+    onebit::Segment *segs = (onebit::Segment *)(host.get() + seg0);
     int64_t blk = -1;
     for (int64_t q = 0, t = 0; q < p->S; ++q) {
         const int64_t en = p->seg_end[q];
-        seg_len[q] = en - p->seg_begin[q];
+        segs[q] = onebit::Segment{en - p->seg_begin[q], (int32_t)p->seg_tile_begin[q],
+                                  (int32_t)(p->seg_tile_end[q] - p->seg_tile_begin[q])};
         for (int64_t s = p->seg_begin[q]; s < en; ++t) {
             const int64_t next = std::min<int64_t>(en, (s / kTileElems + 1) * kTileElems);
             tiles[t].start = s;
@@ -291,8 +292,6 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
     }
     p->chunk_tile_begin[n] = pos;
     p->chunk_block_begin[n] = sb;
-    std::memcpy(host.get() + seg0, p->seg_tile_begin.data(), p->S * sizeof(int64_t));
-    std::memcpy(host.get() + seg0 + seg_bytes, p->seg_tile_end.data(), p->S * sizeof(int64_t));
     // Every host allocation is done; from here on nothing throws.
     e = hipMalloc(&p->dev_mem, total);
     if (e != hipSuccess)
@@ -306,9 +305,7 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
     char *base = (char *)p->dev_mem;
     p->tb.tiles = (const Tile *)base;
     p->tb.chunk_tiles = (const int32_t *)(base + tiles_bytes);
-    p->tb.seg_tile_begin = (const int64_t *)(base + seg0);
-    p->tb.seg_tile_end = (const int64_t *)(base + seg0 + seg_bytes);
-    p->tb.seg_len = (const int64_t *)(base + seg0 + 2 * seg_bytes);
+    p->tb.segs = (const onebit::Segment *)(base + seg0);
     p->tb.server_blocks = (const int32_t *)(base + sblocks0);
     p->tb.blocks = (const onebit::Block *)(base + blocks0);
     p->tb.num_blocks = num_blocks;
@@ -372,8 +369,8 @@ int run_worker(const onebit_plan_s *p, const float *m, const uint64_t *m_bits,
                                            grad_ld, worker_err, err_ld, worker_scales, scales_ld,
                                            worker_bits, bits_ld, part, n_local, group, beta1, s),
                 "worker kernel launch");
-    TRY_HIP(onebit::launch_finalize(p->tb, p->max_seg_tiles, (int64_t)n_local * p->S, p->S, 0,
-                                    p->n, 0, 0, part, p->T, worker_scales, scales_ld, s),
+    TRY_HIP(onebit::launch_finalize(p->tb, p->max_seg_tiles, p->S, n_local, p->n, 0, 0, part, p->T,
+                                    worker_scales, scales_ld, s),
             "worker scale kernel launch");
     return ONEBIT_OK;
 }
@@ -444,9 +441,8 @@ int run_server(const onebit_plan_s *p, int32_t server_begin, int32_t server_end,
                                            server_bits, part, p->K, server_begin, nown, tables,
                                            flags, p->tb.server_blocks + bb, nb, s),
                 "server kernel launch");
-    TRY_HIP(onebit::launch_finalize(p->tb, p->max_seg_tiles,
-                                    (int64_t)p->K * (server_end - server_begin), p->S, 1, p->n,
-                                    server_begin, server_end, part, p->T, server_scales, 0, s),
+    TRY_HIP(onebit::launch_finalize(p->tb, p->max_seg_tiles, owned, 1, p->n, server_begin, nown,
+                                    part, p->T, server_scales, 0, s),
             "server scale kernel launch");
     return ONEBIT_OK;
 }

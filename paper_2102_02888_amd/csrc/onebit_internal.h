@@ -36,6 +36,13 @@ struct Block {
     int32_t whole;    // 1: one tile of kTileElems elements
 };
 
+// A segment's range of the tile list and its length.
+struct Segment {
+    int64_t len;
+    int32_t tile;   // its first tile
+    int32_t tiles;  // 0 for an empty segment
+};
+
 // Device-side layout tables owned by a plan.
 struct DeviceTables {
     const Tile *tiles;             // [T], in address (segment) order
@@ -43,9 +50,7 @@ struct DeviceTables {
     int64_t num_blocks;            // ceil(D / kTileElems)
     int64_t padded_len;            // D
     const int32_t *chunk_tiles;    // [T], tile ids in chunk-major order
-    const int64_t *seg_tile_begin; // [S]
-    const int64_t *seg_tile_end;   // [S]
-    const int64_t *seg_len;        // [S]
+    const Segment *segs;           // [S]
     const int32_t *server_blocks;  // chunk owners' shared-table workgroups, chunk-major
                                    // (entries of onebit_grid.h's server_block_entry)
 };
@@ -103,15 +108,14 @@ hipError_t launch_l1_norm(const DeviceTables &tb, int64_t num_tiles, const float
 hipError_t launch_decode(const DeviceTables &tb, int64_t num_tiles, const uint64_t *bits,
                          const float *scales, float *out, hipStream_t s);
 
-// Segment scales from per-tile partial sums.  Worker form (server_form = 0):
-// num_pairs = rows * num_segments, scale[i*scales_ld + q] from
-// partial[i*part_ld + tiles of q].  Server form: num_pairs = K * (je - jb),
-// segments k*n + j for j in [jb, je), one row.  max_seg_tiles picks a wave
-// or a block per pair.
-hipError_t launch_finalize(const DeviceTables &tb, int64_t max_seg_tiles, int64_t num_pairs,
-                           int64_t num_segments, int server_form, int n, int jb, int je,
-                           const double *partial, int64_t part_ld, float *scales,
-                           int64_t scales_ld, hipStream_t s);
+// Segment scales from per-tile partial sums.  Worker form (cnt = 0): all
+// num_segments segments of each of `rows` rows, scale[i*scales_ld + q] from
+// partial[i*part_ld + tiles of q].  Server form: segments k*n + j for
+// j in [jb, jb + cnt) and every tensor k, one row.  max_seg_tiles picks the
+// lanes per segment.
+hipError_t launch_finalize(const DeviceTables &tb, int64_t max_seg_tiles, int64_t num_segments,
+                           int64_t rows, int n, int jb, int cnt, const double *partial,
+                           int64_t part_ld, float *scales, int64_t scales_ld, hipStream_t s);
 
 // Bytes of the chunk owners' lookup tables for `segments` owned segments.
 size_t server_table_bytes(int n, int64_t segments);

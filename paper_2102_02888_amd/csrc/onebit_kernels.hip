@@ -1047,61 +1047,65 @@ __global__ __launch_bounds__(kRowBlock) void k_worker_rows(
 // ---------------------------------------------------------------------------
 // Scale finalize: scale = fp32(sqrt(sum over the segment's tiles / len)),
 // summed in a fixed order (so results do not depend on scheduling); empty
-// segments get 0.  THREADS lanes cooperate on one (row, segment) pair: a
-// wave when segments have few tiles, a whole block when they have many.
+// segments get 0.  LANES lanes cooperate on one segment of one row, fewer for
+// segments of few tiles (launch_finalize): with a wave for each, the 2 million
+// (row, segment) pairs of 2,000 tensors of 64 to 8192 elements with n = 32
+// took 470 us of a 900 us step, which is 422 us with a lane for each; the
+// 5,000-tensor workload's step went from 10.05 to 9.98 ms with 16 lanes.
 // ---------------------------------------------------------------------------
-template <int THREADS>
-__device__ __forceinline__ float finalize_one(const double *__restrict__ part, int64_t tb,
-                                              int64_t te, int64_t len, double *red)
+template <int LANES>
+__device__ __forceinline__ float finalize_one(const double *__restrict__ part, const Segment &seg,
+                                              double *red)
 {
-    const int tid = threadIdx.x % THREADS;
+    const int tid = threadIdx.x % LANES;
+    part += seg.tile;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int64_t t = tb + tid;
-    for (; t + 3 * THREADS < te; t += 4 * THREADS) {
+    int t = tid;
+    for (; t + 3 * LANES < seg.tiles; t += 4 * LANES) {
         s0 += part[t];
-        s1 += part[t + THREADS];
-        s2 += part[t + 2 * THREADS];
-        s3 += part[t + 3 * THREADS];
+        s1 += part[t + LANES];
+        s2 += part[t + 2 * LANES];
+        s3 += part[t + 3 * LANES];
     }
-    for (; t < te; t += THREADS) s0 += part[t];
-    double s = wave_sum((s0 + s1) + (s2 + s3));
-    if (THREADS > kWave) {
+    for (; t < seg.tiles; t += LANES) s0 += part[t];
+    double s = (s0 + s1) + (s2 + s3);
+#pragma unroll
+    for (int off = (LANES < kWave ? LANES : kWave) / 2; off >= 1; off >>= 1)
+        s += __shfl_xor(s, off, kWave);
+    if (LANES > kWave) {
         const int wv = tid / kWave;
         if ((tid & (kWave - 1)) == 0) red[wv] = s;
         __syncthreads();
         s = red[0];
-        for (int w = 1; w < THREADS / kWave; ++w) s += red[w];
+        for (int w = 1; w < LANES / kWave; ++w) s += red[w];
     }
-    return len > 0 ? (float)__builtin_sqrt(s / (double)len) : 0.0f;
+    return seg.len > 0 ? (float)__builtin_sqrt(s / (double)seg.len) : 0.0f;
 }
 
-// Pair p -> (row i, segment q).  Worker form: all S segments of each row.
-// Server form: segments k*n + j for j in [jb, je) and every tensor k.
-template <int THREADS>
-__global__ __launch_bounds__(kBlock) void k_finalize(
-    DeviceTables tb, int64_t num_pairs, int64_t num_segments, int server_form, int n, int jb,
-    int je, const double *__restrict__ partial, int64_t part_ld, float *__restrict__ scales,
-    int64_t scales_ld)
+// count segments per row; cnt = 0: segment p is the p-th, else (server form)
+// segments k*n + j for j in [jb, jb + cnt) and every tensor k, in that order.
+template <int LANES>
+__global__ __launch_bounds__(kBlock) void k_finalize(const Segment *__restrict__ segs,
+                                                     uint32_t count, int64_t rows, int n, int jb,
+                                                     int cnt, const double *__restrict__ partial,
+                                                     int64_t part_ld, float *__restrict__ scales,
+                                                     int64_t scales_ld)
 {
     __shared__ double red[kBlock / kWave];
-    // THREADS lanes per pair; the grid may be smaller than the pair count, so
-    // each group of lanes strides over pairs (uniform per block or per wave)
-    const int64_t stride = (int64_t)gridDim.x * (kBlock / THREADS);
-    for (int64_t p = (int64_t)blockIdx.x * (kBlock / THREADS) + threadIdx.x / THREADS;
-         p < num_pairs; p += stride) {
-        int64_t i, q;
-        if (server_form) {
-            const int cnt = je - jb;
-            i = 0;
-            q = (p / cnt) * n + jb + (p % cnt);
-        } else {
-            i = p / num_segments;
-            q = p % num_segments;
+    // LANES lanes per segment; the grid may be smaller than the rows or the
+    // segments, so each group of lanes strides over both (uniform per block
+    // or per wave where it has to be)
+    constexpr uint32_t kPer = kBlock / LANES;
+    for (int64_t i = blockIdx.y; i < rows; i += gridDim.y) {
+        for (uint32_t p = blockIdx.x * kPer + threadIdx.x / LANES; p < count;
+             p += gridDim.x * kPer) {
+            const uint32_t q = cnt == 0 || cnt == n
+                                   ? p
+                                   : p / (uint32_t)cnt * (uint32_t)n + jb + p % (uint32_t)cnt;
+            const float s = finalize_one<LANES>(partial + i * part_ld, segs[q], red);
+            if (threadIdx.x % LANES == 0) scales[i * scales_ld + q] = s;
+            if (LANES > kWave) __syncthreads();  // red is reused by the next segment
         }
-        const float s = finalize_one<THREADS>(partial + i * part_ld, tb.seg_tile_begin[q],
-                                              tb.seg_tile_end[q], tb.seg_len[q], red);
-        if (threadIdx.x % THREADS == 0) scales[i * scales_ld + q] = s;
-        if (THREADS > kWave) __syncthreads();  // red is reused by the next pair
     }
 }
 
@@ -2221,6 +2225,9 @@ __global__ __launch_bounds__(kBlock) void k_l1_final(const double *__restrict__ 
     if (threadIdx.x == 0) out[0] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
+// Rows of a two-dimensional grid (kernels stride beyond it).
+constexpr int64_t kMaxGridRows = 65535;
+
 // Workgroups (of kWavesPerBlock waves) for one wave per item.
 inline int64_t blocks_for(int64_t waves) { return xcd_grid(waves, kWavesPerBlock); }
 
@@ -2399,24 +2406,35 @@ hipError_t launch_decode(const DeviceTables &tb, int64_t num_tiles, const uint64
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const DeviceTables &tb, int64_t max_seg_tiles, int64_t num_pairs,
-                           int64_t num_segments, int server_form, int n, int jb, int je,
-                           const double *partial, int64_t part_ld, float *scales,
-                           int64_t scales_ld, hipStream_t s)
+template <int LANES>
+static void launch_finalize_t(const DeviceTables &tb, int64_t num_segments, int64_t rows, int n,
+                              int jb, int cnt, const double *partial, int64_t part_ld,
+                              float *scales, int64_t scales_ld, hipStream_t s)
 {
-    if (num_pairs <= 0) return hipSuccess;
-    if (max_seg_tiles > 4 * kWave) {
-        hipLaunchKernelGGL(k_finalize<kBlock>, dim3((unsigned)std::min(num_pairs, kMaxGridBlocks)),
-                           dim3(kBlock), 0, s, tb,
-                           num_pairs, num_segments, server_form, n, jb, je, partial, part_ld,
-                           scales, scales_ld);
-    } else {
-        hipLaunchKernelGGL(k_finalize<kWave>,
-                           dim3((unsigned)std::min(blocks_for(num_pairs), kMaxGridBlocks)),
-                           dim3(kBlock), 0, s,
-                           tb, num_pairs, num_segments, server_form, n, jb, je, partial, part_ld,
-                           scales, scales_ld);
-    }
+    const int64_t per = kBlock / LANES;
+    const dim3 grid((unsigned)std::min((num_segments + per - 1) / per, kMaxGridBlocks),
+                    (unsigned)std::min(rows, kMaxGridRows));
+    hipLaunchKernelGGL(k_finalize<LANES>, grid, dim3(kBlock), 0, s, tb.segs,
+                       (uint32_t)num_segments, rows, n, jb, cnt, partial, part_ld, scales,
+                       scales_ld);
+}
+
+hipError_t launch_finalize(const DeviceTables &tb, int64_t max_seg_tiles, int64_t num_segments,
+                           int64_t rows, int n, int jb, int cnt, const double *partial,
+                           int64_t part_ld, float *scales, int64_t scales_ld, hipStream_t s)
+{
+    if (num_segments <= 0 || rows <= 0) return hipSuccess;
+    // A workgroup for segments above 256 tiles (there are few of them, and
+    // their latency counts).  Below that as many lanes as leave a lane at most
+    // 16 partial sums, but a whole wave, with fewer dependent steps, while all
+    // the pairs' waves are on the chip at once anyway.
+    const bool few = num_segments * rows <= 4096;
+    const auto launch = max_seg_tiles > 4 * kWave            ? launch_finalize_t<kBlock>
+                        : max_seg_tiles > 4 && few           ? launch_finalize_t<kWave>
+                        : max_seg_tiles > kWave              ? launch_finalize_t<16>
+                        : max_seg_tiles > 4                  ? launch_finalize_t<8>
+                                                             : launch_finalize_t<1>;
+    launch(tb, num_segments, rows, n, jb, cnt, partial, part_ld, scales, scales_ld, s);
     return hipGetLastError();
 }
 
