@@ -464,7 +464,7 @@ int run_update(const onebit_plan_s *p, const uint64_t *server_bits, const float 
                float *x, float *m_out, const float *v_frozen, float lr, float eps, hipStream_t s)
 {
     if (p->T == 0) return ONEBIT_OK;
-    TRY_HIP(onebit::launch_update(p->tb, p->T, server_bits, server_scales, x, m_out, v_frozen,
+    TRY_HIP(onebit::launch_update(p->tb, server_bits, server_scales, x, m_out, v_frozen,
                                   lr, eps, s),
             "update kernel launch");
     return ONEBIT_OK;
@@ -738,7 +738,7 @@ int onebit_adam_message_step(onebit_plan p, float *x, float *m, float *v, const 
         bc1 = (float)(1.0 - std::pow((double)beta1, (double)step));
         bc2 = (float)(1.0 - std::pow((double)beta2, (double)step));
     }
-    TRY_HIP(onebit::launch_adam_message(p->tb, p->T, bits, scales, x, m, v, lr, beta1, beta2, eps,
+    TRY_HIP(onebit::launch_adam_message(p->tb, bits, scales, x, m, v, lr, beta1, beta2, eps,
                                         bias_correction ? 1 : 0, bc1, bc2, (hipStream_t)stream),
             "message Adam kernel launch");
     return ONEBIT_OK;

@@ -92,10 +92,9 @@ hipError_t launch_worker_pass(const DeviceTables &tb, int64_t num_tiles, const f
                               int64_t bits_ld, double *partial, int n_local, int group,
                               float beta1, hipStream_t s);
 
-hipError_t launch_adam_message(const DeviceTables &tb, int64_t num_tiles, const uint64_t *bits,
-                               const float *scales, float *x, float *m, float *v, float lr,
-                               float beta1, float beta2, float eps, int use_bc, float bc1,
-                               float bc2, hipStream_t s);
+hipError_t launch_adam_message(const DeviceTables &tb, const uint64_t *bits, const float *scales,
+                               float *x, float *m, float *v, float lr, float beta1, float beta2,
+                               float eps, int use_bc, float bc1, float bc2, hipStream_t s);
 
 hipError_t launch_uncompressed(const DeviceTables &tb, int64_t num_tiles, float *x, float *m,
                                const float *v, const void *g, int grad_dtype, int64_t g_ld,
@@ -136,9 +135,9 @@ hipError_t launch_server_pass(const DeviceTables &tb, int64_t tile_begin, int64_
                               int nown, double *tables, int32_t *flags,
                               const int32_t *server_blocks, int64_t num_blocks, hipStream_t s);
 
-hipError_t launch_update(const DeviceTables &tb, int64_t num_tiles, const uint64_t *sbits,
-                         const float *sscales, float *x, float *m_out, const float *v,
-                         float lr, float eps, hipStream_t s);
+hipError_t launch_update(const DeviceTables &tb, const uint64_t *sbits, const float *sscales,
+                         float *x, float *m_out, const float *v, float lr, float eps,
+                         hipStream_t s);
 
 // The library's own scratch memory, for callers that cannot allocate: a
 // static device array of kScratchBytes on every device the library runs on,

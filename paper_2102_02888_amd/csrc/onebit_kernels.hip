@@ -404,86 +404,112 @@ __device__ __forceinline__ void warmup_update(const double (&sum)[kSubBlocks][4]
 }
 
 // ---------------------------------------------------------------------------
-// Adam step whose gradient is a decoded message (g = bit ? scale : -scale);
-// the "Adam(1-bit Naive)" comparison variant of Section 7.2 updates m and v
-// from the compressed gradient this way.  Loads first, then stores.
+// One sub-block of a block as a wave of the update-like passes sees it: which
+// elements are real, and the sign word and scale of each lane's segment.  The
+// caller issues its own loads first; INSIDE as in ldb4.
 // ---------------------------------------------------------------------------
-template <bool FULL, int SB>
-__device__ __forceinline__ void adam_message_tile(const Tile &tile, int lane, int sb0,
-                                                  const uint64_t *__restrict__ bits, float s,
-                                                  float *__restrict__ x, float *__restrict__ m,
-                                                  float *__restrict__ v, float lr, float beta1,
-                                                  float omb1, float beta2, float omb2,
-                                                  float eps, int use_bc, float bc1, float bc2)
+struct Lane4 {
+    float s;       // the scale of the lane's segment
+    uint32_t nib;  // the lane's 4 sign bits (bits above are undefined)
+    int valid;     // how many of its 4 elements are real
+};
+
+template <bool WHOLE>
+__device__ __forceinline__ Lane4 lane_message(const Tile *__restrict__ tiles, const Block &rec,
+                                              int64_t base, int li, int lim, uint64_t word, float s0,
+                                              const float *__restrict__ scales)
 {
-    const int len = tile.len;
-    const int64_t base = tile.start;
-    uint64_t word[SB];
-    v4f xv[SB], mv[SB], vv[SB];
-#pragma unroll
-    for (int b = 0; b < SB; ++b) {
-        const int sb = sb0 + b;
-        const int li = sb * (kWave * 4) + 4 * lane;
-        word[b] = (FULL || li < len) ? bits[(base >> 6) + 4 * sb + (lane >> 4)] : 0ull;
-        xv[b] = ld4<FULL>(x + base, li, len);
-        mv[b] = ld4<FULL>(m + base, li, len);
-        vv[b] = ld4<FULL>(v + base, li, len);
-    }
-#pragma unroll
-    for (int b = 0; b < SB; ++b) {
-        const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
-        const uint32_t nib = (uint32_t)(word[b] >> (4 * (lane & 15))) & 0xFu;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float gbar = ((nib >> c) & 1u) ? s : -s;
-            float mn = beta1 * mv[b][c];
-            mn = mn + omb1 * gbar;
-            const float gsq = gbar * gbar;
-            float vn = beta2 * vv[b][c];
-            vn = vn + omb2 * gsq;
-            float mh = mn, vh = vn;
-            if (use_bc) {
-                mh = mn / bc1;
-                vh = vn / bc2;
-            }
-            const float denom = __builtin_sqrtf(vh) + eps;
-            const float ratio = mh / denom;
-            const float step = lr * ratio;
-            xv[b][c] = xv[b][c] - step;
-            mv[b][c] = mn;
-            vv[b][c] = vn;
+    Lane4 r{s0, (uint32_t)(word >> (li & 63)), 4};
+    if (!WHOLE) {
+        r.valid = 0;
+        if (li < lim) {
+            const Tile t = block_word_tile(tiles, rec, li >> 6);
+            r.valid = tile_valid4(t, base + li);
+            r.s = scales[t.seg];
         }
-        st4<FULL>(x + base, li, len, xv[b]);
-        st4<FULL>(m + base, li, len, mv[b]);
-        st4<FULL>(v + base, li, len, vv[b]);
     }
+    return r;
 }
 
-// One 256-element sub-block per wave, four waves per tile, as in the update
-// (fewer bytes in flight per wave).
-constexpr int kAdamMessageSubBlocks = 1;
-constexpr int kAdamMessageWavesPerTile = kSubBlocks / kAdamMessageSubBlocks;
+// ---------------------------------------------------------------------------
+// Adam step whose gradient is a decoded message (g = bit ? scale : -scale);
+// the "Adam(1-bit Naive)" comparison variant of Section 7.2 updates m and v
+// from the compressed gradient this way.  A workgroup takes one block, one
+// 256-element sub-block per wave, as in the update.  Loads first, then stores.
+// Five workgroups per CU, held by unused LDS (3 KB of loads per wave, 15 KB per
+// SIMD): the naive step on 200 fp16 tensors 371.6 us at eight, 367.8 at five.
+// ---------------------------------------------------------------------------
+template <bool WHOLE>
+__device__ __forceinline__ void adam_message_sub(const Lane4 &l, int li, v4f xv, v4f mv, v4f vv,
+                                                 float *__restrict__ x, float *__restrict__ m,
+                                                 float *__restrict__ v, float lr, float beta1,
+                                                 float omb1, float beta2, float omb2, float eps,
+                                                 int use_bc, float bc1, float bc2)
+{
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const float gbar = with_sign(l.s, l.nib, c);
+        float mn = beta1 * mv[c];
+        mn = mn + omb1 * gbar;
+        const float gsq = gbar * gbar;
+        float vn = beta2 * vv[c];
+        vn = vn + omb2 * gsq;
+        float mh = mn, vh = vn;
+        if (use_bc) {
+            mh = mn / bc1;
+            vh = vn / bc2;
+        }
+        const float denom = __builtin_sqrtf(vh) + eps;
+        const float ratio = mh / denom;
+        const float step = lr * ratio;
+        xv[c] = xv[c] - step;
+        mv[c] = mn;
+        vv[c] = vn;
+    }
+    stb4<WHOLE>(x, li, l.valid, xv);
+    stb4<WHOLE>(m, li, l.valid, mv);
+    stb4<WHOLE>(v, li, l.valid, vv);
+}
 
 __global__ __launch_bounds__(kBlock) void k_adam_message(
-    const Tile *__restrict__ tiles, int64_t num_tiles, const uint64_t *__restrict__ bits,
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
+    int64_t num_blocks, int64_t padded_len, const uint64_t *__restrict__ bits,
     const float *__restrict__ scales, float *__restrict__ x, float *__restrict__ m,
     float *__restrict__ v, float lr, float beta1, float omb1, float beta2, float omb2, float eps,
     int use_bc, float bc1, float bc2)
 {
-    constexpr int SB = kAdamMessageSubBlocks;
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t w = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t t = w / kAdamMessageWavesPerTile;
-    const int sb0 = (int)(w % kAdamMessageWavesPerTile) * SB;
-    if (t >= num_tiles) return;
-    const Tile tile = tiles[t];
-    const float s = scales[tile.seg];
-    if (tile.len == kTileElems)
-        adam_message_tile<true, SB>(tile, lane, sb0, bits, s, x, m, v, lr, beta1, omb1, beta2,
-                                    omb2, eps, use_bc, bc1, bc2);
+    const int64_t blk = block_base + xcd_block();
+    if (blk >= num_blocks) return;
+    const int64_t base = blk * kTileElems;
+    const int64_t room = padded_len - base;
+    const int lim = room < kTileElems ? (int)room : kTileElems;
+    const int li = (threadIdx.x >> 6) * (kWave * 4) + 4 * lane;
+    x += base;
+    m += base;
+    v += base;
+    uint64_t word = 0;
+    v4f xv, mv, vv;
+    if (lim == kTileElems || li < lim) word = bits[(base + li) >> 6];
+    if (lim == kTileElems) {
+        xv = ldb4<true>(x, li, lim);
+        mv = ldb4<true>(m, li, lim);
+        vv = ldb4<true>(v, li, lim);
+    } else {
+        xv = ldb4<false>(x, li, lim);
+        mv = ldb4<false>(m, li, lim);
+        vv = ldb4<false>(v, li, lim);
+    }
+    const Block rec = load_block(blocks, blk);
+    const float s0 = scales[rec.seg];
+    if (rec.whole)
+        adam_message_sub<true>(lane_message<true>(tiles, rec, base, li, lim, word, s0, scales), li,
+                               xv, mv, vv, x, m, v, lr, beta1, omb1, beta2, omb2, eps, use_bc, bc1,
+                               bc2);
     else
-        adam_message_tile<false, SB>(tile, lane, sb0, bits, s, x, m, v, lr, beta1, omb1, beta2,
-                                     omb2, eps, use_bc, bc1, bc2);
+        adam_message_sub<false>(lane_message<false>(tiles, rec, base, li, lim, word, s0, scales),
+                                li, xv, mv, vv, x, m, v, lr, beta1, omb1, beta2, omb2, eps, use_bc,
+                                bc1, bc2);
 }
 
 // ---------------------------------------------------------------------------
@@ -652,6 +678,10 @@ __global__ __launch_bounds__(kRowBlock) void k_warmup(
 // An fp32 momentum (the first compression step) is read once per tile for all
 // local workers instead, by k_worker_rows.
 // ---------------------------------------------------------------------------
+// Unused dynamic LDS that lets `groups` workgroups of a kernel onto a CU at
+// once (160 KB of LDS, allocated in steps of 512 bytes or less).
+constexpr int idle_lds(int groups) { return 160 * 1024 / groups / 512 * 512; }
+
 // Sub-blocks per wave of the first compression step's row walk.
 constexpr int kWorkerSubBlocks = 2;
 static_assert(kSubBlocks / kWorkerSubBlocks == kWorkerWavesPerBlock,
@@ -667,7 +697,7 @@ constexpr int kPassWaves = kSubBlocks / kPassSubBlocks<G>;
 // Items of one launch: at most 256 threads each, below 2^32 work-items.
 constexpr int64_t kMaxPassItems = (int64_t)3 << 22;
 template <class G>
-constexpr int kPassIdleLds = sizeof(typename G::T) == 2 ? 15872 : 0;
+constexpr int kPassIdleLds = sizeof(typename G::T) == 2 ? idle_lds(10) - 512 : 0;
 
 // The shared momentum m_{t-1} of sub-blocks sb0 .. sb0+SB-1 of the tile times
 // beta1.  PACKED: m_{t-1} is the previous step's gathered server message,
@@ -2037,75 +2067,72 @@ __global__ __launch_bounds__(kSplitWaves * kWave) void k_server_split(
 // ---------------------------------------------------------------------------
 // Decompress + preconditioned update: x -= lr * (+-scale) / sqrt(v + eps).
 // ---------------------------------------------------------------------------
-// Every load of a wave's part of the tile is issued before its first store.
+// Every load of a wave's part of a block is issued before its first store.
 // Kernels here keep that order wherever a wave would otherwise re-read data
 // after storing: on
 // this hardware a variant that interleaved the sign-word loads with the
 // stores returned wrong words for about 1% of the elements of a 334M-element
 // launch (exact on small grids), and the loads-first form is exact.
-// Sub-blocks sb0 .. sb0+SB-1 of the tile.
-template <bool FULL, int SB>
-__device__ __forceinline__ void update_tile(const Tile &tile, int lane, int sb0,
-                                            const uint64_t *__restrict__ sbits, float s,
-                                            float *__restrict__ x, float *__restrict__ m_out,
-                                            const float *__restrict__ v, float lr, float eps)
+template <bool WHOLE>
+__device__ __forceinline__ void update_sub(const Lane4 &l, int li, v4f xv, v4f vv,
+                                           float *__restrict__ x, float *__restrict__ m_out,
+                                           float lr, float eps)
 {
-    const int len = tile.len;
-    const int64_t base = tile.start;
-    uint64_t word[SB];
-    v4f xv[SB], vv[SB];
+    v4f mv;
 #pragma unroll
-    for (int b = 0; b < SB; ++b) {
-        const int sb = sb0 + b;
-        const int li = sb * (kWave * 4) + 4 * lane;
-        const bool in = FULL || li < len;
-        word[b] = in ? sbits[(base >> 6) + 4 * sb + (lane >> 4)] : 0ull;
-        xv[b] = ld4<FULL>(x + base, li, len);
-        vv[b] = ld4<FULL>(v + base, li, len);
+    for (int c = 0; c < 4; ++c) {
+        const float mbar = with_sign(l.s, l.nib, c);
+        const float denom = __builtin_sqrtf(vv[c] + eps);
+        const float ratio = mbar / denom;
+        const float step = lr * ratio;
+        xv[c] = xv[c] - step;
+        mv[c] = mbar;
     }
-#pragma unroll
-    for (int b = 0; b < SB; ++b) {
-        const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
-        const uint32_t nib = (uint32_t)(word[b] >> (4 * (lane & 15))) & 0xFu;
-        v4f mv;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float mbar = ((nib >> c) & 1u) ? s : -s;
-            const float denom = __builtin_sqrtf(vv[b][c] + eps);
-            const float ratio = mbar / denom;
-            const float step = lr * ratio;
-            xv[b][c] = xv[b][c] - step;
-            mv[c] = mbar;
-        }
-        st4<FULL>(x + base, li, len, xv[b]);
-        if (m_out) st4<FULL>(m_out + base, li, len, mv);
-    }
+    stb4<WHOLE>(x, li, l.valid, xv);
+    if (m_out) stb4<WHOLE>(m_out, li, l.valid, mv);
 }
 
-// One 256-element sub-block per wave, four waves per tile: each wave keeps
-// 2 KB of loads in flight instead of 8 KB (a whole tile), which the mix of
-// two read streams and one written stream favours: 0.667 -> 0.619 ms on the
+// A workgroup takes one block, one 256-element sub-block per wave: each wave
+// keeps 2 KB of loads in flight instead of 8 KB (a whole block), which the mix
+// of two read streams and one written stream favours: 0.667 -> 0.619 ms on the
 // BERT-Large shape, 1.112 -> 1.033 ms on the 5,000-tensor stress workload
-// (half a tile per wave: 0.640 and 1.070 ms), in one A/B process each.
-constexpr int kUpdateSubBlocks = 1;
-constexpr int kUpdateWavesPerTile = kSubBlocks / kUpdateSubBlocks;
-
+// (half a tile per wave: 0.640 and 1.070 ms), in one A/B process each.  Six
+// workgroups per CU, held by unused LDS, keep about 12 KB in flight per SIMD:
+// one GPU's share of a BERT-Large step (its own worker row, the update) 1.306
+// ms at eight, 1.293 at six, 1.366 at five.
 __global__ __launch_bounds__(kBlock) void k_update(
-    const Tile *__restrict__ tiles, int64_t num_tiles, const uint64_t *__restrict__ sbits,
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
+    int64_t num_blocks, int64_t padded_len, const uint64_t *__restrict__ sbits,
     const float *__restrict__ sscales, float *__restrict__ x, float *__restrict__ m_out,
     const float *__restrict__ v, float lr, float eps)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t w = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
-    const int64_t t = w / kUpdateWavesPerTile;
-    const int sb0 = (int)(w % kUpdateWavesPerTile) * kUpdateSubBlocks;
-    if (t >= num_tiles) return;
-    const Tile tile = tiles[t];
-    const float s = sscales[tile.seg];
-    if (tile.len == kTileElems)
-        update_tile<true, kUpdateSubBlocks>(tile, lane, sb0, sbits, s, x, m_out, v, lr, eps);
+    const int64_t blk = block_base + xcd_block();
+    if (blk >= num_blocks) return;
+    const int64_t base = blk * kTileElems;
+    const int64_t room = padded_len - base;
+    const int lim = room < kTileElems ? (int)room : kTileElems;
+    const int li = (threadIdx.x >> 6) * (kWave * 4) + 4 * lane;
+    x += base;
+    if (m_out) m_out += base;
+    uint64_t word = 0;
+    v4f xv, vv;
+    if (lim == kTileElems || li < lim) word = sbits[(base + li) >> 6];
+    if (lim == kTileElems) {
+        xv = ldb4<true>(x, li, lim);
+        vv = ldb4<true>(v + base, li, lim);
+    } else {
+        xv = ldb4<false>(x, li, lim);
+        vv = ldb4<false>(v + base, li, lim);
+    }
+    const Block rec = load_block(blocks, blk);
+    const float s0 = sscales[rec.seg];
+    if (rec.whole)
+        update_sub<true>(lane_message<true>(tiles, rec, base, li, lim, word, s0, sscales), li, xv,
+                         vv, x, m_out, lr, eps);
     else
-        update_tile<false, kUpdateSubBlocks>(tile, lane, sb0, sbits, s, x, m_out, v, lr, eps);
+        update_sub<false>(lane_message<false>(tiles, rec, base, li, lim, word, s0, sscales), li,
+                          xv, vv, x, m_out, lr, eps);
 }
 
 // ---------------------------------------------------------------------------
@@ -2346,16 +2373,17 @@ hipError_t launch_worker_pass(const DeviceTables &tb, int64_t num_tiles, const f
     return hipGetLastError();
 }
 
-hipError_t launch_adam_message(const DeviceTables &tb, int64_t num_tiles, const uint64_t *bits,
-                               const float *scales, float *x, float *m, float *v, float lr,
-                               float beta1, float beta2, float eps, int use_bc, float bc1,
-                               float bc2, hipStream_t s)
+hipError_t launch_adam_message(const DeviceTables &tb, const uint64_t *bits, const float *scales,
+                               float *x, float *m, float *v, float lr, float beta1, float beta2,
+                               float eps, int use_bc, float bc1, float bc2, hipStream_t s)
 {
     const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
-    hipLaunchKernelGGL(k_adam_message, dim3((unsigned)blocks_for(num_tiles * kAdamMessageWavesPerTile)),
-                       dim3(kBlock), 0, s,
-                       tb.tiles, num_tiles, bits, scales, x, m, v, lr, beta1, omb1, beta2, omb2,
-                       eps, use_bc, bc1, bc2);
+    for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
+        const int64_t count = launch_piece(tb.num_blocks, base);
+        hipLaunchKernelGGL(k_adam_message, dim3((unsigned)xcd_grid(count, 1)), dim3(kBlock),
+                           idle_lds(5), s, tb.tiles, tb.blocks, base, base + count, tb.padded_len,
+                           bits, scales, x, m, v, lr, beta1, omb1, beta2, omb2, eps, use_bc, bc1, bc2);
+    }
     return hipGetLastError();
 }
 
@@ -2510,13 +2538,16 @@ hipError_t launch_server_pass(const DeviceTables &tb, int64_t tile_begin, int64_
     return hipGetLastError();
 }
 
-hipError_t launch_update(const DeviceTables &tb, int64_t num_tiles, const uint64_t *sbits,
-                         const float *sscales, float *x, float *m_out, const float *v,
-                         float lr, float eps, hipStream_t s)
+hipError_t launch_update(const DeviceTables &tb, const uint64_t *sbits, const float *sscales,
+                         float *x, float *m_out, const float *v, float lr, float eps,
+                         hipStream_t s)
 {
-    hipLaunchKernelGGL(k_update, dim3((unsigned)blocks_for(num_tiles * kUpdateWavesPerTile)),
-                       dim3(kBlock), 0, s, tb.tiles,
-                       num_tiles, sbits, sscales, x, m_out, v, lr, eps);
+    for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
+        const int64_t count = launch_piece(tb.num_blocks, base);
+        hipLaunchKernelGGL(k_update, dim3((unsigned)xcd_grid(count, 1)), dim3(kBlock), idle_lds(6),
+                           s, tb.tiles, tb.blocks, base, base + count, tb.padded_len, sbits,
+                           sscales, x, m_out, v, lr, eps);
+    }
     return hipGetLastError();
 }
 
