@@ -772,8 +772,9 @@ int onebit_l1_norm(onebit_plan p, const float *v, void *workspace, double *out,
     if (!aligned(workspace, 256)) return fail(ONEBIT_EALIGN, "workspace is not 256-byte aligned");
     if (!out) return fail(ONEBIT_EINVAL, "out is NULL");
     if (!aligned(out, 8)) return fail(ONEBIT_EALIGN, "out is not 8-byte aligned");
+    // the chunk owners' row of the workspace holds T doubles, at least 32
     double *part = (double *)((char *)workspace + server_partial_offset(p));
-    TRY_HIP(onebit::launch_l1_norm(p->tb, p->T, v, part, out, (hipStream_t)stream),
+    TRY_HIP(onebit::launch_l1_norm(p->tb, v, part, out, (hipStream_t)stream),
             "l1 norm kernel launch");
     return ONEBIT_OK;
 }
