@@ -627,7 +627,7 @@ int onebit_warmup_adam_step(onebit_plan p, float *x, float *m, float *v, const v
         bc1 = (float)(1.0 - std::pow((double)beta1, (double)step));
         bc2 = (float)(1.0 - std::pow((double)beta2, (double)step));
     }
-    TRY_HIP(onebit::launch_warmup(p->tb, p->T, x, m, v, grads, grad_dtype, grad_ld, n_grads, lr,
+    TRY_HIP(onebit::launch_warmup(p->tb, x, m, v, grads, grad_dtype, grad_ld, n_grads, lr,
                                   beta1,
                                   beta2, eps, bias_correction ? 1 : 0, bc1, bc2,
                                   (hipStream_t)stream),
@@ -757,7 +757,7 @@ int onebit_uncompressed_step(onebit_plan p, float *x, float *m, const float *v_f
     if (n_grads < 1) return fail(ONEBIT_EINVAL, "n_grads < 1");
     TRY(check_ld(grad_ld, p->D, n_grads > 1, "grad_ld"));
     if (p->T == 0) return ONEBIT_OK;
-    TRY_HIP(onebit::launch_uncompressed(p->tb, p->T, x, m, v_frozen, grads, grad_dtype, grad_ld,
+    TRY_HIP(onebit::launch_uncompressed(p->tb, x, m, v_frozen, grads, grad_dtype, grad_ld,
                                         n_grads, lr, beta1, eps, (hipStream_t)stream),
             "uncompressed step kernel launch");
     return ONEBIT_OK;

@@ -77,7 +77,7 @@ constexpr int kGradF32 = 0;
 constexpr int kGradBF16 = 1;
 constexpr int kGradF16 = 2;
 
-hipError_t launch_warmup(const DeviceTables &tb, int64_t num_tiles, float *x, float *m,
+hipError_t launch_warmup(const DeviceTables &tb, float *x, float *m,
                          float *v, const void *g, int grad_dtype, int64_t g_ld, int n_grads,
                          float lr, float beta1, float beta2, float eps, int use_bc, float bc1,
                          float bc2, hipStream_t s);
@@ -96,7 +96,7 @@ hipError_t launch_adam_message(const DeviceTables &tb, const uint64_t *bits, con
                                float *x, float *m, float *v, float lr, float beta1, float beta2,
                                float eps, int use_bc, float bc1, float bc2, hipStream_t s);
 
-hipError_t launch_uncompressed(const DeviceTables &tb, int64_t num_tiles, float *x, float *m,
+hipError_t launch_uncompressed(const DeviceTables &tb, float *x, float *m,
                                const float *v, const void *g, int grad_dtype, int64_t g_ld,
                                int n, float lr, float beta1, float eps, hipStream_t s);
 

@@ -309,74 +309,155 @@ __device__ __forceinline__ float with_sign(float a, uint32_t nib, int c)
 // ---------------------------------------------------------------------------
 // Warm-up Adam (eq. (alg:v)) on the average of n_grads gradient rows.
 //
-// The row-summing kernels (this one and the 32-bit comparison step) give the
-// 16 waves of a workgroup 16 consecutive tiles and read each gradient row
-// together, with a workgroup barrier after every row: each row is then
-// streamed in 64 KB runs rather than in 16 independent 4 KB pieces.  Waves
-// without a tile keep the pace.  Every wave of a workgroup runs the same row
-// loop, so every wave reaches every barrier.
+// The row-summing kernels (this one and the 32-bit comparison step) come in
+// three shapes (launch_row_sum picks one): SB sub-blocks of a block per wave,
+// WAVES waves per workgroup, the loads of BATCH rows issued together.  With
+// BATCH = 1 the waves of a workgroup read each gradient row together, with a
+// workgroup barrier after every row, so that a row is streamed in runs of
+// WAVES * SB KB (fp32); waves past the last block keep the pace, so every wave
+// reaches every barrier.
 // ---------------------------------------------------------------------------
-// One gradient row of the tile as fp32 (zeros past the tile when !FULL).
-template <bool FULL, class G>
-__device__ __forceinline__ void load_grad_row(v4f (&gv)[kSubBlocks],
-                                              const typename G::T *__restrict__ row, int lane,
-                                              int len)
+template <int SB_, int WAVES_, int BATCH_>
+struct RowShape {
+    static constexpr int SB = SB_, WAVES = WAVES_, BATCH = BATCH_;
+    static constexpr int PARTS = kSubBlocks / SB_;  // waves per block
+};
+
+// This wave's part of a block in the row-summing kernels.
+struct RowPart {
+    int64_t blk, base;
+    int lim, sb0;
+    bool active;
+};
+
+template <class Sh>
+__device__ __forceinline__ RowPart row_part(int64_t block_base, int64_t num_blocks,
+                                            int64_t padded_len)
+{
+    const int64_t u = xcd_block() * Sh::WAVES + wave_id();
+    RowPart r;
+    r.blk = block_base + u / Sh::PARTS;
+    r.sb0 = (int)(u % Sh::PARTS) * Sh::SB;
+    r.active = r.blk < num_blocks;
+    r.base = r.blk * kTileElems;
+    const int64_t room = padded_len - r.base;
+    r.lim = room < kTileElems ? (int)room : kTileElems;
+    return r;
+}
+
+template <bool INSIDE, class G, int SB>
+__device__ __forceinline__ void load_grad_row(v4f (&gv)[SB], const typename G::T *__restrict__ row,
+                                              int sb0, int lane, int lim)
 {
 #pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b) gv[b] = ldg4<FULL, G>(row, b * (kWave * 4) + 4 * lane, len);
+    for (int b = 0; b < SB; ++b)
+        gv[b] = ldgb4<INSIDE, G>(row, (sb0 + b) * (kWave * 4) + 4 * lane, lim);
 }
 
 // sum += one loaded gradient row (fp64, rows added in row order)
-__device__ __forceinline__ void add_grad_row(double (&sum)[kSubBlocks][4],
-                                             const v4f (&gv)[kSubBlocks])
+template <int SB>
+__device__ __forceinline__ void add_grad_row(double (&sum)[SB][4], const v4f (&gv)[SB], bool in)
 {
 #pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b)
+    for (int b = 0; b < SB; ++b)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) sum[b][c] += (double)gv[b][c];
+        for (int c = 0; c < 4; ++c) sum[b][c] += in ? (double)gv[b][c] : 0.0;
 }
 
-// sum = the n gradient rows of the tile, added in row order, with a
-// workgroup barrier after every row; every wave runs the same number of
-// barriers (active: the wave has a tile).  Issuing row i+1's loads before
-// adding row i measured the same (8.79 against 8.74 ms on the BERT-Large
-// shape, same buffers), and without the barriers the pass is 6% slower.
-template <bool FULL, class G>
-__device__ __forceinline__ void warmup_rows_walk(double (&sum)[kSubBlocks][4], const Tile &tile,
-                                                 int lane, bool active,
-                                                 const typename G::T *__restrict__ g,
-                                                 int64_t g_ld, int n)
+// sum += worker i's momentum beta1 m + (1 - beta1) g_i (fp32, then fp64 sum)
+template <int SB>
+__device__ __forceinline__ void add_momentum_row(double (&sum)[SB][4], const v4f (&bm)[SB],
+                                                 const v4f (&gv)[SB], bool in, float omb1)
 {
-    for (int i = 0; i < n; ++i) {
-        if (active) {
-            v4f gv[kSubBlocks];
-            load_grad_row<FULL, G>(gv, g + tile.start + (int64_t)i * g_ld, lane, tile.len);
-            add_grad_row(sum, gv);
+#pragma unroll
+    for (int b = 0; b < SB; ++b)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            float mi = omb1 * gv[b][c];
+            mi = bm[b][c] + mi;
+            sum[b][c] += in ? (double)mi : 0.0;
         }
-        __builtin_amdgcn_s_barrier();  // the workgroup reads each row together
+}
+
+// Reads the n rows of this wave's part in row order, BATCH rows' loads at a
+// time, and hands each to use(gv, last), last telling that it is a row past
+// the end (the last row again, to be left out).  With BATCH = 1 the waves of
+// the workgroup read each row together (a barrier after every row).
+template <bool INSIDE, class G, int SB, int BATCH, class Use>
+__device__ __forceinline__ void walk_rows(const RowPart &p, const typename G::T *__restrict__ row,
+                                          int64_t g_ld, int n, int lane, Use use)
+{
+    for (int i = 0; i < n; i += BATCH) {
+        if (p.active) {
+            v4f gv[BATCH][SB];
+#pragma unroll
+            for (int k = 0; k < BATCH; ++k)
+                load_grad_row<INSIDE, G, SB>(gv[k], row + (int64_t)min(i + k, n - 1) * g_ld, p.sb0,
+                                             lane, p.lim);
+#pragma unroll
+            for (int k = 0; k < BATCH; ++k) use(gv[k], i + k < n);
+        }
+        if (BATCH == 1) __builtin_amdgcn_s_barrier();
     }
 }
 
-// Adam on the averaged gradient sum / n; loads of x, m, v precede the stores.
-template <bool FULL>
-__device__ __forceinline__ void warmup_update(const double (&sum)[kSubBlocks][4], int64_t base,
-                                              int len, int lane, float *__restrict__ x,
-                                              float *__restrict__ m, float *__restrict__ v,
-                                              double dn, float lr, float beta1, float omb1,
-                                              float beta2, float omb2, float eps, int use_bc,
-                                              float bc1, float bc2)
+// How many of the lane's 4 elements of each sub-block are real.
+template <int SB>
+__device__ __forceinline__ void part_valid(int (&valid)[SB], const Tile *__restrict__ tiles,
+                                           const Block &rec, const RowPart &p, int lane)
 {
-    v4f xv[kSubBlocks], mv[kSubBlocks], vv[kSubBlocks];
 #pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b) {
-        const int li = b * (kWave * 4) + 4 * lane;
-        xv[b] = ld4<FULL>(x + base, li, len);
-        mv[b] = ld4<FULL>(m + base, li, len);
-        vv[b] = ld4<FULL>(v + base, li, len);
+    for (int b = 0; b < SB; ++b) {
+        const int li = (p.sb0 + b) * (kWave * 4) + 4 * lane;
+        valid[b] = 4;
+        if (!rec.whole)
+            valid[b] = li < p.lim
+                           ? tile_valid4(block_word_tile(tiles, rec, li >> 6), p.base + li)
+                           : 0;
     }
+}
+
+template <class G, class Sh>
+__global__ __launch_bounds__(Sh::WAVES *kWave) void k_warmup(
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
+    int64_t num_blocks,
+    int64_t padded_len, float *__restrict__ x, float *__restrict__ m, float *__restrict__ v,
+    const typename G::T *__restrict__ g, int64_t g_ld, int n_grads, float lr, float beta1,
+    float omb1, float beta2, float omb2, float eps, int use_bc, float bc1, float bc2)
+{
+    constexpr int SB = Sh::SB;
+    const int lane = threadIdx.x & (kWave - 1);
+    const RowPart p = row_part<Sh>(block_base, num_blocks, padded_len);
+    double sum[SB][4];
 #pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b) {
-        const int li = b * (kWave * 4) + 4 * lane;
+    for (int b = 0; b < SB; ++b)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sum[b][c] = 0.0;
+    const typename G::T *row = g + p.base;
+    const auto use = [&](const v4f(&gv)[SB], bool in) { add_grad_row<SB>(sum, gv, in); };
+    if (p.lim == kTileElems)
+        walk_rows<true, G, SB, Sh::BATCH>(p, row, g_ld, n_grads, lane, use);
+    else
+        walk_rows<false, G, SB, Sh::BATCH>(p, row, g_ld, n_grads, lane, use);
+    if (!p.active) return;
+    const Block rec = load_block(blocks, p.blk);
+    x += p.base;
+    m += p.base;
+    v += p.base;
+    v4f xv[SB], mv[SB], vv[SB];
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+        const int li = (p.sb0 + b) * (kWave * 4) + 4 * lane;
+        xv[b] = ldb4<false>(x, li, p.lim);
+        mv[b] = ldb4<false>(m, li, p.lim);
+        vv[b] = ldb4<false>(v, li, p.lim);
+    }
+    int valid[SB];
+    part_valid<SB>(valid, tiles, rec, p, lane);
+    const double dn = (double)n_grads;
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+        const int li = (p.sb0 + b) * (kWave * 4) + 4 * lane;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const float gbar = (float)(sum[b][c] / dn);
@@ -397,9 +478,84 @@ __device__ __forceinline__ void warmup_update(const double (&sum)[kSubBlocks][4]
             mv[b][c] = mn;
             vv[b][c] = vn;
         }
-        st4<FULL>(x + base, li, len, xv[b]);
-        st4<FULL>(m + base, li, len, mv[b]);
-        st4<FULL>(v + base, li, len, vv[b]);
+        stb4<false>(x, li, valid[b], xv[b]);
+        stb4<false>(m, li, valid[b], mv[b]);
+        stb4<false>(v, li, valid[b], vv[b]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// "1-bit Adam (32-bits)" comparison variant (Section 7.2): the compression
+// stage with the identity compressor -- variance frozen, momenta averaged
+// uncompressed.  m_i = beta1 m + (1-beta1) g_i per worker, m = mean_i m_i
+// (fp64 sum in worker order, one rounding), x -= lr m / sqrt(v + eps).
+// ---------------------------------------------------------------------------
+template <class G, class Sh>
+__global__ __launch_bounds__(Sh::WAVES *kWave) void k_uncompressed(
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
+    int64_t num_blocks,
+    int64_t padded_len, float *__restrict__ x, float *__restrict__ m, const float *__restrict__ v,
+    const typename G::T *__restrict__ g, int64_t g_ld, int n, float lr, float beta1, float omb1,
+    float eps)
+{
+    constexpr int SB = Sh::SB;
+    const int lane = threadIdx.x & (kWave - 1);
+    const RowPart p = row_part<Sh>(block_base, num_blocks, padded_len);
+    double sum[SB][4];
+    v4f bm[SB], xv[SB], vv[SB];
+    // whole-block waves load x and v ahead of the rows, with m (BERT-Base, 16
+    // rows: 1.450 ms against 1.517 after them)
+    constexpr bool kEarly = SB == kSubBlocks;
+    x += p.base;
+    v += p.base;
+    if (p.active) {
+        m += p.base;
+#pragma unroll
+        for (int b = 0; b < SB; ++b) {
+            const int li = (p.sb0 + b) * (kWave * 4) + 4 * lane;
+            bm[b] = beta1 * ldb4<false>(m, li, p.lim);
+            if (kEarly) {
+                xv[b] = ldb4<false>(x, li, p.lim);
+                vv[b] = ldb4<false>(v, li, p.lim);
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum[b][c] = 0.0;
+        }
+    }
+    const typename G::T *row = g + p.base;
+    const auto use = [&](const v4f(&gv)[SB], bool in) { add_momentum_row<SB>(sum, bm, gv, in, omb1); };
+    if (p.lim == kTileElems)
+        walk_rows<true, G, SB, Sh::BATCH>(p, row, g_ld, n, lane, use);
+    else
+        walk_rows<false, G, SB, Sh::BATCH>(p, row, g_ld, n, lane, use);
+    if (!p.active) return;
+    const Block rec = load_block(blocks, p.blk);
+    if (!kEarly) {
+#pragma unroll
+        for (int b = 0; b < SB; ++b) {
+            const int li = (p.sb0 + b) * (kWave * 4) + 4 * lane;
+            xv[b] = ldb4<false>(x, li, p.lim);
+            vv[b] = ldb4<false>(v, li, p.lim);
+        }
+    }
+    int valid[SB];
+    part_valid<SB>(valid, tiles, rec, p, lane);
+    const double dn = (double)n;
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+        const int li = (p.sb0 + b) * (kWave * 4) + 4 * lane;
+        v4f mv;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float mbar = (float)(sum[b][c] / dn);
+            const float denom = __builtin_sqrtf(vv[b][c] + eps);
+            const float ratio = mbar / denom;
+            const float step = lr * ratio;
+            xv[b][c] = xv[b][c] - step;
+            mv[c] = mbar;
+        }
+        stb4<false>(x, li, valid[b], xv[b]);
+        stb4<false>(m, li, valid[b], mv);
     }
 }
 
@@ -510,143 +666,6 @@ __global__ __launch_bounds__(kBlock) void k_adam_message(
         adam_message_sub<false>(lane_message<false>(tiles, rec, base, li, lim, word, s0, scales),
                                 li, xv, mv, vv, x, m, v, lr, beta1, omb1, beta2, omb2, eps, use_bc,
                                 bc1, bc2);
-}
-
-// ---------------------------------------------------------------------------
-// "1-bit Adam (32-bits)" comparison variant (Section 7.2): the compression
-// stage with the identity compressor -- variance frozen, momenta averaged
-// uncompressed.  m_i = beta1 m + (1-beta1) g_i per worker, m = mean_i m_i
-// (fp64 sum in worker order, one rounding), x -= lr m / sqrt(v + eps).
-// ---------------------------------------------------------------------------
-template <bool FULL>
-__device__ __forceinline__ void uncompressed_load(int64_t base, int len, int lane,
-                                                  const float *__restrict__ x,
-                                                  const float *__restrict__ m,
-                                                  const float *__restrict__ v, float beta1,
-                                                  v4f (&bm)[kSubBlocks], v4f (&xv)[kSubBlocks],
-                                                  v4f (&vv)[kSubBlocks])
-{
-#pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b) {
-        const int li = b * (kWave * 4) + 4 * lane;
-        bm[b] = beta1 * ld4<FULL>(m + base, li, len);
-        xv[b] = ld4<FULL>(x + base, li, len);
-        vv[b] = ld4<FULL>(v + base, li, len);
-    }
-}
-
-// sum += worker i's momentum beta1 m + (1 - beta1) g_i (fp32, then fp64 sum)
-template <bool FULL, class G>
-__device__ __forceinline__ void add_momentum_row(double (&sum)[kSubBlocks][4],
-                                                 const v4f (&bm)[kSubBlocks],
-                                                 const typename G::T *__restrict__ row, int lane,
-                                                 int len, float omb1)
-{
-#pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b) {
-        const v4f gv = ldg4<FULL, G>(row, b * (kWave * 4) + 4 * lane, len);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            float mi = omb1 * gv[c];
-            mi = bm[b][c] + mi;
-            sum[b][c] += (double)mi;
-        }
-    }
-}
-
-template <bool FULL>
-__device__ __forceinline__ void uncompressed_store(const double (&sum)[kSubBlocks][4], int64_t base,
-                                                   int len, int lane, v4f (&xv)[kSubBlocks],
-                                                   const v4f (&vv)[kSubBlocks],
-                                                   float *__restrict__ x, float *__restrict__ m,
-                                                   double dn, float lr, float eps)
-{
-#pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b) {
-        const int li = b * (kWave * 4) + 4 * lane;
-        v4f mv;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float mbar = (float)(sum[b][c] / dn);
-            const float denom = __builtin_sqrtf(vv[b][c] + eps);
-            const float ratio = mbar / denom;
-            const float step = lr * ratio;
-            xv[b][c] = xv[b][c] - step;
-            mv[c] = mbar;
-        }
-        st4<FULL>(x + base, li, len, xv[b]);
-        st4<FULL>(m + base, li, len, mv);
-    }
-}
-
-template <class G>
-__global__ __launch_bounds__(kRowBlock) void k_uncompressed(
-    const Tile *__restrict__ tiles, int64_t num_tiles, float *__restrict__ x,
-    float *__restrict__ m, const float *__restrict__ v, const typename G::T *__restrict__ g,
-    int64_t g_ld, int n, float lr, float beta1, float omb1, float eps)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t t = xcd_block() * kRowWaves + (threadIdx.x >> 6);
-    const bool active = t < num_tiles;
-    Tile tile{0, 0, 0};
-    if (active) tile = tiles[t];
-    const bool full = tile.len == kTileElems;
-    v4f bm[kSubBlocks], xv[kSubBlocks], vv[kSubBlocks];
-    if (full)
-        uncompressed_load<true>(tile.start, tile.len, lane, x, m, v, beta1, bm, xv, vv);
-    else
-        uncompressed_load<false>(tile.start, tile.len, lane, x, m, v, beta1, bm, xv, vv);
-    double sum[kSubBlocks][4];
-#pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sum[b][c] = 0.0;
-    for (int i = 0; i < n; ++i) {
-        const typename G::T *row = g + (int64_t)i * g_ld + tile.start;
-        if (full)
-            add_momentum_row<true, G>(sum, bm, row, lane, tile.len, omb1);
-        else if (active)
-            add_momentum_row<false, G>(sum, bm, row, lane, tile.len, omb1);
-        __builtin_amdgcn_s_barrier();  // the workgroup reads each row together
-    }
-    if (!active) return;
-    const double dn = (double)n;
-    if (full)
-        uncompressed_store<true>(sum, tile.start, tile.len, lane, xv, vv, x, m, dn, lr, eps);
-    else
-        uncompressed_store<false>(sum, tile.start, tile.len, lane, xv, vv, x, m, dn, lr, eps);
-}
-
-template <class G>
-__global__ __launch_bounds__(kRowBlock) void k_warmup(
-    const Tile *__restrict__ tiles, int64_t num_tiles, float *__restrict__ x,
-    float *__restrict__ m, float *__restrict__ v, const typename G::T *__restrict__ g, int64_t g_ld,
-    int n_grads, float lr, float beta1, float omb1, float beta2, float omb2, float eps,
-    int use_bc, float bc1, float bc2)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int64_t t = xcd_block() * kRowWaves + (threadIdx.x >> 6);
-    const bool active = t < num_tiles;
-    Tile tile{0, 0, 0};
-    if (active) tile = tiles[t];
-    const bool full = tile.len == kTileElems;
-    double sum[kSubBlocks][4];
-#pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b)
-#pragma unroll
-        for (int c = 0; c < 4; ++c) sum[b][c] = 0.0;
-    if (full)
-        warmup_rows_walk<true, G>(sum, tile, lane, true, g, g_ld, n_grads);
-    else
-        warmup_rows_walk<false, G>(sum, tile, lane, active, g, g_ld, n_grads);
-    if (!active) return;
-    const double dn = (double)n_grads;
-    if (full)
-        warmup_update<true>(sum, tile.start, tile.len, lane, x, m, v, dn, lr, beta1, omb1,
-                            beta2, omb2, eps, use_bc, bc1, bc2);
-    else
-        warmup_update<false>(sum, tile.start, tile.len, lane, x, m, v, dn, lr, beta1, omb1,
-                             beta2, omb2, eps, use_bc, bc1, bc2);
 }
 
 // ---------------------------------------------------------------------------
@@ -2209,9 +2228,9 @@ __global__ __launch_bounds__(kBlock) void k_decode(const Tile *__restrict__ tile
 // l1 norm of a buffer over the real elements (the variance-stability
 // indicator of Section 7.1): fp64 partial sums of |v| over up to kL1Groups
 // workgroups (each a run of blocks, its waves taking turns), then one
-// workgroup sums those in a fixed order.  A partial sum per tile made that
-// last workgroup read 326,000 of them for the BERT-Large shape, 306 us after
-// 187 us for the partial sums; now L1_NOW.
+// workgroup sums those in a fixed order.  With a partial sum per tile that last
+// workgroup read 326,000 of them for the BERT-Large shape: 187 + 306 us, now
+// 204 + 6 us.
 // ---------------------------------------------------------------------------
 constexpr int64_t kL1Groups = 2048;  // 8 waves on every SIMD
 
@@ -2281,36 +2300,65 @@ inline int64_t blocks_for(int64_t waves) { return xcd_grid(waves, kWavesPerBlock
 
 }  // namespace
 
+// The shape of a row-summing launch over num_blocks blocks and n rows.
+// - Small plans (2^21 elements of fp32, 2^22 of 16-bit gradients, whose waves
+//   are all on the chip at once): four rows' loads at a time and no barrier,
+//   since one row after another is a chain of n round trips (10^6 elements, 16
+//   fp32 rows: 13.6 us against 16.8, 18.4 and 35.6 in the shapes (1, 4, 1),
+//   (1, 16, 1) and (4, 16, 1); 10^5 elements, 32 rows 12.6 against 14.2, 20.5
+//   and 45.6; but 4x10^6 elements, 16 rows 59.8 against 51.1 in (1, 16, 1)).
+// - Few rows, or a plan that does not fill the chip with whole blocks: one
+//   sub-block per wave (BERT-Large, fp32 rows: n = 4 2.19 ms against 2.26 with
+//   a whole block, n = 8 with the norm 3.46 against 3.53; fp16 n = 4 1.73
+//   against 1.78 with two; 6x10^6 elements, 16 fp32 rows 82 us against 98).
+// - Many rows: the longer runs of a whole block (fp32; BERT-Base, n = 32: 2.72
+//   against 2.84 ms) or two sub-blocks (16-bit; 12 million elements, n = 16:
+//   114 us against 123 with one and 137 with four).
 template <class G>
-static hipError_t launch_warmup_t(const DeviceTables &tb, int64_t num_tiles, float *x, float *m,
-                                  float *v, const void *g, int64_t g_ld, int n_grads, float lr,
-                                  float beta1, float beta2, float eps, int use_bc, float bc1,
-                                  float bc2, hipStream_t s)
+using ManyRows = RowShape<sizeof(typename G::T) == 4 ? 4 : 2, 16, 1>;
+using FewRows = RowShape<1, 16, 1>;
+using SmallPlan = RowShape<1, 4, 4>;
+
+template <class G, class F>
+static void launch_row_sum(const DeviceTables &tb, int n, F launch)
 {
-    const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
-    hipLaunchKernelGGL(k_warmup<G>, dim3((unsigned)xcd_grid(num_tiles, kRowWaves)), dim3(kRowBlock), 0, s,
-                       tb.tiles,
-                       num_tiles, x, m, v, (const typename G::T *)g, g_ld, n_grads, lr, beta1,
-                       omb1, beta2, omb2, eps, use_bc, bc1, bc2);
-    return hipGetLastError();
+    constexpr bool f32 = sizeof(typename G::T) == 4;
+    if (tb.num_blocks <= (f32 ? 2048 : 4096))
+        launch(SmallPlan{});
+    else if (n <= (f32 ? 12 : 4) || (f32 && tb.num_blocks <= 8192))
+        launch(FewRows{});
+    else
+        launch(ManyRows<G>{});
 }
 
-hipError_t launch_warmup(const DeviceTables &tb, int64_t num_tiles, float *x, float *m,
-                         float *v, const void *g, int grad_dtype, int64_t g_ld, int n_grads,
-                         float lr, float beta1, float beta2, float eps, int use_bc, float bc1,
-                         float bc2, hipStream_t s)
+template <class G>
+static void launch_warmup_t(const DeviceTables &tb, float *x, float *m, float *v, const void *g,
+                            int64_t g_ld, int n_grads, float lr, float beta1, float beta2,
+                            float eps, int use_bc, float bc1, float bc2, hipStream_t s)
 {
-    switch (grad_dtype) {
-    case kGradBF16:
-        return launch_warmup_t<GradBF16>(tb, num_tiles, x, m, v, g, g_ld, n_grads, lr, beta1,
-                                         beta2, eps, use_bc, bc1, bc2, s);
-    case kGradF16:
-        return launch_warmup_t<GradF16>(tb, num_tiles, x, m, v, g, g_ld, n_grads, lr, beta1,
-                                        beta2, eps, use_bc, bc1, bc2, s);
-    default:
-        return launch_warmup_t<GradF32>(tb, num_tiles, x, m, v, g, g_ld, n_grads, lr, beta1,
-                                        beta2, eps, use_bc, bc1, bc2, s);
-    }
+    const float omb1 = 1.0f - beta1, omb2 = 1.0f - beta2;
+    launch_row_sum<G>(tb, n_grads, [&](auto shape) {
+        using Sh = decltype(shape);
+        for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
+            const int64_t count = launch_piece(tb.num_blocks, base);
+            hipLaunchKernelGGL((k_warmup<G, Sh>),
+                               dim3((unsigned)xcd_grid(count * Sh::PARTS, Sh::WAVES)),
+                               dim3(Sh::WAVES * kWave), 0, s, tb.tiles, tb.blocks, base,
+                               base + count, tb.padded_len, x, m, v, (const typename G::T *)g, g_ld,
+                               n_grads, lr, beta1, omb1, beta2, omb2, eps, use_bc, bc1, bc2);
+        }
+    });
+}
+
+hipError_t launch_warmup(const DeviceTables &tb, float *x, float *m, float *v, const void *g,
+                         int grad_dtype, int64_t g_ld, int n_grads, float lr, float beta1,
+                         float beta2, float eps, int use_bc, float bc1, float bc2, hipStream_t s)
+{
+    const auto launch = grad_dtype == kGradBF16  ? launch_warmup_t<GradBF16>
+                        : grad_dtype == kGradF16 ? launch_warmup_t<GradF16>
+                                                 : launch_warmup_t<GradF32>;
+    launch(tb, x, m, v, g, g_ld, n_grads, lr, beta1, beta2, eps, use_bc, bc1, bc2, s);
+    return hipGetLastError();
 }
 
 template <bool PACKED, class G>
@@ -2409,31 +2457,32 @@ hipError_t launch_adam_message(const DeviceTables &tb, const uint64_t *bits, con
 }
 
 template <class G>
-static void launch_uncompressed_t(const DeviceTables &tb, int64_t num_tiles, float *x, float *m,
-                                  const float *v, const void *g, int64_t g_ld, int n, float lr,
-                                  float beta1, float eps, hipStream_t s)
+static void launch_uncompressed_t(const DeviceTables &tb, float *x, float *m, const float *v,
+                                  const void *g, int64_t g_ld, int n, float lr, float beta1,
+                                  float eps, hipStream_t s)
 {
     const float omb1 = 1.0f - beta1;
-    hipLaunchKernelGGL(k_uncompressed<G>, dim3((unsigned)xcd_grid(num_tiles, kRowWaves)),
-                       dim3(kRowBlock), 0, s,
-                       tb.tiles, num_tiles, x, m, v, (const typename G::T *)g, g_ld, n, lr, beta1,
-                       omb1, eps);
+    launch_row_sum<G>(tb, n, [&](auto shape) {
+        using Sh = decltype(shape);
+        for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
+            const int64_t count = launch_piece(tb.num_blocks, base);
+            hipLaunchKernelGGL((k_uncompressed<G, Sh>),
+                               dim3((unsigned)xcd_grid(count * Sh::PARTS, Sh::WAVES)),
+                               dim3(Sh::WAVES * kWave), 0, s, tb.tiles, tb.blocks, base,
+                               base + count, tb.padded_len, x, m, v, (const typename G::T *)g, g_ld,
+                               n, lr, beta1, omb1, eps);
+        }
+    });
 }
 
-hipError_t launch_uncompressed(const DeviceTables &tb, int64_t num_tiles, float *x, float *m,
-                               const float *v, const void *g, int grad_dtype, int64_t g_ld,
-                               int n, float lr, float beta1, float eps, hipStream_t s)
+hipError_t launch_uncompressed(const DeviceTables &tb, float *x, float *m, const float *v,
+                               const void *g, int grad_dtype, int64_t g_ld, int n, float lr,
+                               float beta1, float eps, hipStream_t s)
 {
-    switch (grad_dtype) {
-    case kGradBF16:
-        launch_uncompressed_t<GradBF16>(tb, num_tiles, x, m, v, g, g_ld, n, lr, beta1, eps, s);
-        break;
-    case kGradF16:
-        launch_uncompressed_t<GradF16>(tb, num_tiles, x, m, v, g, g_ld, n, lr, beta1, eps, s);
-        break;
-    default:
-        launch_uncompressed_t<GradF32>(tb, num_tiles, x, m, v, g, g_ld, n, lr, beta1, eps, s);
-    }
+    const auto launch = grad_dtype == kGradBF16  ? launch_uncompressed_t<GradBF16>
+                        : grad_dtype == kGradF16 ? launch_uncompressed_t<GradF16>
+                                                 : launch_uncompressed_t<GradF32>;
+    launch(tb, x, m, v, g, g_ld, n, lr, beta1, eps, s);
     return hipGetLastError();
 }
 

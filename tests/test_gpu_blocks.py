@@ -93,3 +93,57 @@ def test_short_tiles_free_running(dev, name, numel, n, packed, grad_dtype):
     for t in (st.x, st.v, st.worker_err, st.server_err):
         assert bool((t[..., pad] == PAD).all()), "a padding element was written"
     plan.close()
+
+
+# Row-summing shapes: small plans take four rows at a time, larger ones one
+# sub-block per wave for few rows and a whole block (fp32) or two sub-blocks
+# (16-bit) for many; the sizes lie on both sides of each line and end inside a
+# block (odd sizes) or on its edge.
+@pytest.mark.parametrize("variant", ["warmup", "uncompressed"])
+@pytest.mark.parametrize("grad_dtype,numel,n", [
+    (torch.float32, [1], 1), (torch.float32, [2048 * 1024 - 64, 63], 5),
+    (torch.float32, [2048 * 1024 + 1], 3), (torch.float32, [8192 * 1024], 13),
+    (torch.float32, [8192 * 1024 + 77], 12), (torch.float32, [8000 * 1024, 300_007], 13),
+    (torch.bfloat16, [4096 * 1024], 7), (torch.bfloat16, [4096 * 1024 + 1], 4),
+    (torch.float16, [4096 * 1024, 1000], 5),
+])
+def test_row_sum_shapes(dev, variant, grad_dtype, numel, n):
+    """Against the same formula in torch: the fp64 sum of the rows in row
+    order, one rounding, then fp32 operations rounded one by one."""
+    import paper_2102_02888_amd as ob
+    lr, b1, b2, eps = 1e-3, 0.9, 0.999, 1e-8
+    plan = ob.Plan(numel, n)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(n)
+    f = dict(device=dev, dtype=torch.float32)
+    x, m = (torch.empty(plan.D, **f).normal_(generator=gen) for _ in range(2))
+    v = torch.empty(plan.D, **f).uniform_(0.1, 1.0, generator=gen)
+    g = torch.empty((n, plan.D), dtype=grad_dtype, device=dev).normal_(generator=gen)
+    real = torch.from_numpy(oracle.Layout(numel, n).real_mask()).to(dev)
+    one = np.float32(1)
+    o1, o2 = float(one - np.float32(b1)), float(one - np.float32(b2))
+    total = torch.zeros(plan.D, dtype=torch.float64, device=dev)
+    if variant == "warmup":
+        for i in range(n):
+            total += g[i].double()
+        gbar = (total / n).float()
+        m1 = b1 * m + o1 * gbar
+        v1 = b2 * v + o2 * (gbar * gbar)
+        x1 = x - lr * (m1 / (v1.sqrt() + eps))
+    else:
+        for i in range(n):
+            total += (b1 * m + o1 * g[i].float()).double()
+        m1, v1 = (total / n).float(), v
+        x1 = x - lr * (m1 / (v + eps).sqrt())
+    want = [torch.where(real, a, b) for a, b in ((x1, x), (m1, m), (v1, v))]
+    if variant == "warmup":
+        ob.onebit_warmup_adam_step(plan, x, m, v, g, lr, b1, b2, eps, 0, 1)
+    else:
+        ob.onebit_uncompressed_step(plan, x, m, v, g, lr, b1, eps)
+    torch.cuda.synchronize()
+    # torch's fp32 division and square root round as the kernels do, but for
+    # an ulp here and there: 2 ulp of the value, as x is near 1
+    for name, a, b in zip("xmv", (x, m, v), want):
+        worst = float(((a - b).abs() / b.abs().clamp(min=1e-3)).max())
+        assert worst <= 2 ** -22, (name, worst)
+    plan.close()
