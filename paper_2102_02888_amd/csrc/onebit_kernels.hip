@@ -718,107 +718,6 @@ constexpr int64_t kMaxPassItems = (int64_t)3 << 22;
 template <class G>
 constexpr int kPassIdleLds = sizeof(typename G::T) == 2 ? idle_lds(10) - 512 : 0;
 
-// The shared momentum m_{t-1} of sub-blocks sb0 .. sb0+SB-1 of the tile times
-// beta1.  PACKED: m_{t-1} is the previous step's gathered server message,
-// decoded from its sign words and segment scale (+-scale, exactly the fp32
-// value the update would have stored), so no fp32 momentum buffer is read.
-template <bool FULL, bool PACKED, int SB>
-__device__ __forceinline__ void beta1_momentum(v4f (&bm)[SB], const Tile &tile, int lane, int sb0,
-                                               const float *__restrict__ m,
-                                               const uint64_t *__restrict__ m_bits,
-                                               const float *__restrict__ m_scales, float beta1)
-{
-    const int len = tile.len;
-    const int64_t base = tile.start;
-    if (PACKED) {
-        const float s = m_scales[tile.seg];
-#pragma unroll
-        for (int b = 0; b < SB; ++b) {
-            const int sb = sb0 + b;
-            const int li = sb * (kWave * 4) + 4 * lane;
-            const uint64_t word =
-                (FULL || li < len) ? m_bits[(base >> 6) + 4 * sb + (lane >> 4)] : 0ull;
-            const uint32_t nib = (uint32_t)(word >> (4 * (lane & 15))) & 0xFu;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) bm[b][c] = beta1 * (((nib >> c) & 1u) ? s : -s);
-        }
-    } else {
-#pragma unroll
-        for (int b = 0; b < SB; ++b)
-            bm[b] = beta1 * ld4<FULL>(m + base, (sb0 + b) * (kWave * 4) + 4 * lane, len);
-    }
-}
-
-// Worker i's row over sub-blocks sb0 .. sb0+SB-1 of the tile: z_i from the
-// momentum term bm = beta1 m, the gradient row and the previous compensated
-// value; its sign words, sum of squares and new compensated value.  Split into
-// the loads of the row and the arithmetic and stores, so that a caller can
-// issue the next row's loads before this row's stores.
-template <bool FULL, class G, int SB>
-__device__ __forceinline__ void worker_row_load(const Tile &tile, int lane, int sb0, int i,
-                                                const typename G::T *__restrict__ g, int64_t g_ld,
-                                                const float *__restrict__ err, int64_t err_ld,
-                                                const float *__restrict__ scales,
-                                                int64_t scales_ld, v4f (&gv)[SB], v4f (&cv)[SB],
-                                                float &sp)
-{
-    const int len = tile.len;
-    sp = scales[(int64_t)i * scales_ld + tile.seg];
-    const typename G::T *gi = g + (int64_t)i * g_ld + tile.start;
-    const float *ei = err + (int64_t)i * err_ld + tile.start;
-#pragma unroll
-    for (int b = 0; b < SB; ++b) {
-        const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
-        gv[b] = ldg4<FULL, G>(gi, li, len);
-        cv[b] = ld4<FULL>(ei, li, len);
-    }
-}
-
-// Returns this wave's sum of z_i^2 over its sub-blocks (lanes summed in a
-// fixed order); the caller writes the tile's partial sum.  Each sub-block is
-// stored as soon as it is computed: computing every sub-block first keeps
-// more values live, and at the worker pass's 80 VGPRs the compiler then
-// issues a 16-bit-gradient row's loads one after another (measured 5.7%
-// slower for bf16 gradients, no faster for fp32).
-template <bool FULL, int SB>
-__device__ __forceinline__ double worker_row_store(const Tile &tile, int lane, int sb0,
-                                                   const v4f (&bm)[SB], int i, const v4f (&gv)[SB],
-                                                   const v4f (&cv)[SB], float sp,
-                                                   float *__restrict__ err, int64_t err_ld,
-                                                   uint64_t *__restrict__ bits, int64_t bits_ld,
-                                                   float omb1)
-{
-    const int len = tile.len;
-    const int64_t base = tile.start;
-    const int nwords = (len + 63) >> 6;
-    float *ei = err + (int64_t)i * err_ld + base;
-    uint64_t *bi = bits + (int64_t)i * bits_ld + (base >> 6);
-    double acc = 0.0;
-#pragma unroll
-    for (int b = 0; b < SB; ++b) {
-        const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
-        v4f zv;
-        uint32_t nib = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float d = error_of(cv[b][c], sp);
-            float mi = omb1 * gv[b][c];
-            mi = bm[b][c] + mi;
-            const float z = mi + d;
-            zv[c] = z;
-            const bool valid = FULL || li + c < len;
-            const double zd = valid ? (double)z : 0.0;
-            acc += zd * zd;
-            nib |= (valid && z >= 0.f) ? (1u << c) : 0u;
-        }
-        st4<FULL>(ei, li, len, zv);
-        const uint64_t word = row_sign_word(nib, lane);
-        const int w = 4 * (sb0 + b) + (lane >> 4);
-        if ((lane & 15) == 0 && (FULL || w < nwords)) bi[w] = word;
-    }
-    return wave_sum(acc);
-}
-
 // A wave's loads of its part of one block: the gradient row, the compensated
 // row and the momentum (sign words, or fp32 values).
 template <bool INSIDE, bool PACKED, class G, int SB>
@@ -844,59 +743,30 @@ __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&
     }
 }
 
-// One block of a worker's row (this wave's sub-blocks) from its loaded values:
-// scales, arithmetic and stores.  The waves' sums meet in red and are added in
-// wave or word order.  Both waves have the same block, so both reach the
-// barrier.
-template <bool WHOLE, bool PACKED, int SB>
-__device__ __forceinline__ void worker_block(
-    double (&red)[kTileWords], const Tile *__restrict__ tiles, const Block &rec, int64_t base,
-    int lim, int lane, int wv, const v4f (&mv)[SB], const uint64_t (&word)[SB], float s0,
-    float ms0, const float *__restrict__ m_scales, const v4f (&gv)[SB], const v4f (&cv)[SB],
-    const float *__restrict__ scales, float *__restrict__ ei, uint64_t *__restrict__ bi,
-    double *__restrict__ partial, float beta1, float omb1)
+// The arithmetic and stores of this wave's sub-blocks of one block of a
+// worker's row: z = (beta1 m + (1 - beta1) g) + delta from the momentum term
+// bm = beta1 m, the gradient and the previous compensated value with its scale
+// sp; the new compensated value and the sign words are stored.  Returns the
+// lane's sum of z^2 (WHOLE), or writes the words' sums to words.
+template <bool WHOLE, int SB>
+__device__ __forceinline__ double worker_compute(const float (&sp)[SB], const int (&valid)[SB],
+                                                 const v4f (&bm)[SB], const v4f (&gv)[SB],
+                                                 const v4f (&cv)[SB], float *__restrict__ ei,
+                                                 uint64_t *__restrict__ bi, int sb0, int lane,
+                                                 int lim, float omb1, double *words)
 {
-    const int sb0 = wv * SB;
-    // the scales of each sub-block's elements, one segment for a whole block
-    float sp[SB], bs[SB];
-    int valid[SB];
-    if (WHOLE) {
-        const float bms = PACKED ? beta1 * ms0 : 0.f;
-#pragma unroll
-        for (int b = 0; b < SB; ++b) {
-            sp[b] = s0;
-            bs[b] = bms;
-            valid[b] = 4;
-        }
-    } else {
-#pragma unroll
-        for (int b = 0; b < SB; ++b) {
-            const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
-            sp[b] = s0;
-            bs[b] = beta1 * ms0;
-            valid[b] = 0;
-            if (li < lim) {
-                const Tile t = block_word_tile(tiles, rec, li >> 6);
-                valid[b] = tile_valid4(t, base + li);
-                sp[b] = scales[t.seg];
-                if (PACKED) bs[b] = beta1 * m_scales[t.seg];
-            }
-        }
-    }
     double acc = 0.0;
 #pragma unroll
     for (int b = 0; b < SB; ++b) {
         const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
-        const uint32_t mnib = (uint32_t)(word[b] >> (4 * (lane & 15)));
         v4f zv;
         uint32_t nib = 0;
         double sub = 0.0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const float d = error_of(cv[b][c], sp[b]);
-            const float bm = PACKED ? with_sign(bs[b], mnib, c) : beta1 * mv[b][c];
             float mi = omb1 * gv[b][c];
-            mi = bm + mi;
+            mi = bm[b][c] + mi;
             const float z = mi + d;
             zv[c] = z;
             const bool in = WHOLE || c < valid[b];
@@ -912,24 +782,70 @@ __device__ __forceinline__ void worker_block(
             acc += sub;
         } else {
             const double row = row_sum(sub);
-            if ((lane & 15) == 0) red[w] = row;
+            if ((lane & 15) == 0) words[w] = row;
         }
     }
+    return acc;
+}
+
+// The block's partial sums (one per tile) from its waves' sums (WHOLE, waves
+// of them) or its words' sums, by the lanes of one wave.
+template <bool WHOLE>
+__device__ __forceinline__ void block_partials(double *__restrict__ partial, const Block &rec,
+                                               const double *sums, int waves, int lane)
+{
+    if (WHOLE) {
+        if (lane == 0) {
+            double sum = sums[0];
+            for (int k = 1; k < waves; ++k) sum += sums[k];
+            partial[rec.tile] = sum;
+        }
+    } else if (lane < __popc(rec.starts)) {
+        partial[rec.tile + lane] = block_tile_sum(sums, rec.starts, lane);
+    }
+}
+
+// One block of a worker's row (this wave's sub-blocks) from its loaded values.
+// Every wave of the workgroup has the same block, so all reach the barrier.
+template <bool WHOLE, bool PACKED, int SB>
+__device__ __forceinline__ void worker_block(
+    double (&red)[kTileWords], const Tile *__restrict__ tiles, const Block &rec, int64_t base,
+    int lim, int lane, int wv, const v4f (&mv)[SB], const uint64_t (&word)[SB], float s0,
+    float ms0, const float *__restrict__ m_scales, const v4f (&gv)[SB], const v4f (&cv)[SB],
+    const float *__restrict__ scales, float *__restrict__ ei, uint64_t *__restrict__ bi,
+    double *__restrict__ partial, float beta1, float omb1)
+{
+    const int sb0 = wv * SB;
+    // the scales of each sub-block's elements, one segment for a whole block
+    float sp[SB];
+    v4f bm[SB];
+    int valid[SB];
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+        float bs = PACKED ? beta1 * ms0 : 0.f;
+        sp[b] = s0;
+        valid[b] = 4;
+        if (!WHOLE) {
+            const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
+            valid[b] = 0;
+            if (li < lim) {
+                const Tile t = block_word_tile(tiles, rec, li >> 6);
+                valid[b] = tile_valid4(t, base + li);
+                sp[b] = scales[t.seg];
+                if (PACKED) bs = beta1 * m_scales[t.seg];
+            }
+        }
+        const uint32_t mnib = (uint32_t)(word[b] >> (4 * (lane & 15)));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) bm[b][c] = PACKED ? with_sign(bs, mnib, c) : beta1 * mv[b][c];
+    }
+    double acc = worker_compute<WHOLE, SB>(sp, valid, bm, gv, cv, ei, bi, sb0, lane, lim, omb1, red);
     if (WHOLE) {
         acc = wave_sum(acc);
         if (lane == 0) red[wv] = acc;
-        __syncthreads();
-        if (wv == 0 && lane == 0) {
-            double sum = red[0];
-#pragma unroll
-            for (int k = 1; k < kSubBlocks / SB; ++k) sum += red[k];
-            partial[rec.tile] = sum;
-        }
-    } else {
-        __syncthreads();
-        if (wv == 0 && lane < __popc(rec.starts))
-            partial[rec.tile + lane] = block_tile_sum(red, rec.starts, lane);
     }
+    __syncthreads();
+    if (wv == 0) block_partials<WHOLE>(partial, rec, red, kSubBlocks / SB, lane);
 }
 
 // PACKED: m_{t-1} is the previous step's gathered server message, decoded
@@ -986,111 +902,121 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
 
 // ---------------------------------------------------------------------------
 // The worker pass with an fp32 momentum (the first compression step): m is
-// read once per tile for all local workers, and the 16 waves of a workgroup
+// read once per block for all local workers, and the 16 waves of a workgroup
 // walk the worker rows together (one barrier per row), as in the warm-up.
-// The rows are double-buffered: row i+1's loads (gradient, error state and
-// scale) are issued before row i's arithmetic and stores, so each wave keeps
-// two rows of loads in flight and never waits on a load issued right after
-// its own stores (measured 23.75 against 23.86 ms for one row at a time, and
-// 24.76 ms without the barriers, on the BERT-Large shape, same buffers).
-// As in the packed pass, two waves share each tile, half a tile each (8 tiles
-// per workgroup); the pair's sums of squares of row i meet in red[i & 1] at
-// the barrier after row i, and the pair's first wave adds them in wave order
-// and writes the partial sum.  A wave writes red[i & 1] again only after the
-// next barrier, by which time the read of row i is done.
+// The waves of a block leave their sums of row i in red[i & 1]; after the
+// barrier its first wave adds them and writes the partial sums.  red[i & 1] is
+// written again only after the next barrier, by which time that read is done.
+//
+// Two sub-blocks per wave and one workgroup per CU keep 16 KB of loads in
+// flight per SIMD, in runs of 32 KB per row.  Step with an fp32 momentum of the
+// BERT-Base shape, n = 16, one process, same buffers: 4.37 ms with each row's
+// loads issued before the previous row's stores (two rows in flight), 4.21 ms
+// without; one sub-block per wave 4.35, four 4.32, workgroups of 8 waves
+// 4.54, of 4 (one sub-block) 4.68, two workgroups per CU 4.45, the packed pass
+// reading m for every worker 4.80.
 // ---------------------------------------------------------------------------
-template <bool FULL, class G, int SB>
+constexpr int kWalkSubBlocks = 2;
+constexpr int kWalkWaves = 16;
+constexpr int kWalkParts = kSubBlocks / kWalkSubBlocks;   // waves per block
+constexpr int kWalkBlocks = kWalkWaves / kWalkParts;      // blocks per workgroup
+
+template <bool WHOLE, class G>
 __device__ __forceinline__ void worker_rows_walk(
-    double (&red)[2][kRowWaves], const Tile &tile, int64_t t, int lane, int wv, int64_t num_tiles,
-    bool active, const v4f (&bm)[SB], const typename G::T *__restrict__ g, int64_t g_ld,
+    double (&red)[2][kWalkBlocks][kTileWords], const Tile *__restrict__ tiles, const Block &rec,
+    int64_t base, int lim, int sb0, int lane, int wb, bool active,
+    const v4f (&bm)[kWalkSubBlocks], const typename G::T *__restrict__ g, int64_t g_ld,
     float *__restrict__ err, int64_t err_ld, const float *__restrict__ scales, int64_t scales_ld,
-    uint64_t *__restrict__ bits, int64_t bits_ld, double *__restrict__ partial, int n_local,
-    float omb1)
+    uint64_t *__restrict__ bits, int64_t bits_ld, double *__restrict__ partial, int64_t num_tiles,
+    int n_local, float omb1)
 {
-    constexpr int W = kSubBlocks / SB;
-    const int sb0 = (wv % W) * SB;
-    v4f ga[SB], ca[SB], gb[SB], cb[SB];
-    float sa = 0.f, sb = 0.f;
-#define ROW_LOAD(i, gv, cv, sp) \
-    worker_row_load<FULL, G, SB>(tile, lane, sb0, i, g, g_ld, err, err_ld, scales, scales_ld, gv, cv, sp)
-#define ROW_STORE(i, gv, cv, sp)                                                                   \
-    do {                                                                                           \
-        const double acc = worker_row_store<FULL, SB>(tile, lane, sb0, bm, i, gv, cv, sp, err,     \
-                                                      err_ld, bits, bits_ld, omb1);                \
-        if (W == 1) {                                                                              \
-            if (lane == 0) partial[(int64_t)(i) * num_tiles + t] = acc;                            \
-        } else if (lane == 0) {                                                                    \
-            red[(i) & 1][wv] = acc;                                                                \
-        }                                                                                          \
-    } while (0)
-#define ROW_SUM(i)                                                                                 \
-    do {                                                                                           \
-        if (W > 1 && active && wv % W == 0 && lane == 0) {                                         \
-            double s_ = red[(i) & 1][wv];                                                          \
-            for (int k_ = 1; k_ < W; ++k_) s_ += red[(i) & 1][wv + k_];                            \
-            partial[(int64_t)(i) * num_tiles + t] = s_;                                            \
-        }                                                                                          \
-    } while (0)
-    if (active) ROW_LOAD(0, ga, ca, sa);
-    int i = 0;
-    for (; i + 2 < n_local; i += 2) {
-        if (active) ROW_LOAD(i + 1, gb, cb, sb);
-        if (active) ROW_STORE(i, ga, ca, sa);
-        __builtin_amdgcn_s_barrier();
-        ROW_SUM(i);
-        if (active) ROW_LOAD(i + 2, ga, ca, sa);
-        if (active) ROW_STORE(i + 1, gb, cb, sb);
-        __builtin_amdgcn_s_barrier();
-        ROW_SUM(i + 1);
+    constexpr int SB = kWalkSubBlocks;
+    int seg[SB], valid[SB];
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+        seg[b] = rec.seg;
+        valid[b] = 4;
+        if (!WHOLE) {
+            const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
+            valid[b] = 0;
+            if (active && li < lim) {
+                const Tile t = block_word_tile(tiles, rec, li >> 6);
+                seg[b] = t.seg;
+                valid[b] = tile_valid4(t, base + li);
+            }
+        }
     }
-    if (i + 1 < n_local) {
-        if (active) ROW_LOAD(i + 1, gb, cb, sb);
-        if (active) ROW_STORE(i, ga, ca, sa);
-        __builtin_amdgcn_s_barrier();
-        ROW_SUM(i);
-        if (active) ROW_STORE(i + 1, gb, cb, sb);
-        __builtin_amdgcn_s_barrier();
-        ROW_SUM(i + 1);
-    } else {
-        if (active) ROW_STORE(i, ga, ca, sa);
-        __builtin_amdgcn_s_barrier();
-        ROW_SUM(i);
+    g += base;
+    err += base;
+    bits += base >> 6;
+    const auto load = [&](int64_t i, v4f(&gv)[SB], v4f(&cv)[SB], float(&sp)[SB]) {
+        if (!active) return;
+#pragma unroll
+        for (int b = 0; b < SB; ++b) {
+            const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
+            gv[b] = ldgb4<WHOLE, G>(g + i * g_ld, li, lim);
+            cv[b] = ldb4<WHOLE>(err + i * err_ld, li, lim);
+            sp[b] = scales[i * scales_ld + seg[b]];
+        }
+    };
+    const auto finish = [&](int64_t i, const v4f(&gv)[SB], const v4f(&cv)[SB],
+                            const float(&sp)[SB]) {
+        double *sums = red[i & 1][wb];
+        if (active) {
+            double acc = worker_compute<WHOLE, SB>(sp, valid, bm, gv, cv, err + i * err_ld,
+                                                   bits + i * bits_ld, sb0, lane, lim, omb1, sums);
+            if (WHOLE) {
+                acc = wave_sum(acc);
+                if (lane == 0) sums[sb0 / SB] = acc;
+            }
+        }
+        __syncthreads();  // and the workgroup moves to the next row together
+        if (active && sb0 == 0)
+            block_partials<WHOLE>(partial + i * num_tiles, rec, sums, kWalkParts, lane);
+    };
+    for (int i = 0; i < n_local; ++i) {
+        v4f ga[SB], ca[SB];
+        float sa[SB];
+        load(i, ga, ca, sa);
+        finish(i, ga, ca, sa);
     }
-#undef ROW_LOAD
-#undef ROW_STORE
-#undef ROW_SUM
 }
 
 template <class G>
-__global__ __launch_bounds__(kRowBlock) void k_worker_rows(
-    const Tile *__restrict__ tiles, int64_t num_tiles, const float *__restrict__ m,
+__global__ __launch_bounds__(kWalkWaves *kWave) void k_worker_rows(
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
+    int64_t num_blocks, int64_t padded_len, int64_t num_tiles, const float *__restrict__ m,
     const typename G::T *__restrict__ g, int64_t g_ld, float *__restrict__ err, int64_t err_ld,
     const float *__restrict__ scales, int64_t scales_ld, uint64_t *__restrict__ bits,
-    int64_t bits_ld, double *__restrict__ partial, int n_local, float beta1, float omb1,
-    int64_t tile_base)
+    int64_t bits_ld, double *__restrict__ partial, int n_local, float beta1, float omb1)
 {
-    constexpr int SB = kWorkerSubBlocks;
-    constexpr int W = kSubBlocks / SB;
-    static_assert(W * kWorkerRowTiles == kRowWaves, "two waves per tile");
-    __shared__ double red[2][kRowWaves];
+    constexpr int SB = kWalkSubBlocks;
+    __shared__ double red[2][kWalkBlocks][kTileWords];
     const int lane = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x >> 6;
-    const int64_t t = tile_base + xcd_block() * kWorkerRowTiles + wv / W;
-    const bool active = t < num_tiles;
-    Tile tile{0, 0, 0};
-    if (active) tile = tiles[t];
-    const bool full = tile.len == kTileElems;
+    const int wv = wave_id();
+    const int wb = wv / kWalkParts;
+    const int sb0 = wv % kWalkParts * SB;
+    const int64_t blk = block_base + xcd_block() * kWalkBlocks + wb;
+    const bool active = blk < num_blocks;
+    const int64_t base = blk * kTileElems;
+    const int64_t room = padded_len - base;
+    const int lim = room < kTileElems ? (int)room : kTileElems;
+    Block rec{0, 0, 0, 0};
     v4f bm[SB];
-    if (full) {
-        beta1_momentum<true, false, SB>(bm, tile, lane, (wv % W) * SB, m, nullptr, nullptr, beta1);
-        worker_rows_walk<true, G, SB>(red, tile, t, lane, wv, num_tiles, true, bm, g, g_ld, err,
-                                      err_ld, scales, scales_ld, bits, bits_ld, partial, n_local, omb1);
-    } else {
-        beta1_momentum<false, false, SB>(bm, tile, lane, (wv % W) * SB, m, nullptr, nullptr, beta1);
-        worker_rows_walk<false, G, SB>(red, tile, t, lane, wv, num_tiles, active, bm, g, g_ld, err,
-                                       err_ld, scales, scales_ld, bits, bits_ld, partial, n_local,
-                                       omb1);
+    if (active) {
+        rec = load_block(blocks, blk);
+#pragma unroll
+        for (int b = 0; b < SB; ++b)
+            bm[b] = beta1 * ldb4<false>(m + base, (sb0 + b) * (kWave * 4) + 4 * lane, lim);
     }
+    if (rec.whole)
+        worker_rows_walk<true, G>(red, tiles, rec, base, lim, sb0, lane, wb, true, bm, g, g_ld,
+                                  err, err_ld, scales, scales_ld, bits, bits_ld, partial,
+                                  num_tiles, n_local, omb1);
+    else
+        worker_rows_walk<false, G>(red, tiles, rec, base, lim, sb0, lane, wb, active, bm, g, g_ld,
+                                   err, err_ld, scales, scales_ld, bits, bits_ld, partial,
+                                   num_tiles, n_local, omb1);
 }
 
 // ---------------------------------------------------------------------------
@@ -2362,39 +2288,21 @@ hipError_t launch_warmup(const DeviceTables &tb, float *x, float *m, float *v, c
 }
 
 template <bool PACKED, class G>
-static void launch_worker_t(const DeviceTables &tb, int64_t num_tiles, const float *m,
-                            const uint64_t *m_bits, const float *m_scales, const void *g,
-                            int64_t g_ld, float *err, int64_t err_ld, const float *scales,
-                            int64_t scales_ld, uint64_t *bits, int64_t bits_ld, double *partial,
-                            int n_local, int group, float beta1, hipStream_t s)
+static void launch_worker_items(const DeviceTables &tb, int64_t num_tiles, const float *m,
+                                const uint64_t *m_bits, const float *m_scales, const void *g,
+                                int64_t g_ld, float *err, int64_t err_ld, const float *scales,
+                                int64_t scales_ld, uint64_t *bits, int64_t bits_ld,
+                                double *partial, int n_local, float beta1, hipStream_t s)
 {
-    const float omb1 = 1.0f - beta1;
-    if constexpr (PACKED) {
-        const int64_t items = (int64_t)n_local * tb.num_blocks;
-        for (int64_t base = 0; base < items; base += kMaxPassItems) {
-            const int64_t count = std::min(items - base, kMaxPassItems);
-            hipLaunchKernelGGL((k_worker_pass<PACKED, G>),
-                               dim3((unsigned)worker_grid(count, kMaxPassItems)),
-                               dim3(kWave * kPassWaves<G>), kPassIdleLds<G>, s, tb.tiles,
-                               tb.blocks, tb.num_blocks, fast_div(tb.num_blocks), tb.padded_len,
-                               num_tiles, m, m_bits, m_scales, (const typename G::T *)g, g_ld, err, err_ld, scales,
-                               scales_ld, bits, bits_ld, partial, base, count, beta1, omb1);
-        }
-    } else {
-        (void)m_bits;
-        (void)m_scales;
-        (void)group;
-        // every launch but the last covers exactly kMaxLaunchTiles tiles (its
-        // grid has no spare workgroups), and the last one's spare waves see
-        // t >= num_tiles
-        static_assert(kMaxLaunchTiles % (kWorkerRowTiles * kXcds) == 0, "whole grids");
-        for (int64_t base = 0; base < num_tiles; base += kMaxLaunchTiles) {
-            const int64_t count = launch_piece(num_tiles, base);
-            hipLaunchKernelGGL(k_worker_rows<G>, dim3((unsigned)xcd_grid(count, kWorkerRowTiles)),
-                               dim3(kRowBlock), 0, s, tb.tiles, num_tiles, m,
-                               (const typename G::T *)g, g_ld, err, err_ld, scales, scales_ld,
-                               bits, bits_ld, partial, n_local, beta1, omb1, base);
-        }
+    const int64_t items = (int64_t)n_local * tb.num_blocks;
+    for (int64_t base = 0; base < items; base += kMaxPassItems) {
+        const int64_t count = std::min(items - base, kMaxPassItems);
+        hipLaunchKernelGGL((k_worker_pass<PACKED, G>),
+                           dim3((unsigned)worker_grid(count, kMaxPassItems)),
+                           dim3(kWave * kPassWaves<G>), kPassIdleLds<G>, s, tb.tiles, tb.blocks,
+                           tb.num_blocks, fast_div(tb.num_blocks), tb.padded_len, num_tiles, m,
+                           m_bits, m_scales, (const typename G::T *)g, g_ld, err, err_ld, scales,
+                           scales_ld, bits, bits_ld, partial, base, count, beta1, 1.0f - beta1);
     }
 }
 
@@ -2403,42 +2311,45 @@ static void launch_worker_g(const DeviceTables &tb, int64_t num_tiles, const flo
                             const uint64_t *m_bits, const float *m_scales, const void *g,
                             int64_t g_ld, float *err, int64_t err_ld, const float *scales,
                             int64_t scales_ld, uint64_t *bits, int64_t bits_ld, double *partial,
-                            int n_local, int group, float beta1, hipStream_t s)
+                            int n_local, float beta1, hipStream_t s)
 {
-    if (m)
-        launch_worker_t<false, G>(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld,
-                                  scales, scales_ld, bits, bits_ld, partial, n_local, group,
-                                  beta1, s);
-    else
-        launch_worker_t<true, G>(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld,
-                                 scales, scales_ld, bits, bits_ld, partial, n_local, group,
-                                 beta1, s);
+    if (!m) {
+        launch_worker_items<true, G>(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld,
+                                     scales, scales_ld, bits, bits_ld, partial, n_local, beta1, s);
+        return;
+    }
+    // One row has no other to share m with; and a small plan's row walk is a
+    // handful of workgroups walking n rows one round trip after another, where
+    // m read again by every worker comes from the caches (32 rows, step in us:
+    // 10^5 elements 103 -> 32, 10^6 137 -> 99; 2x10^6 164 in the walk, 188).
+    if (tb.num_blocks <= 1024 || n_local == 1) {
+        launch_worker_items<false, G>(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld,
+                                      scales, scales_ld, bits, bits_ld, partial, n_local, beta1,
+                                      s);
+        return;
+    }
+    for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
+        const int64_t count = launch_piece(tb.num_blocks, base);
+        hipLaunchKernelGGL(k_worker_rows<G>, dim3((unsigned)xcd_grid(count, kWalkBlocks)),
+                           dim3(kWalkWaves * kWave), 0, s, tb.tiles, tb.blocks, base, base + count,
+                           tb.padded_len, num_tiles, m, (const typename G::T *)g, g_ld, err,
+                           err_ld, scales, scales_ld, bits, bits_ld, partial, n_local, beta1,
+                           1.0f - beta1);
+    }
 }
 
 hipError_t launch_worker_pass(const DeviceTables &tb, int64_t num_tiles, const float *m,
                               const uint64_t *m_bits, const float *m_scales, const void *g,
                               int grad_dtype, int64_t g_ld, float *err, int64_t err_ld,
                               const float *scales, int64_t scales_ld, uint64_t *bits,
-                              int64_t bits_ld, double *partial, int n_local, int group,
-                              float beta1, hipStream_t s)
+                              int64_t bits_ld, double *partial, int n_local, float beta1,
+                              hipStream_t s)
 {
-    if (group < 1 || group > n_local) group = n_local;
-    switch (grad_dtype) {
-    case kGradBF16:
-        launch_worker_g<GradBF16>(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld,
-                                  scales, scales_ld, bits, bits_ld, partial, n_local, group,
-                                  beta1, s);
-        break;
-    case kGradF16:
-        launch_worker_g<GradF16>(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld,
-                                 scales, scales_ld, bits, bits_ld, partial, n_local, group,
-                                 beta1, s);
-        break;
-    default:
-        launch_worker_g<GradF32>(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld,
-                                 scales, scales_ld, bits, bits_ld, partial, n_local, group,
-                                 beta1, s);
-    }
+    const auto launch = grad_dtype == kGradBF16  ? launch_worker_g<GradBF16>
+                        : grad_dtype == kGradF16 ? launch_worker_g<GradF16>
+                                                 : launch_worker_g<GradF32>;
+    launch(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld, scales, scales_ld, bits,
+           bits_ld, partial, n_local, beta1, s);
     return hipGetLastError();
 }
 
