@@ -337,6 +337,11 @@ int onebit_l1_norm(onebit_plan plan, const float *v, void *workspace, double *ou
 int onebit_decode(onebit_plan plan, const uint64_t *bits, const float *scales, float *out,
                   onebit_stream stream);
 
+/* onebit_decode that also writes 0 to the padding elements of out, so that a
+ * buffer need not be cleared before. */
+int onebit_decode_padded(onebit_plan plan, const uint64_t *bits, const float *scales, float *out,
+                         onebit_stream stream);
+
 /* Explicit errors from the compensated form: for `rows` rows,
  *   delta_out[r*out_ld + e] = z - C[z] with z = err_state[r*err_ld + e] and
  *   the scale of e's segment from scales[r*scales_ld + q]
@@ -346,6 +351,13 @@ int onebit_decode(onebit_plan plan, const uint64_t *bits, const float *scales, f
  * pair consistent.
  * Errors: EINVAL, EALIGN, EHIP. */
 int onebit_error_materialize(onebit_plan plan, const float *err_state,
+                             int64_t err_ld, const float *scales,
+                             int64_t scales_ld, int32_t rows, float *delta_out,
+                             int64_t out_ld, onebit_stream stream);
+
+/* onebit_error_materialize that also writes 0 to the padding elements of each
+ * row of delta_out. */
+int onebit_error_materialize_padded(onebit_plan plan, const float *err_state,
                              int64_t err_ld, const float *scales,
                              int64_t scales_ld, int32_t rows, float *delta_out,
                              int64_t out_ld, onebit_stream stream);

@@ -45,12 +45,14 @@ SIGNATURES = {
     "onebit_step_events": [_vp, _vp, _vp, _vp, _vp, _i32, _i64, _vp, _i64, _vp, _vp, _vp, _vp,
                            _vp, _f32, _f32, _f32, _vp, _vp, _vp],
     "onebit_decode": [_vp, _vp, _vp, _vp, _vp],
+    "onebit_decode_padded": [_vp, _vp, _vp, _vp, _vp],
     "onebit_l1_norm": [_vp, _vp, _vp, _vp, _vp],
     "onebit_uncompressed_step": [_vp, _vp, _vp, _vp, _vp, _i32, _i64, _i32, _f32, _f32, _f32,
                                  _vp],
     "onebit_adam_message_step": [_vp, _vp, _vp, _vp, _vp, _vp, _f32, _f32, _f32, _f32, _i32,
                                  _i64, _vp],
     "onebit_error_materialize": [_vp, _vp, _i64, _vp, _i64, _i32, _vp, _i64, _vp],
+    "onebit_error_materialize_padded": [_vp, _vp, _i64, _vp, _i64, _i32, _vp, _i64, _vp],
     "onebit_status_str": [_i32],
     "onebit_last_error": [],
 }

@@ -774,8 +774,8 @@ int onebit_l1_norm(onebit_plan p, const float *v, void *workspace, double *out,
     return ONEBIT_OK;
 }
 
-int onebit_decode(onebit_plan p, const uint64_t *bits, const float *scales, float *out,
-                  onebit_stream stream)
+static int decode_impl(onebit_plan p, const uint64_t *bits, const float *scales, float *out,
+                       int zero_padding, onebit_stream stream)
 {
     TRY(check_plan(p));
     TRY(check_u64(p, bits, "bits"));
@@ -783,14 +783,27 @@ int onebit_decode(onebit_plan p, const uint64_t *bits, const float *scales, floa
     if (!aligned(scales, 4)) return fail(ONEBIT_EALIGN, "scales misaligned");
     TRY(check_f32(p, out, "out"));
     if (p->T == 0) return ONEBIT_OK;
-    TRY_HIP(onebit::launch_decode(p->tb, p->T, bits, scales, out, (hipStream_t)stream),
+    TRY_HIP(onebit::launch_decode(p->tb, bits, scales, out, zero_padding, (hipStream_t)stream),
             "decode kernel launch");
     return ONEBIT_OK;
 }
 
-int onebit_error_materialize(onebit_plan p, const float *err_state, int64_t err_ld,
-                             const float *scales, int64_t scales_ld, int32_t rows,
-                             float *delta_out, int64_t out_ld, onebit_stream stream)
+int onebit_decode(onebit_plan p, const uint64_t *bits, const float *scales, float *out,
+                  onebit_stream stream)
+{
+    return decode_impl(p, bits, scales, out, 0, stream);
+}
+
+int onebit_decode_padded(onebit_plan p, const uint64_t *bits, const float *scales, float *out,
+                         onebit_stream stream)
+{
+    return decode_impl(p, bits, scales, out, 1, stream);
+}
+
+static int materialize_impl(onebit_plan p, const float *err_state, int64_t err_ld,
+                            const float *scales, int64_t scales_ld, int32_t rows,
+                            float *delta_out, int64_t out_ld, int zero_padding,
+                            onebit_stream stream)
 {
     TRY(check_plan(p));
     TRY(check_f32(p, err_state, "err_state"));
@@ -804,10 +817,26 @@ int onebit_error_materialize(onebit_plan p, const float *err_state, int64_t err_
     if (delta_out == err_state && out_ld != err_ld)
         return fail(ONEBIT_EINVAL, "in-place materialize needs out_ld == err_ld");
     if (p->T == 0) return ONEBIT_OK;
-    TRY_HIP(onebit::launch_materialize(p->tb, p->T, rows, err_state, err_ld, scales, scales_ld,
-                                       delta_out, out_ld, (hipStream_t)stream),
+    TRY_HIP(onebit::launch_materialize(p->tb, rows, err_state, err_ld, scales, scales_ld,
+                                       delta_out, out_ld, zero_padding, (hipStream_t)stream),
             "materialize kernel launch");
     return ONEBIT_OK;
+}
+
+int onebit_error_materialize(onebit_plan p, const float *err_state, int64_t err_ld,
+                             const float *scales, int64_t scales_ld, int32_t rows,
+                             float *delta_out, int64_t out_ld, onebit_stream stream)
+{
+    return materialize_impl(p, err_state, err_ld, scales, scales_ld, rows, delta_out, out_ld, 0,
+                            stream);
+}
+
+int onebit_error_materialize_padded(onebit_plan p, const float *err_state, int64_t err_ld,
+                                    const float *scales, int64_t scales_ld, int32_t rows,
+                                    float *delta_out, int64_t out_ld, onebit_stream stream)
+{
+    return materialize_impl(p, err_state, err_ld, scales, scales_ld, rows, delta_out, out_ld, 1,
+                            stream);
 }
 
 }  // extern "C"

@@ -103,8 +103,9 @@ hipError_t launch_uncompressed(const DeviceTables &tb, float *x, float *m,
 hipError_t launch_l1_norm(const DeviceTables &tb, const float *v, double *partial, double *out,
                           hipStream_t s);
 
-hipError_t launch_decode(const DeviceTables &tb, int64_t num_tiles, const uint64_t *bits,
-                         const float *scales, float *out, hipStream_t s);
+// zero_padding (here and below): padding elements are written as 0.
+hipError_t launch_decode(const DeviceTables &tb, const uint64_t *bits, const float *scales,
+                         float *out, int zero_padding, hipStream_t s);
 
 // Segment scales from per-tile partial sums.  Worker form (cnt = 0): all
 // num_segments segments of each of `rows` rows, scale[i*scales_ld + q] from
@@ -149,8 +150,8 @@ constexpr size_t kScratchBytes = (size_t)96 << 20;
 constexpr int kMaxScratchDevices = 64;
 hipError_t scratch_address(int device, void **ptr);
 
-hipError_t launch_materialize(const DeviceTables &tb, int64_t num_tiles, int rows,
-                              const float *err, int64_t err_ld, const float *scales,
-                              int64_t scales_ld, float *out, int64_t out_ld, hipStream_t s);
+hipError_t launch_materialize(const DeviceTables &tb, int rows, const float *err, int64_t err_ld,
+                              const float *scales, int64_t scales_ld, float *out, int64_t out_ld,
+                              int zero_padding, hipStream_t s);
 
 }  // namespace onebit

@@ -2081,73 +2081,81 @@ __global__ __launch_bounds__(kBlock) void k_update(
 }
 
 // ---------------------------------------------------------------------------
-// Explicit error from the compensated form.
+// Explicit values: the error from the compensated form, and the decoded
+// message (+-scale of each element's segment).  A workgroup takes one block of
+// one row, one sub-block per wave, every load before its stores (a wave that
+// walked the rows of its tile lane by lane took 362 us for 8 rows of 30 million
+// elements, 284 us now).  zero_padding: padding elements are written
+// as 0 (the caller then need not clear the buffer first); else they are left.
 // ---------------------------------------------------------------------------
+// Zeros past the first `valid` elements; returns how many to store.
+__device__ __forceinline__ int pad_zeros(v4f &v, int valid, int li, int lim, int zero_padding)
+{
+    if (!zero_padding) return valid;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        if (c >= valid) v[c] = 0.f;
+    return li < lim ? 4 : 0;
+}
+
 __global__ __launch_bounds__(kBlock) void k_materialize(
-    const Tile *__restrict__ tiles, int64_t num_tiles, int rows, const float *err,
-    int64_t err_ld, const float *__restrict__ scales, int64_t scales_ld, float *out,
-    int64_t out_ld)
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t num_blocks,
+    FastDiv by_blocks, int64_t padded_len, const float *err, int64_t err_ld,
+    const float *__restrict__ scales, int64_t scales_ld, float *out, int64_t out_ld,
+    int zero_padding, int64_t item_base, int64_t num_items)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t t = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
-    if (t >= num_tiles) return;
-    const Tile tile = tiles[t];
-    const int len = tile.len;
-    const int64_t base = tile.start;
-    for (int r = 0; r < rows; ++r) {
-        const float s = scales[(int64_t)r * scales_ld + tile.seg];
-#pragma unroll
-        for (int b = 0; b < kSubBlocks; ++b) {
-            const int li = b * (kWave * 4) + 4 * lane;
-            if (li >= len) break;
-            v4f zv = ld4<false>(err + (int64_t)r * err_ld + base, li, len);
-#pragma unroll
-            for (int c = 0; c < 4; ++c) zv[c] = error_of(zv[c], s);
-            st4<false>(out + (int64_t)r * out_ld + base, li, len, zv);
+    const ItemWalk walk = xcd_item_walk(blockIdx.x, gridDim.x, num_items);
+    if (walk.first >= walk.end) return;
+    const int64_t item = item_base + walk.first;
+    const int64_t r = (int64_t)(((uint64_t)item * by_blocks.mul) >> by_blocks.shift);
+    const int64_t blk = item - r * num_blocks;
+    const int64_t base = blk * kTileElems;
+    const int64_t room = padded_len - base;
+    const int lim = room < kTileElems ? (int)room : kTileElems;
+    const int li = (threadIdx.x >> 6) * (kWave * 4) + 4 * lane;
+    const float *src = err + r * err_ld + base;
+    v4f zv = lim == kTileElems ? ldb4<true>(src, li, lim) : ldb4<false>(src, li, lim);
+    const Block rec = load_block(blocks, blk);
+    scales += r * scales_ld;
+    float s = scales[rec.seg];
+    int valid = 4;
+    if (!rec.whole) {
+        valid = 0;
+        if (li < lim) {
+            const Tile t = block_word_tile(tiles, rec, li >> 6);
+            valid = tile_valid4(t, base + li);
+            s = scales[t.seg];
         }
     }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) zv[c] = error_of(zv[c], s);
+    valid = pad_zeros(zv, valid, li, lim, zero_padding);
+    stb4<false>(out + r * out_ld + base, li, valid, zv);
 }
 
-// ---------------------------------------------------------------------------
-// Decoded message: out = +-scale of each element's segment.
-// ---------------------------------------------------------------------------
-template <bool FULL>
-__device__ __forceinline__ void decode_tile(const Tile &tile, int lane,
-                                            const uint64_t *__restrict__ bits, float s,
-                                            float *__restrict__ out)
-{
-    const int len = tile.len;
-    const int64_t base = tile.start;
-    uint64_t word[kSubBlocks];
-#pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b) {
-        const int li = b * (kWave * 4) + 4 * lane;
-        word[b] = (FULL || li < len) ? bits[(base >> 6) + 4 * b + (lane >> 4)] : 0ull;
-    }
-#pragma unroll
-    for (int b = 0; b < kSubBlocks; ++b) {
-        const int li = b * (kWave * 4) + 4 * lane;
-        const uint32_t nib = (uint32_t)(word[b] >> (4 * (lane & 15))) & 0xFu;
-        v4f v;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) v[c] = ((nib >> c) & 1u) ? s : -s;
-        st4<FULL>(out + base, li, len, v);
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_decode(const Tile *__restrict__ tiles,
-                                                   int64_t num_tiles,
-                                                   const uint64_t *__restrict__ bits,
-                                                   const float *__restrict__ scales,
-                                                   float *__restrict__ out)
+__global__ __launch_bounds__(kBlock) void k_decode(
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
+    int64_t num_blocks, int64_t padded_len, const uint64_t *__restrict__ bits,
+    const float *__restrict__ scales, float *__restrict__ out, int zero_padding)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int64_t t = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
-    if (t >= num_tiles) return;
-    const Tile tile = tiles[t];
-    const float s = scales[tile.seg];
-    if (tile.len == kTileElems) decode_tile<true>(tile, lane, bits, s, out);
-    else decode_tile<false>(tile, lane, bits, s, out);
+    const int64_t blk = block_base + xcd_block();
+    if (blk >= num_blocks) return;
+    const int64_t base = blk * kTileElems;
+    const int64_t room = padded_len - base;
+    const int lim = room < kTileElems ? (int)room : kTileElems;
+    const int li = (threadIdx.x >> 6) * (kWave * 4) + 4 * lane;
+    const uint64_t word = li < lim ? bits[(base + li) >> 6] : 0;
+    const Block rec = load_block(blocks, blk);
+    const float s0 = scales[rec.seg];
+    const Lane4 l = rec.whole ? lane_message<true>(tiles, rec, base, li, lim, word, s0, scales)
+                              : lane_message<false>(tiles, rec, base, li, lim, word, s0, scales);
+    v4f v;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = with_sign(l.s, l.nib, c);
+    const int valid = pad_zeros(v, l.valid, li, lim, zero_padding);
+    stb4<false>(out + base, li, valid, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -2409,11 +2417,15 @@ hipError_t launch_l1_norm(const DeviceTables &tb, const float *v, double *partia
     return hipGetLastError();
 }
 
-hipError_t launch_decode(const DeviceTables &tb, int64_t num_tiles, const uint64_t *bits,
-                         const float *scales, float *out, hipStream_t s)
+hipError_t launch_decode(const DeviceTables &tb, const uint64_t *bits, const float *scales,
+                         float *out, int zero_padding, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_decode, dim3((unsigned)blocks_for(num_tiles)), dim3(kBlock), 0, s, tb.tiles,
-                       num_tiles, bits, scales, out);
+    for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
+        const int64_t count = launch_piece(tb.num_blocks, base);
+        hipLaunchKernelGGL(k_decode, dim3((unsigned)xcd_grid(count, 1)), dim3(kBlock), 0, s,
+                           tb.tiles, tb.blocks, base, base + count, tb.padded_len, bits, scales,
+                           out, zero_padding);
+    }
     return hipGetLastError();
 }
 
@@ -2534,12 +2546,18 @@ hipError_t launch_update(const DeviceTables &tb, const uint64_t *sbits, const fl
     return hipGetLastError();
 }
 
-hipError_t launch_materialize(const DeviceTables &tb, int64_t num_tiles, int rows,
-                              const float *err, int64_t err_ld, const float *scales,
-                              int64_t scales_ld, float *out, int64_t out_ld, hipStream_t s)
+hipError_t launch_materialize(const DeviceTables &tb, int rows, const float *err, int64_t err_ld,
+                              const float *scales, int64_t scales_ld, float *out, int64_t out_ld,
+                              int zero_padding, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_materialize, dim3((unsigned)blocks_for(num_tiles)), dim3(kBlock), 0, s,
-                       tb.tiles, num_tiles, rows, err, err_ld, scales, scales_ld, out, out_ld);
+    const int64_t items = (int64_t)rows * tb.num_blocks;
+    for (int64_t base = 0; base < items; base += kMaxPassItems) {
+        const int64_t count = std::min(items - base, kMaxPassItems);
+        hipLaunchKernelGGL(k_materialize, dim3((unsigned)worker_grid(count, kMaxPassItems)),
+                           dim3(kBlock), 0, s, tb.tiles, tb.blocks, tb.num_blocks,
+                           fast_div(tb.num_blocks), tb.padded_len, err, err_ld, scales, scales_ld,
+                           out, out_ld, zero_padding, base, count);
+    }
     return hipGetLastError();
 }
 

@@ -312,8 +312,10 @@ def onebit_step_noalloc(plan, x, m, v_frozen, grads, worker_err, server_err, wor
     call("onebit_step_noalloc", *args, _stream(stream))
 
 
-def onebit_decode(plan, bits, scales, out, stream=None):
-    call("onebit_decode", plan.handle, _ptr(bits, torch.int64, "bits", plan.W),
+def onebit_decode(plan, bits, scales, out, stream=None, zero_padding=False):
+    """zero_padding: write 0 to the padding elements, which are left as they
+    are otherwise."""
+    call("onebit_decode_padded" if zero_padding else "onebit_decode", plan.handle, _ptr(bits, torch.int64, "bits", plan.W),
          _ptr(scales, torch.float32, "scales", plan.S), _ptr(out, torch.float32, "out", plan.D),
          _stream(stream))
 
@@ -345,10 +347,13 @@ def onebit_l1_norm(plan, v, workspace, out, stream=None):
          _ptr(out, torch.float64, "out", 1), _stream(stream))
 
 
-def onebit_error_materialize(plan, err_state, scales, delta_out, rows=None, stream=None):
+def onebit_error_materialize(plan, err_state, scales, delta_out, rows=None, stream=None,
+                             zero_padding=False):
+    """zero_padding: as in onebit_decode."""
     r = _rows(err_state) if rows is None else rows
     D = plan.D
-    call("onebit_error_materialize", plan.handle,
+    call("onebit_error_materialize_padded" if zero_padding else "onebit_error_materialize",
+         plan.handle,
          _ptr(err_state, torch.float32, "err_state", D, r), _ld(err_state),
          _ptr(scales, torch.float32, "scales", plan.S, r), _ld(scales), r,
          _ptr(delta_out, torch.float32, "delta_out", D, r), _ld(delta_out), _stream(stream))
@@ -490,17 +495,19 @@ class State:
 
     def momentum(self):
         if self.compression_steps > 1 and self.packed_momentum:
-            out = torch.zeros_like(self.m)
-            onebit_decode(self.plan, self.server_bits, self.server_scales, out)
+            out = torch.empty_like(self.m)
+            onebit_decode(self.plan, self.server_bits, self.server_scales, out, zero_padding=True)
             return out
         return self.m
 
     def worker_delta(self):
-        out = torch.zeros_like(self.worker_err)
-        onebit_error_materialize(self.plan, self.worker_err, self.worker_scales, out)
+        out = torch.empty_like(self.worker_err)
+        onebit_error_materialize(self.plan, self.worker_err, self.worker_scales, out,
+                                 zero_padding=True)
         return out
 
     def server_delta(self):
-        out = torch.zeros_like(self.server_err)
-        onebit_error_materialize(self.plan, self.server_err, self.server_scales, out, rows=1)
+        out = torch.empty_like(self.server_err)
+        onebit_error_materialize(self.plan, self.server_err, self.server_scales, out, rows=1,
+                                 zero_padding=True)
         return out

@@ -76,6 +76,20 @@ def test_short_tiles_free_running(dev, name, numel, n, packed, grad_dtype):
                        ("worker delta", st.worker_delta(), ref.delta),
                        ("server delta", st.server_delta(), ref.delta_bar)):
         check_fp(what, host(a), b, mask=mask)
+    # explicit values leave the padding of a caller's buffer alone unless asked
+    for got, fill in ((torch.full_like(st.x, PAD), False), (torch.full_like(st.x, PAD), True)):
+        ob.onebit_decode(plan, st.server_bits, st.server_scales, got, zero_padding=fill)
+        err = got.clone() if fill else torch.full_like(got, PAD)
+        ob.onebit_error_materialize(plan, st.server_err, st.server_scales, err, rows=1,
+                                    zero_padding=fill)
+        check_fp("decoded", host(got), ref.m, mask=mask)
+        check_fp("server delta", host(err), ref.delta_bar, mask=mask)
+        for t in (got, err):
+            assert bool((t[pad] == (0.0 if fill else PAD)).all())
+    for t in (st.momentum() if packed else torch.zeros(1, device=dev), st.worker_delta(),
+              st.server_delta()):
+        if t.shape[-1] == plan.D:
+            assert bool((t[..., pad] == 0).all())
     # the comparison steps on the same layout
     m, v, x = host(st.momentum()).copy(), host(st.v).copy(), host(st.x).copy()
     st.m.copy_(torch.from_numpy(m))
