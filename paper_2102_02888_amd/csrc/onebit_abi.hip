@@ -29,6 +29,7 @@ struct onebit_plan_s {
     int32_t K = 0, n = 0;
     int64_t d = 0, D = 0, W = 0, S = 0, T = 0;
     int64_t max_seg_tiles = 0;                          // most tiles in one segment
+    int64_t tile_pairs = 0;  // sum over segments of their tiles squared
     std::vector<int64_t> tensor_off, chunk_len, seg_begin, seg_end;
     std::vector<int64_t> seg_tile_begin, seg_tile_end;  // [S]
     std::vector<int64_t> chunk_tile_begin;              // [n+1], into chunk_tiles
@@ -92,6 +93,49 @@ constexpr size_t kServerTableBudget = (size_t)32 << 20;
 // (1-3 us on calls of 1,024 to 16,384 tiles with n = 4 to 32).
 constexpr int64_t kServerTableMinTiles = 4;
 constexpr int64_t kServerTableMinWork = 32768;
+
+// Whether the chunk owners' call over [begin, end) takes its lookup tables from
+// the workspace.
+bool server_uses_tables(const onebit_plan_s *p, int32_t begin, int32_t end)
+{
+    const int64_t tc = p->chunk_tile_begin[end] - p->chunk_tile_begin[begin];
+    const int64_t owned = (int64_t)p->K * (end - begin);
+    const bool worth = tc >= kServerTableMinTiles * owned &&
+                       tc * ((p->n + 7) / 8) >= kServerTableMinWork;
+    return p->table_bytes > 0 &&
+           (p->server_tables == ONEBIT_SERVER_TABLES_ON ||
+            (p->server_tables == ONEBIT_SERVER_TABLES_AUTO && worth));
+}
+
+// On small plans the fused step leaves out the two finalize launches: the chunk
+// owners' pass forms the workers' scales, and the update the owners', from the
+// partial sums of each tile's segment.  A launch costs about 3.3 us of the host
+// and 2 to 5 us of the GPU; forming costs every tile a few dependent loads and
+// its segment's partial sums again.  Measured (fp32, us a step, with both
+// finalize launches / worker scales formed / owners' formed / both): 10^5
+// elements n = 8 32.4 / 29.3 / 29.6 / 25.9; 2^20, n = 4 32.9 / 28.8 / 28.9 /
+// 26.0; 160 tensors up to 2^16, n = 8 46.8 / 44.5 / 45.8 / 43.3; 40 tensors up
+// to 2^20, n = 8 83.4 / 81.2 / 85.3 / 82.7; 2x10^6, n = 16 83.6 / 83.7 / 85.0 /
+// 84.8; 4x10^6, n = 16 148 / 153 / 157 / 162; 160 tensors up to 2^20, n = 4 183 /
+// 186 / 207 / 209.
+constexpr int64_t kFormMaxSegTiles = 256;
+
+// Worker scales: a tile reads n rows of its segment's partial sums, at most
+// 1,024 on average, and there are at most 8,192 tiles (no lookup tables then).
+bool forms_worker_scales(const onebit_plan_s *p)
+{
+    return p->T > 0 && p->T <= 8192 && p->max_seg_tiles <= kFormMaxSegTiles &&
+           p->n <= onebit::kServerRowBatch && p->n * p->tile_pairs <= 1024 * p->T &&
+           !server_uses_tables(p, 0, p->n);
+}
+
+// Owners' scales: each of the update's many short waves waits for them, so the
+// plan is a single round of waves, or a few with short segments.
+bool forms_server_scales(const onebit_plan_s *p)
+{
+    return p->T > 0 && p->max_seg_tiles <= kFormMaxSegTiles &&
+           (p->T <= 1200 || (p->T <= 4096 && p->tile_pairs <= 16 * p->T));
+}
 
 int check_plan(const onebit_plan_s *p)
 {
@@ -226,6 +270,7 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
         p->seg_tile_begin[q] = at;
         p->seg_tile_end[q] = at += cnt;
         p->max_seg_tiles = std::max(p->max_seg_tiles, cnt);
+        p->tile_pairs += cnt * cnt;
         server_block_count += onebit::server_blocks_of(cnt);
     }
     p->T = tile_count;
@@ -255,7 +300,7 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
     for (int64_t q = 0, t = 0; q < p->S; ++q) {
         const int64_t en = p->seg_end[q];
         segs[q] = onebit::Segment{en - p->seg_begin[q], (int32_t)p->seg_tile_begin[q],
-                                  (int32_t)(p->seg_tile_end[q] - p->seg_tile_begin[q])};
+                                  (int32_t)(p->seg_tile_end[q] - p->seg_tile_begin[q]), 0, {}};
         for (int64_t s = p->seg_begin[q]; s < en; ++t) {
             const int64_t next = std::min<int64_t>(en, (s / kTileElems + 1) * kTileElems);
             tiles[t].start = s;
@@ -268,6 +313,10 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
             blocks[blk].starts |= 1u << (s % kTileElems / 64);
             s = next;
         }
+    }
+    for (int64_t q = p->S, next = p->S; q-- > 0;) {
+        segs[q].next = (int32_t)next;
+        if (segs[q].tiles > 0) next = q;
     }
     // the tiles of chunk owner j, chunk-major, as one contiguous range of
     // chunk_tiles, and its shared-table workgroups in the same order
@@ -306,6 +355,7 @@ int plan_create_impl(const int64_t *tensor_numel, int32_t num_tensors, int32_t n
     p->tb.tiles = (const Tile *)base;
     p->tb.chunk_tiles = (const int32_t *)(base + tiles_bytes);
     p->tb.segs = (const onebit::Segment *)(base + seg0);
+    p->tb.num_segments = p->S;
     p->tb.server_blocks = (const int32_t *)(base + sblocks0);
     p->tb.blocks = (const onebit::Block *)(base + blocks0);
     p->tb.num_blocks = num_blocks;
@@ -356,7 +406,7 @@ int run_worker(const onebit_plan_s *p, const float *m, const uint64_t *m_bits,
                const float *m_scales, const void *grads, int32_t grad_dtype, int64_t grad_ld,
                int32_t n_local, float *worker_err, int64_t err_ld, uint64_t *worker_bits,
                int64_t bits_ld, float *worker_scales, int64_t scales_ld, float beta1,
-               void *workspace, hipStream_t s)
+               void *workspace, bool finalize, hipStream_t s)
 {
     double *part = (double *)((char *)workspace + worker_partial_offset(p));
     if (p->T > 0)
@@ -364,6 +414,7 @@ int run_worker(const onebit_plan_s *p, const float *m, const uint64_t *m_bits,
                                            grad_ld, worker_err, err_ld, worker_scales, scales_ld,
                                            worker_bits, bits_ld, part, n_local, beta1, s),
                 "worker kernel launch");
+    if (!finalize) return ONEBIT_OK;
     TRY_HIP(onebit::launch_finalize(p->tb, p->max_seg_tiles, p->S, n_local, p->n, 0, 0, part, p->T,
                                     worker_scales, scales_ld, s),
             "worker scale kernel launch");
@@ -409,22 +460,23 @@ int check_server(const onebit_plan_s *p, int32_t server_begin, int32_t server_en
     return ONEBIT_OK;
 }
 
+// form_worker: worker_scales is formed by the pass from the workers' partial
+// sums in the workspace (and written); finalize: the chunk owners' scales are
+// (otherwise the update forms them).
 int run_server(const onebit_plan_s *p, int32_t server_begin, int32_t server_end,
                const uint64_t *worker_bits, int64_t bits_ld, int64_t bits_word_base,
-               const float *worker_scales, int64_t scales_ld, int64_t scales_seg_base,
+               float *worker_scales, int64_t scales_ld, int64_t scales_seg_base,
                float *server_err, uint64_t *server_bits, float *server_scales, void *workspace,
-               hipStream_t s)
+               bool form_worker, bool finalize, hipStream_t s)
 {
     const int64_t tb = p->chunk_tile_begin[server_begin];
     const int64_t tc = p->chunk_tile_begin[server_end] - tb;
     double *part = (double *)((char *)workspace + server_partial_offset(p));
     const int nown = server_end - server_begin;
     const int64_t owned = (int64_t)p->K * nown;
-    const bool worth = tc >= kServerTableMinTiles * owned &&
-                       tc * ((p->n + 7) / 8) >= kServerTableMinWork;
-    const bool use_tables = p->table_bytes > 0 &&
-                            (p->server_tables == ONEBIT_SERVER_TABLES_ON ||
-                             (p->server_tables == ONEBIT_SERVER_TABLES_AUTO && worth));
+    const bool use_tables = server_uses_tables(p, server_begin, server_end);
+    const double *wpart =
+        form_worker ? (const double *)((char *)workspace + worker_partial_offset(p)) : nullptr;
     double *tables = use_tables ? (double *)((char *)workspace + server_table_offset(p)) : nullptr;
     int32_t *flags = use_tables ? (int32_t *)((char *)workspace + server_flag_offset(p)) : nullptr;
     const int64_t bb = p->chunk_block_begin[server_begin];
@@ -433,9 +485,10 @@ int run_server(const onebit_plan_s *p, int32_t server_begin, int32_t server_end,
         TRY_HIP(onebit::launch_server_pass(p->tb, tb, tc, p->n, worker_bits, bits_ld,
                                            bits_word_base, worker_scales, scales_ld,
                                            scales_seg_base, server_err, server_scales,
-                                           server_bits, part, p->K, server_begin, nown, tables,
-                                           flags, p->tb.server_blocks + bb, nb, s),
+                                           server_bits, part, wpart, p->T, p->K, server_begin,
+                                           nown, tables, flags, p->tb.server_blocks + bb, nb, s),
                 "server kernel launch");
+    if (!finalize) return ONEBIT_OK;
     TRY_HIP(onebit::launch_finalize(p->tb, p->max_seg_tiles, owned, 1, p->n, server_begin, nown,
                                     part, p->T, server_scales, 0, s),
             "server scale kernel launch");
@@ -455,12 +508,17 @@ int check_update(const onebit_plan_s *p, const uint64_t *server_bits,
     return ONEBIT_OK;
 }
 
-int run_update(const onebit_plan_s *p, const uint64_t *server_bits, const float *server_scales,
-               float *x, float *m_out, const float *v_frozen, float lr, float eps, hipStream_t s)
+// workspace != NULL: server_scales is formed by the pass from the chunk owners'
+// partial sums there (and written).
+int run_update(const onebit_plan_s *p, const uint64_t *server_bits, float *server_scales,
+               const void *workspace, float *x, float *m_out, const float *v_frozen, float lr,
+               float eps, hipStream_t s)
 {
     if (p->T == 0) return ONEBIT_OK;
-    TRY_HIP(onebit::launch_update(p->tb, server_bits, server_scales, x, m_out, v_frozen,
-                                  lr, eps, s),
+    const double *part =
+        workspace ? (const double *)((const char *)workspace + server_partial_offset(p)) : nullptr;
+    TRY_HIP(onebit::launch_update(p->tb, server_bits, server_scales, part, x, m_out, v_frozen, lr,
+                                  eps, s),
             "update kernel launch");
     return ONEBIT_OK;
 }
@@ -487,15 +545,18 @@ int step_impl(onebit_plan_s *p, float *x, float *m, const float *v_frozen, const
     TRY(check_server(p, 0, p->n, worker_bits, p->W, 0, worker_scales, p->S, 0, server_err,
                      server_bits, server_scales, workspace));
     TRY(check_update(p, server_bits, server_scales, x, m, v_frozen));
+    const bool form_worker = forms_worker_scales(p);
+    const bool form_server = forms_server_scales(p);
     TRY(record(events, 0, s));
     TRY(run_worker(p, m, server_bits, server_scales, grads, grad_dtype, grad_ld, p->n,
                    worker_err, err_ld, worker_bits, p->W, worker_scales, p->S, beta1, workspace,
-                   s));
+                   !form_worker, s));
     TRY(record(events, 1, s));
     TRY(run_server(p, 0, p->n, worker_bits, p->W, 0, worker_scales, p->S, 0, server_err,
-                   server_bits, server_scales, workspace, s));
+                   server_bits, server_scales, workspace, form_worker, !form_server, s));
     TRY(record(events, 2, s));
-    TRY(run_update(p, server_bits, server_scales, x, m, v_frozen, lr, eps, s));
+    TRY(run_update(p, server_bits, server_scales, form_server ? workspace : nullptr, x, m,
+                   v_frozen, lr, eps, s));
     return record(events, 3, s);
 }
 
@@ -641,7 +702,7 @@ int onebit_worker_compress(onebit_plan p, const float *m, const uint64_t *m_bits
     TRY(check_worker(p, m, m_bits, m_scales, grads, grad_dtype, grad_ld, n_local, worker_err,
                      err_ld, worker_bits, bits_ld, worker_scales, scales_ld, workspace));
     return run_worker(p, m, m_bits, m_scales, grads, grad_dtype, grad_ld, n_local, worker_err,
-                      err_ld, worker_bits, bits_ld, worker_scales, scales_ld, beta1, workspace,
+                      err_ld, worker_bits, bits_ld, worker_scales, scales_ld, beta1, workspace, true,
                       (hipStream_t)stream);
 }
 
@@ -657,8 +718,8 @@ int onebit_server_reduce_compress(onebit_plan p, int32_t server_begin, int32_t s
                      worker_scales, scales_ld, scales_seg_base, server_err, server_bits,
                      server_scales, workspace));
     return run_server(p, server_begin, server_end, worker_bits, bits_ld, bits_word_base,
-                      worker_scales, scales_ld, scales_seg_base, server_err, server_bits,
-                      server_scales, workspace, (hipStream_t)stream);
+                      const_cast<float *>(worker_scales), scales_ld, scales_seg_base, server_err,
+                      server_bits, server_scales, workspace, false, true, (hipStream_t)stream);
 }
 
 int onebit_decompress_update(onebit_plan p, const uint64_t *server_bits,
@@ -667,8 +728,8 @@ int onebit_decompress_update(onebit_plan p, const uint64_t *server_bits,
 {
     TRY(check_plan(p));
     TRY(check_update(p, server_bits, server_scales, x, m_out, v_frozen));
-    return run_update(p, server_bits, server_scales, x, m_out, v_frozen, lr, eps,
-                      (hipStream_t)stream);
+    return run_update(p, server_bits, const_cast<float *>(server_scales), nullptr, x, m_out,
+                      v_frozen, lr, eps, (hipStream_t)stream);
 }
 
 int onebit_step(onebit_plan p, float *x, float *m, const float *v_frozen, const void *grads,

@@ -37,10 +37,12 @@ struct Block {
 };
 
 // A segment's range of the tile list and its length.
-struct Segment {
+struct alignas(16) Segment {
     int64_t len;
     int32_t tile;   // its first tile
     int32_t tiles;  // 0 for an empty segment
+    int32_t next;   // the next segment that is not empty (num_segments: none)
+    int32_t pad[3];
 };
 
 // Device-side layout tables owned by a plan.
@@ -51,6 +53,7 @@ struct DeviceTables {
     int64_t padded_len;            // D
     const int32_t *chunk_tiles;    // [T], tile ids in chunk-major order
     const Segment *segs;           // [S]
+    int64_t num_segments;          // S
     const int32_t *server_blocks;  // chunk owners' shared-table workgroups, chunk-major
                                    // (entries of onebit_grid.h's server_block_entry)
 };
@@ -126,18 +129,25 @@ size_t server_table_bytes(int n, int64_t segments);
 // owned segments' tables are built there first and copied by the pass, which
 // for n <= 32 runs the num_blocks shared-table workgroups of server_blocks
 // (the call's range of DeviceTables::server_blocks); tables == NULL: the
-// pass builds them per tile.
+// pass builds them per tile.  wpartial != NULL (only with every chunk owned,
+// tables == NULL, n <= kServerRowBatch and both bases 0): wscales is written
+// instead of read, from the workers' per-tile partial sums (rows of wpart_ld),
+// as in launch_update.
 hipError_t launch_server_pass(const DeviceTables &tb, int64_t tile_begin, int64_t tile_count,
                               int n, const uint64_t *wbits, int64_t bits_ld,
-                              int64_t bits_word_base, const float *wscales, int64_t scales_ld,
+                              int64_t bits_word_base, float *wscales, int64_t scales_ld,
                               int64_t scales_seg_base, float *serr, float *sscales,
-                              uint64_t *sbits, double *partial, int num_tensors, int cb,
+                              uint64_t *sbits, double *partial, const double *wpartial,
+                              int64_t wpart_ld, int num_tensors, int cb,
                               int nown, double *tables, int32_t *flags,
                               const int32_t *server_blocks, int64_t num_blocks, hipStream_t s);
 
-hipError_t launch_update(const DeviceTables &tb, const uint64_t *sbits, const float *sscales,
-                         float *x, float *m_out, const float *v, float lr, float eps,
-                         hipStream_t s);
+// partial != NULL: sscales is written instead of read, each segment's scale
+// being formed from the chunk owners' per-tile partial sums (launch_finalize's
+// work, in the pass that needs the scales).
+hipError_t launch_update(const DeviceTables &tb, const uint64_t *sbits, float *sscales,
+                         const double *partial, float *x, float *m_out, const float *v, float lr,
+                         float eps, hipStream_t s);
 
 // The library's own scratch memory, for callers that cannot allocate: a
 // static device array of kScratchBytes on every device the library runs on,

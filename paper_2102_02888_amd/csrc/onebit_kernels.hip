@@ -560,6 +560,47 @@ __global__ __launch_bounds__(Sh::WAVES *kWave) void k_uncompressed(
 }
 
 // ---------------------------------------------------------------------------
+// Scales formed where they are needed (the fused step on plans whose segments
+// have few tiles): the pass that reads a scale sums its segment's partial sums
+// itself, and the part that holds the segment's first word writes the scale
+// out, with the zeros of the empty segments around it.  Every reader sums in
+// the same order, so all get the same value.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ float scale_of(double sum, int64_t len)
+{
+    return (float)__builtin_sqrt(sum / (double)len);
+}
+
+// Zeros for the empty segments after segment q (and before it, when q is the
+// first that is not empty), by `lanes` lanes.
+__device__ __forceinline__ void zero_empty(float *__restrict__ scales, int q, const Segment &sg,
+                                           int lane, int lanes)
+{
+    for (int e = q + 1 + lane; e < sg.next; e += lanes) scales[e] = 0.f;
+    if (sg.tile == 0)
+        for (int e = lane; e < q; e += lanes) scales[e] = 0.f;
+}
+
+// The server scale of the row's segment q (all 16 lanes of a row have the same
+// q): the row's lanes sum the segment's partial sums.  `first`: this row holds
+// the segment's first word and writes the scale.
+__device__ __forceinline__ float row_scale(const Segment *__restrict__ segs, int q, bool first,
+                                           const double *__restrict__ partial,
+                                           float *__restrict__ scales, int lane)
+{
+    const Segment sg = segs[q];
+    double s = 0.0;
+#pragma unroll 4
+    for (int t = lane & 15; t < sg.tiles; t += 16) s += partial[sg.tile + t];
+    const float r = scale_of(row_sum(s), sg.len);
+    if (first) {
+        if ((lane & 15) == 0) scales[q] = r;
+        zero_empty(scales, q, sg, lane & 15, 16);
+    }
+    return r;
+}
+
+// ---------------------------------------------------------------------------
 // One sub-block of a block as a wave of the update-like passes sees it: which
 // elements are real, and the sign word and scale of each lane's segment.  The
 // caller issues its own loads first; INSIDE as in ldb4.
@@ -1578,14 +1619,19 @@ __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70)
 // workgroups per CU; asking for five waves per SIMD keeps the registers
 // there too (95 instead of 126 VGPRs, no spills): 0.90 -> 0.86 ms on the
 // stress workload.  Larger G8 is limited by its LDS.
-template <int G8>  // groups of 8 workers the LDS tables hold: n <= 8 G8
+//
+// FORM (every chunk owned): the tiles are taken in address order, and the
+// workers' scales are formed here from their partial sums, 64 / (n rounded up
+// to a power of two) lanes per worker, which saves the finalize kernel's launch.
+template <int G8, bool FORM>  // groups of 8 workers the LDS tables hold: n <= 8 G8
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G8 == 1 ? 5 : 1))) void k_server_pass(
     const Tile *__restrict__ tiles, const int32_t *__restrict__ chunk_tiles, int64_t tile_begin,
     int64_t tile_count, int n,
     int grouping_limit, const uint64_t *__restrict__ wbits, int64_t bits_ld,
-    int64_t bits_word_base, const float *__restrict__ wscales, int64_t scales_ld,
+    int64_t bits_word_base, float *__restrict__ wscales, int64_t scales_ld,
     int64_t scales_seg_base, float *__restrict__ serr, const float *__restrict__ sscales,
-    uint64_t *__restrict__ sbits, double *__restrict__ partial)
+    uint64_t *__restrict__ sbits, double *__restrict__ partial, const Segment *__restrict__ segs,
+    const double *__restrict__ wpartial, int64_t wpart_ld)
 {
     __shared__ __align__(16) ServerTileLds<G8> s_lds[kWavesPerBlock];
     const int lane = threadIdx.x & (kWave - 1);
@@ -1595,7 +1641,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G8 == 1 
     if (rel >= tile_count) return;
     ServerTileLds<G8> &L = s_lds[wv];
     const int groups8 = (n + 7) >> 3;
-    const int64_t t = chunk_tiles[tile_begin + rel];
+    const int64_t t = FORM ? tile_begin + rel : (int64_t)chunk_tiles[tile_begin + rel];
     const Tile tile = tiles[t];
     const int len = tile.len;
     const int64_t base = tile.start;
@@ -1611,9 +1657,34 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G8 == 1 
     }
     uint64_t stg[kServerRowBatch / 4];
     server_load_words(in, 0, n, lane, stg);
-    const float scl = lane < n ? in.scales[(int64_t)lane * in.scales_ld] : 0.f;
+    float scl;
+    if (FORM) {
+        const Segment sg = segs[tile.seg];
+        const int per = n > 1 ? kWave >> (32 - __clz(n - 1)) : kWave;  // lanes per worker
+        const int r = lane / per;
+        double s = 0.0;
+        if (r < n) {
+            const double *src = wpartial + (int64_t)r * wpart_ld + sg.tile;
+#pragma unroll 4
+            for (int k = lane % per; k < sg.tiles; k += per) s += src[k];
+        }
+        for (int off = per >> 1; off >= 1; off >>= 1) s += __shfl_xor(s, off, kWave);
+        const float sr = scale_of(s, sg.len);
+        const bool first = sg.tile == t;
+        if (r < n && lane % per == 0) {
+            L.scale[r] = sr;
+            if (first) wscales[(int64_t)r * scales_ld + tile.seg] = sr;
+        }
+        if (first)
+            for (int i = 0; i < n; ++i)
+                zero_empty(wscales + (int64_t)i * scales_ld, tile.seg, sg, lane, kWave);
+        wave_sync();
+        scl = lane < n ? L.scale[lane] : 0.f;
+    } else {
+        scl = lane < n ? in.scales[(int64_t)lane * in.scales_ld] : 0.f;
+        if (lane < n) L.scale[lane] = scl;
+    }
     const bool grouped = server_grouped(in, n, grouping_limit, lane, scl);
-    if (lane < n) L.scale[lane] = scl;
     if (grouped) {
         wave_sync();
         server_build_lut4(L, n, lane);
@@ -2045,10 +2116,15 @@ __device__ __forceinline__ void update_sub(const Lane4 &l, int li, v4f xv, v4f v
 // workgroups per CU, held by unused LDS, keep about 12 KB in flight per SIMD:
 // one GPU's share of a BERT-Large step (its own worker row, the update) 1.306
 // ms at eight, 1.293 at six, 1.366 at five.
+//
+// FORM: the scales are formed here from the chunk owners' partial sums (see
+// row_scale), which saves the finalize kernel's launch.
+template <bool FORM>
 __global__ __launch_bounds__(kBlock) void k_update(
     const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
-    int64_t num_blocks, int64_t padded_len, const uint64_t *__restrict__ sbits,
-    const float *__restrict__ sscales, float *__restrict__ x, float *__restrict__ m_out,
+    int64_t num_blocks, int64_t padded_len, const Segment *__restrict__ segs,
+    const double *__restrict__ partial, const uint64_t *__restrict__ sbits,
+    float *__restrict__ sscales, float *__restrict__ x, float *__restrict__ m_out,
     const float *__restrict__ v, float lr, float eps)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -2071,6 +2147,28 @@ __global__ __launch_bounds__(kBlock) void k_update(
         vv = ldb4<false>(v + base, li, lim);
     }
     const Block rec = load_block(blocks, blk);
+    if (FORM) {
+        Lane4 l{0.f, (uint32_t)(word >> (li & 63)), 0};
+        if (rec.whole || li < lim) {
+            const int w = li >> 6;
+            const int t = rec.whole ? rec.tile
+                                    : rec.tile + __popc(rec.starts & ((2u << w) - 1u)) - 1;
+            int q = rec.seg;
+            l.valid = 4;
+            if (!rec.whole) {
+                const Tile tile = tiles[t];
+                q = tile.seg;
+                l.valid = tile_valid4(tile, base + li);
+            }
+            const bool first = segs[q].tile == t && ((rec.starts >> w) & 1u);
+            l.s = row_scale(segs, q, first, partial, sscales, lane);
+        }
+        if (rec.whole)
+            update_sub<true>(l, li, xv, vv, x, m_out, lr, eps);
+        else
+            update_sub<false>(l, li, xv, vv, x, m_out, lr, eps);
+        return;
+    }
     const float s0 = sscales[rec.seg];
     if (rec.whole)
         update_sub<true>(lane_message<true>(tiles, rec, base, li, lim, word, s0, sscales), li, xv,
@@ -2468,10 +2566,10 @@ size_t server_table_bytes(int n, int64_t segments)
 
 hipError_t launch_server_pass(const DeviceTables &tb, int64_t tile_begin, int64_t tile_count,
                               int n, const uint64_t *wbits, int64_t bits_ld,
-                              int64_t bits_word_base, const float *wscales, int64_t scales_ld,
+                              int64_t bits_word_base, float *wscales, int64_t scales_ld,
                               int64_t scales_seg_base, float *serr, float *sscales,
-                              uint64_t *sbits, double *partial, int num_tensors, int cb,
-                              int nown, double *tables, int32_t *flags,
+                              uint64_t *sbits, double *partial, const double *wpartial,
+                              int64_t wpart_ld, int num_tensors, int cb, int nown, double *tables, int32_t *flags,
                               const int32_t *server_blocks, int64_t num_blocks, hipStream_t s)
 {
     int log2n = 0;
@@ -2513,35 +2611,27 @@ hipError_t launch_server_pass(const DeviceTables &tb, int64_t tile_begin, int64_
     } else {
         // tables for as many groups of 8 as n needs: more workgroups per CU
         // for small n
-        const dim3 grid((unsigned)blocks_for(tile_count)), block(kBlock);
-        if (n <= 8)
-            hipLaunchKernelGGL(k_server_pass<1>, grid, block, 0, s, tb.tiles, tb.chunk_tiles,
-                               tile_begin, tile_count, n, grouping_limit, wbits, bits_ld,
-                               bits_word_base, wscales, scales_ld, scales_seg_base, serr, sscales,
-                               sbits, partial);
-        else if (n <= 16)
-            hipLaunchKernelGGL(k_server_pass<2>, grid, block, 0, s, tb.tiles, tb.chunk_tiles,
-                               tile_begin, tile_count, n, grouping_limit, wbits, bits_ld,
-                               bits_word_base, wscales, scales_ld, scales_seg_base, serr, sscales,
-                               sbits, partial);
-        else
-            hipLaunchKernelGGL(k_server_pass<4>, grid, block, 0, s, tb.tiles, tb.chunk_tiles,
-                               tile_begin, tile_count, n, grouping_limit, wbits, bits_ld,
-                               bits_word_base, wscales, scales_ld, scales_seg_base, serr, sscales,
-                               sbits, partial);
+        const auto kernel = n <= 8    ? (wpartial ? k_server_pass<1, true> : k_server_pass<1, false>)
+                            : n <= 16 ? (wpartial ? k_server_pass<2, true> : k_server_pass<2, false>)
+                                      : (wpartial ? k_server_pass<4, true> : k_server_pass<4, false>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks_for(tile_count)), dim3(kBlock), 0, s,
+                           tb.tiles, tb.chunk_tiles, tile_begin, tile_count, n, grouping_limit,
+                           wbits, bits_ld, bits_word_base, wscales, scales_ld, scales_seg_base,
+                           serr, sscales, sbits, partial, tb.segs, wpartial, wpart_ld);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_update(const DeviceTables &tb, const uint64_t *sbits, const float *sscales,
-                         float *x, float *m_out, const float *v, float lr, float eps,
-                         hipStream_t s)
+hipError_t launch_update(const DeviceTables &tb, const uint64_t *sbits, float *sscales,
+                         const double *partial, float *x, float *m_out, const float *v, float lr,
+                         float eps, hipStream_t s)
 {
+    const auto kernel = partial ? k_update<true> : k_update<false>;
     for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
         const int64_t count = launch_piece(tb.num_blocks, base);
-        hipLaunchKernelGGL(k_update, dim3((unsigned)xcd_grid(count, 1)), dim3(kBlock), idle_lds(6),
-                           s, tb.tiles, tb.blocks, base, base + count, tb.padded_len, sbits,
-                           sscales, x, m_out, v, lr, eps);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(count, 1)), dim3(kBlock), idle_lds(6),
+                           s, tb.tiles, tb.blocks, base, base + count, tb.padded_len, tb.segs,
+                           partial, sbits, sscales, x, m_out, v, lr, eps);
     }
     return hipGetLastError();
 }

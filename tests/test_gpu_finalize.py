@@ -51,3 +51,52 @@ def test_scales_of_every_lane_count(dev, big, small, n):
     want = np.where(own, _rms(host(st.server_err), plan), host(before))
     check_scales("owner 1", host(st.server_scales), want)
     plan.close()
+
+
+@pytest.mark.parametrize("numel,n", [
+    ([1 << 20], 4),                                   # 256 tiles a segment: both formed
+    ([1 << 20], 3),                                   # 342 tiles: neither
+    ([0, 0, 100, 0, 5000, 64, 0], 32),                # empty segments before, between, after
+    ([300] * 40 + [0] + [4000] * 30, 7),              # mixed blocks, both formed
+    ([2000 * 1024 + 5], 16),                          # 125 tiles, over 1,200: neither owners'
+    ([65_000] * 50, 8),                               # owners' from few tiles a segment
+    ([1_000_000, 70_000], 8),                         # workers' alone
+    ([129 * 64], 33),                                 # n > 32: owners' alone
+    ([1], 1),
+])
+def test_fused_step_equals_the_three_calls(dev, numel, n):
+    """The fused step, which forms the scales inside its passes on small
+    plans, against the separate calls, which finalize them: every output bit
+    for bit but a scale that another order of its 64-bit sum rounds to the
+    next fp32 value (none is expected in so few)."""
+    import paper_2102_02888_amd as ob
+    plan = ob.Plan(numel, n)
+    a, b = ob.State(plan, dev), ob.State(plan, dev)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    a.x.normal_(generator=g)
+    a.m.normal_(generator=g)
+    a.v.uniform_(0.5, 1.0, generator=g)
+    for k in ("x", "m", "v"):
+        getattr(b, k).copy_(getattr(a, k))
+    for t in (a.worker_scales, a.server_scales):
+        t.fill_(3.0)   # a scale that is not written would show, in an error too
+    b.worker_scales.fill_(3.0)
+    b.server_scales.fill_(3.0)
+    for step in range(3):
+        a.grads.normal_(generator=g)
+        b.grads.copy_(a.grads)
+        m = b.m if step == 0 else None
+        a.step(1e-3, 0.9, 1e-8)
+        ob.onebit_worker_compress(plan, m, b.grads, b.worker_err, b.worker_bits, b.worker_scales,
+                                  0.9, b.workspace, m_bits=b.server_bits, m_scales=b.server_scales)
+        ob.onebit_server_reduce_compress(plan, 0, n, b.worker_bits, b.worker_scales, b.server_err,
+                                         b.server_bits, b.server_scales, b.workspace)
+        ob.onebit_decompress_update(plan, b.server_bits, b.server_scales, b.x, m, b.v, 1e-3, 1e-8)
+        torch.cuda.synchronize()
+        for k in ("worker_bits", "server_bits"):
+            assert torch.equal(getattr(a, k), getattr(b, k)), (k, step)
+        for k in ("worker_scales", "server_scales", "worker_err", "server_err", "x"):
+            assert torch.equal(getattr(a, k).view(torch.int32), getattr(b, k).view(torch.int32)), \
+                (k, step)
+    plan.close()
