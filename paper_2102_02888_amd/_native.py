@@ -7,7 +7,7 @@ binding fails loudly.  Build it with ``python -m paper_2102_02888_amd.build``
 import ctypes
 import os
 
-from .build import LIB as LIB_PATH
+from .build import ARGS as ARGS_PATH, LIB as LIB_PATH
 
 _vp = ctypes.c_void_p
 _i64 = ctypes.c_int64
@@ -75,6 +75,20 @@ def lib():
             fn.restype = RESTYPES.get(name, ctypes.c_int32)
         _lib = L
     return _lib
+
+
+def args_module():
+    """The binding's native argument checks (csrc/binding_args.cpp)."""
+    import importlib.machinery
+    import importlib.util
+    if not os.path.exists(ARGS_PATH):
+        raise ImportError("onebit_args.so is not built (%s); run "
+                          "`python -m paper_2102_02888_amd.build`" % ARGS_PATH)
+    loader = importlib.machinery.ExtensionFileLoader("onebit_args", ARGS_PATH)
+    module = importlib.util.module_from_spec(
+        importlib.util.spec_from_loader("onebit_args", loader))
+    loader.exec_module(module)
+    return module
 
 
 class OnebitError(RuntimeError):

@@ -1,5 +1,6 @@
-"""Builds libonebit.so (the gfx950 HIP kernels and the C ABI) in-tree, and
-the HBM streaming probe's own library lib/libhbmprobe.so."""
+"""Builds libonebit.so (the gfx950 HIP kernels and the C ABI) in-tree, the
+binding's native argument checks lib/onebit_args.so, and the HBM streaming
+probe's own library lib/libhbmprobe.so."""
 import os
 import subprocess
 import sys
@@ -8,6 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("onebit_kernels.hip", "onebit_abi.hip")]
 LIB = os.path.join(HERE, "lib", "libonebit.so")
+ARGS_SOURCE = os.path.join(HERE, "csrc", "binding_args.cpp")
+ARGS = os.path.join(HERE, "lib", "onebit_args.so")
 PROBE_SOURCE = os.path.join(HERE, "csrc", "hbm_probe.hip")
 PROBE = os.path.join(HERE, "lib", "libhbmprobe.so")
 
@@ -22,10 +25,10 @@ HIPCC_FLAGS = [
 ]
 
 
-def _hipcc(flags, sources, target, verbose):
+def _compile(compiler, flags, sources, target, verbose, libs=()):
     os.makedirs(os.path.dirname(target), exist_ok=True)
     tmp = target + ".tmp%d" % os.getpid()
-    cmd = ["hipcc"] + flags + ["-o", tmp] + sources
+    cmd = [compiler] + flags + ["-o", tmp] + sources + list(libs)
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -33,16 +36,32 @@ def _hipcc(flags, sources, target, verbose):
                     if "packed-fp32-ops" not in l and "unused during compilation" not in l)
     if r.returncode != 0:
         sys.stderr.write(out + "\n")
-        raise RuntimeError("hipcc failed building " + os.path.basename(target))
+        raise RuntimeError("%s failed building %s" % (compiler, os.path.basename(target)))
     if verbose and out.strip():
         print(out)
     os.replace(tmp, target)
     return target
 
 
+def _args_flags():
+    """Host compiler flags and libraries for an extension against torch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    flags = ["-O2", "-std=c++17", "-fPIC", "-shared",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    for path in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
+        flags += ["-isystem", path]
+    libs = ["-L" + path for path in cpp_extension.library_paths()]
+    return flags, libs + ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+
+
 def build(verbose: bool = False) -> str:
-    _hipcc(HIPCC_FLAGS, SOURCES, LIB, verbose)
-    _hipcc(HIPCC_FLAGS, [PROBE_SOURCE], PROBE, verbose)
+    _compile("hipcc", HIPCC_FLAGS, SOURCES, LIB, verbose)
+    flags, libs = _args_flags()
+    _compile("g++", flags, [ARGS_SOURCE], ARGS, verbose, libs)
+    _compile("hipcc", HIPCC_FLAGS, [PROBE_SOURCE], PROBE, verbose)
     return LIB
 
 

@@ -11,7 +11,7 @@ import ctypes
 import numpy as np
 import torch
 
-from ._native import PlanInfo, call, lib
+from ._native import PlanInfo, args_module, call, lib
 
 __all__ = [
     "Plan", "onebit_plan_create", "onebit_warmup_adam_step", "onebit_worker_compress",
@@ -23,15 +23,31 @@ __all__ = [
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """HIP stream handle of a torch stream (default: torch's current one)."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
+
+
+def _pointer(*args):
+    """The native argument checks (csrc/binding_args.cpp), loaded on first use."""
+    global _pointer
+    _pointer = args_module().pointer
+    return _pointer(*args)
 
 
 def _ptr(t, dtype, name, cols=None, rows=1):
-    """Device pointer of a tensor after checking its type, device and layout.
-    With `cols`, the tensor must also cover what the kernels touch: `rows`
-    rows of `cols` elements (a 1-D tensor is one row), so that a short
-    buffer is refused here instead of being read or written out of bounds."""
+    """Device pointer of a tensor after checking its type, device and layout
+    (None stays None).  With `cols`, the tensor must also cover what the
+    kernels touch: `rows` rows of `cols` elements (a 1-D tensor is one row),
+    so that a short buffer is refused here instead of being read or written
+    out of bounds.  One native call makes all checks; if any fails (or t is no
+    plain tensor) they are repeated here one by one."""
+    p = _pointer(t, dtype, -1 if cols is None else cols, rows, True)
+    return p if p >= 0 else _ptr_checked(t, dtype, name, cols, rows)
+
+
+def _ptr_checked(t, dtype, name, cols, rows):
     if t is None:
         return None
     if not isinstance(t, torch.Tensor):
@@ -49,7 +65,7 @@ def _ptr(t, dtype, name, cols=None, rows=1):
         if have_rows < rows or have_cols < cols:
             raise ValueError("%s is %s; the call needs %d row(s) of at least %d elements"
                              % (name, tuple(t.shape), rows, cols))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _flat(t, dtype, name, need):

@@ -85,3 +85,41 @@ def test_paired_rows_layout(dtype):
         paired_rows(n, 100, dtype, "cpu")
     with pytest.raises(ValueError):
         paired_rows(n, 0, dtype, "cpu")
+
+
+@pytest.mark.parametrize("make", [
+    lambda: torch.zeros(10), lambda: torch.zeros(0), lambda: torch.zeros(()),
+    lambda: torch.zeros(4, 64), lambda: torch.zeros(0, 64), lambda: torch.zeros(3, 130)[:, 64:128],
+    lambda: torch.zeros(64, 4).t(), lambda: torch.zeros(20)[::2], lambda: torch.zeros(2, 2, 64),
+    lambda: torch.zeros(4, 64, dtype=torch.float64), lambda: torch.zeros(128)[3:],
+    lambda: torch.zeros(1, 64).expand(4, 64), lambda: torch.nn.Parameter(torch.zeros(64)),
+    lambda: torch.zeros(4, 64, device="meta"), lambda: None, lambda: 5, lambda: np.zeros(64),
+])
+@pytest.mark.parametrize("cols,rows", [(None, 1), (64, 1), (64, 4), (65, 1), (10, 2), (0, 1)])
+def test_native_argument_checks_accept_what_the_binding_does(make, cols, rows):
+    """pointer() gives the data pointer exactly where the one-by-one checks
+    accept a tensor (their device check left out here), else -1."""
+    from paper_2102_02888_amd._native import args_module
+    pointer = args_module().pointer
+    t = make()
+    want = -1
+    if isinstance(t, torch.Tensor) and t.dtype == torch.float32 and t.dim() <= 2 \
+            and (t.dim() == 0 or t.stride(-1) == 1):
+        have = tuple(t.shape) if t.dim() == 2 else (1, t.numel())
+        if cols is None or (have[0] >= rows and have[1] >= cols):
+            want = t.data_ptr()
+    args = (t, torch.float32, -1 if cols is None else cols, rows)
+    assert pointer(*args, False) == want
+    assert pointer(*args, True) == -1  # no GPU tensor
+
+
+def test_a_failed_check_is_named():
+    from paper_2102_02888_amd.onebit import _ptr
+    f = torch.float32
+    assert _ptr(None, f, "m") is None
+    with pytest.raises(TypeError, match="m must be a torch.Tensor"):
+        _ptr(np.zeros(4), f, "m")
+    with pytest.raises(TypeError, match="m must be torch.float32, got torch.float64"):
+        _ptr(torch.zeros(4, dtype=torch.float64), f, "m")
+    with pytest.raises(ValueError, match="m must be a GPU tensor"):
+        _ptr(torch.zeros(4), f, "m", 4)
