@@ -107,6 +107,20 @@ bool server_uses_tables(const onebit_plan_s *p, int32_t begin, int32_t end)
             (p->server_tables == ONEBIT_SERVER_TABLES_AUTO && worth));
 }
 
+// Whether the chunk owners' call over [begin, end) adds the workers one by one
+// over blocks instead of giving each tile a wave and lookup tables: with every
+// chunk owned, a third of a block or less per tile on average, and more than
+// 8,192 tiles (smaller plans form the workers' scales in the tables' pass).
+// Step, in us, tables / one by one: 2,000 tensors of 64 to 8192 elements (17
+// tiles a block with n = 32, 4.3 with n = 8) 402 / 350, naive 128 / 119; 640
+// tensors up to 2^16 n = 32 (3.6 a block) 497 / 491; 2,000 up to 2^16 n = 8 (2.1 a
+// block) 413 / 419; one flat buffer of 64 million, n = 8 1154 / 1185.
+bool server_direct(const onebit_plan_s *p, int32_t begin, int32_t end)
+{
+    return begin == 0 && end == p->n && p->server_tables != ONEBIT_SERVER_TABLES_ON &&
+           p->T > 8192 && p->T >= 3 * p->tb.num_blocks;
+}
+
 // On small plans the fused step leaves out the two finalize launches: the chunk
 // owners' pass forms the workers' scales, and the update the owners', from the
 // partial sums of each tile's segment.  A launch costs about 3.3 us of the host
@@ -474,7 +488,8 @@ int run_server(const onebit_plan_s *p, int32_t server_begin, int32_t server_end,
     double *part = (double *)((char *)workspace + server_partial_offset(p));
     const int nown = server_end - server_begin;
     const int64_t owned = (int64_t)p->K * nown;
-    const bool use_tables = server_uses_tables(p, server_begin, server_end);
+    const bool direct = server_direct(p, server_begin, server_end);
+    const bool use_tables = !direct && server_uses_tables(p, server_begin, server_end);
     const double *wpart =
         form_worker ? (const double *)((char *)workspace + worker_partial_offset(p)) : nullptr;
     double *tables = use_tables ? (double *)((char *)workspace + server_table_offset(p)) : nullptr;
@@ -486,7 +501,8 @@ int run_server(const onebit_plan_s *p, int32_t server_begin, int32_t server_end,
                                            bits_word_base, worker_scales, scales_ld,
                                            scales_seg_base, server_err, server_scales,
                                            server_bits, part, wpart, p->T, p->K, server_begin,
-                                           nown, tables, flags, p->tb.server_blocks + bb, nb, s),
+                                           nown, tables, flags, p->tb.server_blocks + bb, nb,
+                                           direct, s),
                 "server kernel launch");
     if (!finalize) return ONEBIT_OK;
     TRY_HIP(onebit::launch_finalize(p->tb, p->max_seg_tiles, owned, 1, p->n, server_begin, nown,

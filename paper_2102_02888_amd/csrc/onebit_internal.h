@@ -132,7 +132,8 @@ size_t server_table_bytes(int n, int64_t segments);
 // pass builds them per tile.  wpartial != NULL (only with every chunk owned,
 // tables == NULL, n <= kServerRowBatch and both bases 0): wscales is written
 // instead of read, from the workers' per-tile partial sums (rows of wpart_ld),
-// as in launch_update.
+// as in launch_update.  direct (every chunk owned, both bases 0, any n): the
+// pass that adds the workers one by one, over blocks.
 hipError_t launch_server_pass(const DeviceTables &tb, int64_t tile_begin, int64_t tile_count,
                               int n, const uint64_t *wbits, int64_t bits_ld,
                               int64_t bits_word_base, float *wscales, int64_t scales_ld,
@@ -140,7 +141,8 @@ hipError_t launch_server_pass(const DeviceTables &tb, int64_t tile_begin, int64_
                               uint64_t *sbits, double *partial, const double *wpartial,
                               int64_t wpart_ld, int num_tensors, int cb,
                               int nown, double *tables, int32_t *flags,
-                              const int32_t *server_blocks, int64_t num_blocks, hipStream_t s);
+                              const int32_t *server_blocks, int64_t num_blocks, bool direct,
+                              hipStream_t s);
 
 // partial != NULL: sscales is written instead of read, each segment's scale
 // being formed from the chunk owners' per-tile partial sums (launch_finalize's

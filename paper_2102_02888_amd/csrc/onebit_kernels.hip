@@ -1606,6 +1606,134 @@ __device__ __forceinline__ int64_t owned_segment(int64_t q, int n, const ServerT
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 // ---------------------------------------------------------------------------
+// Chunk owners' pass over blocks, every chunk owned: a workgroup takes one
+// block, one sub-block per wave, and each lane adds the n decoded values of its
+// 4 elements one by one in worker order (the oracle's sum whatever the scales),
+// reading the byte that holds its 4 sign bits from each worker's row.  No LDS
+// tables, no regrouping and no exactness check, so a short tile costs what its
+// elements do, where a wave per tile builds its tables for 64 elements as for
+// 1,024 (the caller's rule says from where on this pays).
+// ---------------------------------------------------------------------------
+constexpr int kDirectBatch = 8;  // workers whose sign bits are loaded together
+
+// sum[c] += +-s by the lane's bit c of nib.
+__device__ __forceinline__ void add_decoded(double (&sum)[4], float s, uint32_t nib)
+{
+    const double d = (double)s;
+    const int lo = __double2loint(d);
+    const uint32_t hi = (uint32_t)__double2hiint(d);
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        sum[c] += __hiloint2double((int)(hi ^ ((~nib << (31 - c)) & 0x80000000u)), lo);
+}
+
+template <bool WHOLE>
+__device__ __forceinline__ void server_direct_block(
+    double (&red)[kTileWords], const Tile *__restrict__ tiles, const Block &rec, int64_t base,
+    int lim, int lane, int wv, v4f cv, int n, const uint8_t *__restrict__ bytes,
+    int64_t bytes_ld, uint32_t (&first)[kDirectBatch], const float *__restrict__ wscales,
+    int64_t scales_ld, float *__restrict__ serr, float sprev,
+    const float *__restrict__ sscales, uint64_t *__restrict__ sbits,
+    double *__restrict__ partial)
+{
+    const int li = wv * (kWave * 4) + 4 * lane;
+    const bool in = WHOLE || li < lim;
+    int seg = rec.seg, valid = 4;
+    if (!WHOLE) {
+        valid = 0;
+        if (in) {
+            const Tile tile = block_word_tile(tiles, rec, li >> 6);
+            seg = tile.seg;
+            valid = tile_valid4(tile, base + li);
+            sprev = sscales[seg];
+        }
+    }
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i0 = 0; i0 < n; i0 += kDirectBatch) {
+        uint32_t cur[kDirectBatch];
+#pragma unroll
+        for (int k = 0; k < kDirectBatch; ++k) {
+            cur[k] = first[k];
+            const int i = i0 + kDirectBatch + k;
+            if (i < n && in) first[k] = bytes[(int64_t)i * bytes_ld];
+        }
+#pragma unroll
+        for (int k = 0; k < kDirectBatch; ++k) {
+            const int i = i0 + k;
+            if (i >= n) break;
+            const float s = wscales[(int64_t)i * scales_ld + seg];
+            add_decoded(sum, s, cur[k] >> (lane & 1 ? 4 : 0));
+        }
+    }
+    const double dn = (double)n;
+    const bool pow2 = (n & (n - 1)) == 0;
+    const double inv_n = 1.0 / dn;
+    double acc = 0.0;
+    v4f zv;
+    uint32_t nib = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        // for a power-of-two n, sum * (1/n) is the same exact scaling
+        const float avg = (float)(pow2 ? sum[c] * inv_n : sum[c] / dn);
+        const float z = avg + error_of(cv[c], sprev);
+        zv[c] = z;
+        const bool real = WHOLE || c < valid;
+        const double zd = real ? (double)z : 0.0;
+        acc = __builtin_fma(zd, zd, acc);  // zd * zd is exact in fp64
+        nib |= (real && z >= 0.f) ? (1u << c) : 0u;
+    }
+    stb4<WHOLE>(serr, li, valid, zv);
+    const uint64_t word = row_sign_word(nib, lane);
+    if ((lane & 15) == 0 && in) sbits[li >> 6] = word;
+    if (WHOLE) {
+        acc = wave_sum_dpp(acc);
+        if (lane == 0) red[wv] = acc;
+    } else {
+        acc = row_sum(acc);
+        if ((lane & 15) == 0) red[li >> 6] = acc;
+    }
+    __syncthreads();
+    if (wv == 0) block_partials<WHOLE>(partial, rec, red, kSubBlocks, lane);
+}
+
+__global__ __launch_bounds__(kBlock) void k_server_direct(
+    const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
+    int64_t num_blocks, int64_t padded_len, int n, const uint64_t *__restrict__ wbits,
+    int64_t bits_ld, const float *__restrict__ wscales, int64_t scales_ld, float *__restrict__ serr, const float *__restrict__ sscales,
+    uint64_t *__restrict__ sbits, double *__restrict__ partial)
+{
+    __shared__ double red[kTileWords];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wv = threadIdx.x >> 6;
+    const int64_t blk = block_base + xcd_block();
+    if (blk >= num_blocks) return;  // the whole workgroup
+    const int64_t base = blk * kTileElems;
+    const int64_t room = padded_len - base;
+    const int lim = room < kTileElems ? (int)room : kTileElems;
+    const int li = wv * (kWave * 4) + 4 * lane;
+    serr += base;
+    sbits += base >> 6;
+    const uint8_t *bytes = (const uint8_t *)wbits + ((base + li) >> 3);
+    const int64_t bytes_ld = bits_ld * 8;
+    const v4f cv = lim == kTileElems ? ldb4<true>(serr, li, lim) : ldb4<false>(serr, li, lim);
+    uint32_t first[kDirectBatch];
+#pragma unroll
+    for (int k = 0; k < kDirectBatch; ++k) {
+        first[k] = 0;
+        if (k < n && li < lim) first[k] = bytes[k * bytes_ld];
+    }
+    const Block rec = load_block(blocks, blk);
+    const float sprev = sscales[rec.seg];
+    if (rec.whole)
+        server_direct_block<true>(red, tiles, rec, base, lim, lane, wv, cv, n, bytes, bytes_ld,
+                                  first, wscales, scales_ld, serr, sprev, sscales, sbits, partial);
+    else
+        server_direct_block<false>(red, tiles, rec, base, lim, lane, wv, cv, n, bytes, bytes_ld,
+                                   first, wscales, scales_ld, serr, sprev, sscales, sbits,
+                                   partial);
+}
+
+// ---------------------------------------------------------------------------
 // Chunk owners' pass for n <= kServerRowBatch, one wave per tile, building
 // the tables itself.  The tile's error-state and sign-word loads are issued
 // first; the wave then reads the segment's scales, decides between the
@@ -2570,8 +2698,18 @@ hipError_t launch_server_pass(const DeviceTables &tb, int64_t tile_begin, int64_
                               int64_t scales_seg_base, float *serr, float *sscales,
                               uint64_t *sbits, double *partial, const double *wpartial,
                               int64_t wpart_ld, int num_tensors, int cb, int nown, double *tables, int32_t *flags,
-                              const int32_t *server_blocks, int64_t num_blocks, hipStream_t s)
+                              const int32_t *server_blocks, int64_t num_blocks, bool direct,
+                              hipStream_t s)
 {
+    if (direct) {
+        for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
+            const int64_t count = launch_piece(tb.num_blocks, base);
+            hipLaunchKernelGGL(k_server_direct, dim3((unsigned)xcd_grid(count, 1)), dim3(kBlock),
+                               0, s, tb.tiles, tb.blocks, base, base + count, tb.padded_len, n,
+                               wbits, bits_ld, wscales, scales_ld, serr, sscales, sbits, partial);
+        }
+        return hipGetLastError();
+    }
     int log2n = 0;
     while ((1 << log2n) < n) ++log2n;
     const int grouping_limit = 29 - log2n;

@@ -161,3 +161,38 @@ def test_row_sum_shapes(dev, variant, grad_dtype, numel, n):
         worst = float(((a - b).abs() / b.abs().clamp(min=1e-3)).max())
         assert worst <= 2 ** -22, (name, worst)
     plan.close()
+
+
+@pytest.mark.parametrize("n,narrow", [(2, True), (5, True), (8, False), (9, True), (32, True),
+                                      (33, False), (70, True)])
+def test_one_by_one_owners_equal_the_lookup_tables(dev, n, narrow):
+    """Plans of many short tiles take the owners' pass that adds the workers
+    one by one; with the tables forced on, the same call takes the lookup
+    tables: equal bit for bit, for scales whose sums are exact in any order
+    (narrow) and for scales of 40 binades and zeros, which are not."""
+    import paper_2102_02888_amd as ob
+    rng = np.random.default_rng(n)
+    numel = [int(a) for a in rng.integers(1, 64 * 2 * n, size=14000 // n + 300)] + [1 << 15, 0, 1024]
+    plan = ob.Plan(numel, n)
+    assert plan.T > 8192 and plan.T >= 3 * ((plan.D + 1023) // 1024)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n)
+    bits = torch.randint(-(1 << 62), 1 << 62, (n, plan.W), dtype=torch.int64, device=dev,
+                         generator=g)
+    scales = torch.empty((n, plan.S), device=dev).log_normal_(-7, 0.3 if narrow else 7.0,
+                                                              generator=g)
+    if not narrow:
+        scales[:, ::5] = 0
+    err = torch.empty(plan.D, device=dev).normal_(0, 1e-3, generator=g)
+    old = torch.empty(plan.S, device=dev).log_normal_(-7, 0.3, generator=g)
+    out = []
+    for mode in (ob.SERVER_TABLES_AUTO, ob.SERVER_TABLES_ON):
+        plan.set_server_tables(mode)
+        e, sb, ss = err.clone(), torch.zeros(plan.W, dtype=torch.int64, device=dev), old.clone()
+        ob.onebit_server_reduce_compress(plan, 0, n, bits, scales, e, sb, ss, plan.workspace(dev))
+        torch.cuda.synchronize()
+        out.append((e, sb, ss))
+    assert torch.equal(out[0][0].view(torch.int32), out[1][0].view(torch.int32))
+    assert torch.equal(out[0][1], out[1][1])
+    check_scales("server scales", host(out[0][2]), host(out[1][2]))
+    plan.close()
