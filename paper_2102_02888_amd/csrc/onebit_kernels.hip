@@ -581,23 +581,46 @@ __device__ __forceinline__ void zero_empty(float *__restrict__ scales, int q, co
         for (int e = lane; e < q; e += lanes) scales[e] = 0.f;
 }
 
-// The server scale of the row's segment q (all 16 lanes of a row have the same
-// q): the row's lanes sum the segment's partial sums.  `first`: this row holds
-// the segment's first word and writes the scale.
-__device__ __forceinline__ float row_scale(const Segment *__restrict__ segs, int q, bool first,
-                                           const double *__restrict__ partial,
-                                           float *__restrict__ scales, int lane)
+// The scale of segment sg from its partial sums, by a whole wave or by each
+// 16-lane row for a segment of its own, in one order: 64 strided sums (v, v +
+// 64, ...), added as v and v + 32, then with v + 16 and v + 48, then over 16.
+// A round of loads covers 256 tiles, issued together.
+__device__ __forceinline__ float wave_scale(const Segment &sg, const double *__restrict__ partial,
+                                            int lane)
 {
-    const Segment sg = segs[q];
     double s = 0.0;
-#pragma unroll 4
-    for (int t = lane & 15; t < sg.tiles; t += 16) s += partial[sg.tile + t];
-    const float r = scale_of(row_sum(s), sg.len);
-    if (first) {
-        if ((lane & 15) == 0) scales[q] = r;
-        zero_empty(scales, q, sg, lane & 15, 16);
+    for (int t0 = lane; t0 < sg.tiles; t0 += 4 * kWave) {
+        double p[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            p[k] = t0 + k * kWave < sg.tiles ? partial[sg.tile + t0 + k * kWave] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s += p[k];
     }
-    return r;
+    s += __shfl_xor(s, 32, kWave);
+    s += __shfl_xor(s, 16, kWave);
+    return scale_of(row_sum(s), sg.len);
+}
+
+__device__ __forceinline__ float row_scale(const Segment &sg, const double *__restrict__ partial,
+                                           int lane)
+{
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int t0 = lane & 15; t0 < sg.tiles; t0 += 4 * kWave) {
+        double p[4][4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int t = t0 + k * kWave + 16 * j;
+                p[k][j] = t < sg.tiles ? partial[sg.tile + t] : 0.0;
+            }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) s[j] += p[k][j];
+    }
+    return scale_of(row_sum((s[0] + s[2]) + (s[1] + s[3])), sg.len);
 }
 
 // ---------------------------------------------------------------------------
@@ -1793,8 +1816,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G8 == 1 
         double s = 0.0;
         if (r < n) {
             const double *src = wpartial + (int64_t)r * wpart_ld + sg.tile;
-#pragma unroll 4
-            for (int k = lane % per; k < sg.tiles; k += per) s += src[k];
+            for (int k0 = lane % per; k0 < sg.tiles; k0 += 8 * per) {
+                double p[8];  // eight loads in flight
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    p[k] = k0 + k * per < sg.tiles ? src[k0 + k * per] : 0.0;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) s += p[k];
+            }
         }
         for (int off = per >> 1; off >= 1; off >>= 1) s += __shfl_xor(s, off, kWave);
         const float sr = scale_of(s, sg.len);
@@ -2246,7 +2275,7 @@ __device__ __forceinline__ void update_sub(const Lane4 &l, int li, v4f xv, v4f v
 // ms at eight, 1.293 at six, 1.366 at five.
 //
 // FORM: the scales are formed here from the chunk owners' partial sums (see
-// row_scale), which saves the finalize kernel's launch.
+// wave_scale), which saves the finalize kernel's launch.
 template <bool FORM>
 __global__ __launch_bounds__(kBlock) void k_update(
     const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
@@ -2276,25 +2305,28 @@ __global__ __launch_bounds__(kBlock) void k_update(
     }
     const Block rec = load_block(blocks, blk);
     if (FORM) {
-        Lane4 l{0.f, (uint32_t)(word >> (li & 63)), 0};
-        if (rec.whole || li < lim) {
-            const int w = li >> 6;
-            const int t = rec.whole ? rec.tile
-                                    : rec.tile + __popc(rec.starts & ((2u << w) - 1u)) - 1;
-            int q = rec.seg;
-            l.valid = 4;
-            if (!rec.whole) {
-                const Tile tile = tiles[t];
-                q = tile.seg;
-                l.valid = tile_valid4(tile, base + li);
+        if (rec.whole) {
+            const Segment sg = segs[rec.seg];
+            const float s = wave_scale(sg, partial, lane);
+            if (threadIdx.x < kWave && sg.tile == rec.tile) {
+                if (lane == 0) sscales[rec.seg] = s;
+                zero_empty(sscales, rec.seg, sg, lane, kWave);
             }
-            const bool first = segs[q].tile == t && ((rec.starts >> w) & 1u);
-            l.s = row_scale(segs, q, first, partial, sscales, lane);
+            update_sub<true>(Lane4{s, (uint32_t)(word >> (li & 63)), 4}, li, xv, vv, x, m_out, lr,
+                             eps);
+        } else if (li < lim) {
+            const int w = li >> 6;
+            const int t = rec.tile + __popc(rec.starts & ((2u << w) - 1u)) - 1;
+            const Tile tile = tiles[t];
+            const Segment sg = segs[tile.seg];
+            const float s = row_scale(sg, partial, lane);
+            if (sg.tile == t && ((rec.starts >> w) & 1u)) {  // the segment's first word
+                if ((lane & 15) == 0) sscales[tile.seg] = s;
+                zero_empty(sscales, tile.seg, sg, lane & 15, 16);
+            }
+            update_sub<false>(Lane4{s, (uint32_t)(word >> (li & 63)), tile_valid4(tile, base + li)},
+                              li, xv, vv, x, m_out, lr, eps);
         }
-        if (rec.whole)
-            update_sub<true>(l, li, xv, vv, x, m_out, lr, eps);
-        else
-            update_sub<false>(l, li, xv, vv, x, m_out, lr, eps);
         return;
     }
     const float s0 = sscales[rec.seg];
