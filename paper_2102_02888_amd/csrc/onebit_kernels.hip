@@ -41,6 +41,10 @@ typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
 // tile; its fourth word is the gfx9-family buffer format word.
 constexpr int kStreamLoad = 2;        // nt
 constexpr int kStreamStore = 2 | 16;  // nt, sc1
+// Small plans, whose rows stay in the last-level cache from step to step
+// (rows_cached): loads and stores without nt.
+constexpr int kCachedLoad = 0;
+constexpr int kCachedStore = 16;      // sc1
 
 // Resource for a wave-uniform base p (a tile's start in some row: every
 // caller's p is the same in all lanes).  p is read from the first active lane,
@@ -110,34 +114,23 @@ __device__ __forceinline__ float widen(_Float16 a) { return (float)a; }
 typedef uint16_t v4u16 __attribute__((ext_vector_type(4)));
 typedef _Float16 v4f16 __attribute__((ext_vector_type(4)));
 
-// Gradient elements li..li+3 as fp32 (zeros past len when !FULL).
-template <bool FULL, class G>
-__device__ __forceinline__ v4f ldg4(const typename G::T *__restrict__ p, int li, int len)
+// 16-bit gradient elements li..li+3 as fp32.
+template <class G, bool CACHED>
+__device__ __forceinline__ v4f ldg4(const typename G::T *__restrict__ p, int li)
 {
-    if constexpr (sizeof(typename G::T) == 4) {
-        return ld4<FULL>((const float *)p, li, len);
+    const v2u32 w = __builtin_amdgcn_raw_buffer_load_b64(stream_rsrc(p), li * 2, 0,
+                                                         CACHED ? kCachedLoad : kStreamLoad);
+    v4f r;
+    if constexpr (__is_same(typename G::T, uint16_t)) {
+        const v4u16 h = __builtin_bit_cast(v4u16, w);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) r[c] = widen((uint16_t)h[c]);
     } else {
-        v4f r = {0.f, 0.f, 0.f, 0.f};
-        if (FULL || li + 4 <= len) {
-            const v2u32 w =
-                FULL ? __builtin_amdgcn_raw_buffer_load_b64(stream_rsrc(p), li * 2, 0, kStreamLoad)
-                     : __builtin_nontemporal_load((const v2u32 *)(p + li));
-            if constexpr (__is_same(typename G::T, uint16_t)) {
-                const v4u16 h = __builtin_bit_cast(v4u16, w);
+        const v4f16 h = __builtin_bit_cast(v4f16, w);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) r[c] = widen((uint16_t)h[c]);
-            } else {
-                const v4f16 h = __builtin_bit_cast(v4f16, w);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) r[c] = widen((_Float16)h[c]);
-            }
-            return r;
-        }
-        if (li < len) r.x = widen(p[li]);
-        if (li + 1 < len) r.y = widen(p[li + 1]);
-        if (li + 2 < len) r.z = widen(p[li + 2]);
-        return r;
+        for (int c = 0; c < 4; ++c) r[c] = widen((_Float16)h[c]);
     }
+    return r;
 }
 
 // OR of a 32-bit value over the 16 lanes of each DPP row (every lane of the
@@ -233,22 +226,23 @@ __device__ __forceinline__ Block load_block(const Block *__restrict__ blocks, in
 
 // Loads elements li..li+3 of the block at p; lim = elements of the block
 // inside the padded length (a multiple of 64).  INSIDE: the whole block is.
-template <bool INSIDE>
+template <bool INSIDE, bool CACHED = false>
 __device__ __forceinline__ v4f ldb4(const float *__restrict__ p, int li, int lim)
 {
     if (INSIDE || li < lim)
         return __builtin_bit_cast(
-            v4f, __builtin_amdgcn_raw_buffer_load_b128(stream_rsrc(p), li * 4, 0, kStreamLoad));
+            v4f, __builtin_amdgcn_raw_buffer_load_b128(stream_rsrc(p), li * 4, 0,
+                                                       CACHED ? kCachedLoad : kStreamLoad));
     return v4f{0.f, 0.f, 0.f, 0.f};
 }
 
-template <bool INSIDE, class G>
+template <bool INSIDE, class G, bool CACHED = false>
 __device__ __forceinline__ v4f ldgb4(const typename G::T *__restrict__ p, int li, int lim)
 {
     if constexpr (sizeof(typename G::T) == 4) {
-        return ldb4<INSIDE>((const float *)p, li, lim);
+        return ldb4<INSIDE, CACHED>((const float *)p, li, lim);
     } else {
-        if (INSIDE || li < lim) return ldg4<true, G>(p, li, 0);
+        if (INSIDE || li < lim) return ldg4<G, CACHED>(p, li);
         return v4f{0.f, 0.f, 0.f, 0.f};
     }
 }
@@ -268,12 +262,12 @@ __device__ __forceinline__ int tile_valid4(const Tile &t, int64_t e)
 }
 
 // Stores elements li..li+3 of the block at p, the first `valid` of them.
-template <bool WHOLE>
+template <bool WHOLE, bool CACHED = false>
 __device__ __forceinline__ void stb4(float *__restrict__ p, int li, int valid, v4f v)
 {
     if (WHOLE || valid == 4) {
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u32, v), stream_rsrc(p),
-                                               li * 4, 0, kStreamStore);
+                                               li * 4, 0, CACHED ? kCachedStore : kStreamStore);
         return;
     }
     if (valid > 0) p[li] = v.x;
@@ -784,7 +778,7 @@ constexpr int kPassIdleLds = sizeof(typename G::T) == 2 ? idle_lds(10) - 512 : 0
 
 // A wave's loads of its part of one block: the gradient row, the compensated
 // row and the momentum (sign words, or fp32 values).
-template <bool INSIDE, bool PACKED, class G, int SB>
+template <bool INSIDE, bool PACKED, class G, int SB, bool CACHED>
 __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&mv)[SB],
                                             uint64_t (&word)[SB],
                                             const typename G::T *__restrict__ gi,
@@ -800,10 +794,10 @@ __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&
         if (PACKED) {
             if (INSIDE || li < lim) word[b] = m_bits[li >> 6];
         } else {
-            mv[b] = ldb4<INSIDE>(m, li, lim);
+            mv[b] = ldb4<INSIDE, CACHED>(m, li, lim);
         }
-        gv[b] = ldgb4<INSIDE, G>(gi, li, lim);
-        cv[b] = ldb4<INSIDE>(ei, li, lim);
+        gv[b] = ldgb4<INSIDE, G, CACHED>(gi, li, lim);
+        cv[b] = ldb4<INSIDE, CACHED>(ei, li, lim);
     }
 }
 
@@ -812,7 +806,7 @@ __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&
 // bm = beta1 m, the gradient and the previous compensated value with its scale
 // sp; the new compensated value and the sign words are stored.  Returns the
 // lane's sum of z^2 (WHOLE), or writes the words' sums to words.
-template <bool WHOLE, int SB>
+template <bool WHOLE, int SB, bool CACHED = false>
 __device__ __forceinline__ double worker_compute(const float (&sp)[SB], const int (&valid)[SB],
                                                  const v4f (&bm)[SB], const v4f (&gv)[SB],
                                                  const v4f (&cv)[SB], float *__restrict__ ei,
@@ -838,7 +832,7 @@ __device__ __forceinline__ double worker_compute(const float (&sp)[SB], const in
             sub += zd * zd;
             nib |= (in && z >= 0.f) ? (1u << c) : 0u;
         }
-        stb4<WHOLE>(ei, li, valid[b], zv);
+        stb4<WHOLE, CACHED>(ei, li, valid[b], zv);
         const uint64_t out = row_sign_word(nib, lane);
         const int w = 4 * (sb0 + b) + (lane >> 4);
         if ((lane & 15) == 0 && (WHOLE || li < lim)) bi[w] = out;
@@ -871,7 +865,7 @@ __device__ __forceinline__ void block_partials(double *__restrict__ partial, con
 
 // One block of a worker's row (this wave's sub-blocks) from its loaded values.
 // Every wave of the workgroup has the same block, so all reach the barrier.
-template <bool WHOLE, bool PACKED, int SB>
+template <bool WHOLE, bool PACKED, int SB, bool CACHED>
 __device__ __forceinline__ void worker_block(
     double (&red)[kTileWords], const Tile *__restrict__ tiles, const Block &rec, int64_t base,
     int lim, int lane, int wv, const v4f (&mv)[SB], const uint64_t (&word)[SB], float s0,
@@ -903,7 +897,8 @@ __device__ __forceinline__ void worker_block(
 #pragma unroll
         for (int c = 0; c < 4; ++c) bm[b][c] = PACKED ? with_sign(bs, mnib, c) : beta1 * mv[b][c];
     }
-    double acc = worker_compute<WHOLE, SB>(sp, valid, bm, gv, cv, ei, bi, sb0, lane, lim, omb1, red);
+    double acc = worker_compute<WHOLE, SB, CACHED>(sp, valid, bm, gv, cv, ei, bi, sb0, lane, lim,
+                                                   omb1, red);
     if (WHOLE) {
         acc = wave_sum(acc);
         if (lane == 0) red[wv] = acc;
@@ -915,7 +910,7 @@ __device__ __forceinline__ void worker_block(
 // PACKED: m_{t-1} is the previous step's gathered server message, decoded
 // from its sign words and segment scale (+-scale, exactly the fp32 value the
 // update would have stored), so no fp32 momentum buffer is read.
-template <bool PACKED, class G>
+template <bool PACKED, class G, bool CACHED>
 __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t num_blocks,
     FastDiv by_blocks, int64_t padded_len, int64_t num_tiles, const float *__restrict__ m,
@@ -943,10 +938,10 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     v4f gv[SB], cv[SB], mv[SB];
     uint64_t word[SB];
     if (lim == kTileElems)
-        worker_load<true, PACKED, G, SB>(gv, cv, mv, word, gi, ei, m + base, m_bits + (base >> 6),
+        worker_load<true, PACKED, G, SB, CACHED>(gv, cv, mv, word, gi, ei, m + base, m_bits + (base >> 6),
                                          wv * SB, lane, lim);
     else
-        worker_load<false, PACKED, G, SB>(gv, cv, mv, word, gi, ei, m + base,
+        worker_load<false, PACKED, G, SB, CACHED>(gv, cv, mv, word, gi, ei, m + base,
                                           m_bits + (base >> 6), wv * SB, lane, lim);
     const Block rec = load_block(blocks, blk);
     scales += i * scales_ld;
@@ -955,11 +950,11 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     const float ms0 = PACKED ? m_scales[rec.seg] : 0.f;
     uint64_t *bi = bits + i * bits_ld + (base >> 6);
     if (rec.whole)
-        worker_block<true, PACKED, SB>(red, tiles, rec, base, lim, lane, wv, mv, word, s0, ms0,
+        worker_block<true, PACKED, SB, CACHED>(red, tiles, rec, base, lim, lane, wv, mv, word, s0, ms0,
                                        m_scales, gv, cv, scales, ei, bi, partial + i * num_tiles,
                                        beta1, omb1);
     else
-        worker_block<false, PACKED, SB>(red, tiles, rec, base, lim, lane, wv, mv, word, s0, ms0,
+        worker_block<false, PACKED, SB, CACHED>(red, tiles, rec, base, lim, lane, wv, mv, word, s0, ms0,
                                         m_scales, gv, cv, scales, ei, bi, partial + i * num_tiles,
                                         beta1, omb1);
 }
@@ -2553,6 +2548,17 @@ hipError_t launch_warmup(const DeviceTables &tb, float *x, float *m, float *v, c
     return hipGetLastError();
 }
 
+// Whether a call's gradient and error rows stay in the 256 MB last-level cache
+// until the next step: up to a quarter of it.  Non-temporal accesses then only
+// push them out.  Step over three states in turn, fp32, us, streamed / cached:
+// 2^20 elements n = 4 (32 MB) 22.8 / 21.6, 5x10^5 n = 16 (64 MB) 29.9 / 28.0,
+// 10^6 n = 8 31.3 / 29.6, 2x10^6 n = 4 37.8 / 36.3; but 10^6 n = 16 (128 MB)
+// 45.6 / 49.2, 4x10^6 n = 4 59.6 / 63.1.
+static bool rows_cached(int64_t items, size_t grad_bytes)
+{
+    return items * kTileElems * (int64_t)(grad_bytes + 4) <= (int64_t)64 << 20;
+}
+
 template <bool PACKED, class G>
 static void launch_worker_items(const DeviceTables &tb, int64_t num_tiles, const float *m,
                                 const uint64_t *m_bits, const float *m_scales, const void *g,
@@ -2561,10 +2567,12 @@ static void launch_worker_items(const DeviceTables &tb, int64_t num_tiles, const
                                 double *partial, int n_local, float beta1, hipStream_t s)
 {
     const int64_t items = (int64_t)n_local * tb.num_blocks;
+    const auto kernel = rows_cached(items, sizeof(typename G::T))
+                            ? k_worker_pass<PACKED, G, true>
+                            : k_worker_pass<PACKED, G, false>;
     for (int64_t base = 0; base < items; base += kMaxPassItems) {
         const int64_t count = std::min(items - base, kMaxPassItems);
-        hipLaunchKernelGGL((k_worker_pass<PACKED, G>),
-                           dim3((unsigned)worker_grid(count, kMaxPassItems)),
+        hipLaunchKernelGGL(kernel, dim3((unsigned)worker_grid(count, kMaxPassItems)),
                            dim3(kWave * kPassWaves<G>), kPassIdleLds<G>, s, tb.tiles, tb.blocks,
                            tb.num_blocks, fast_div(tb.num_blocks), tb.padded_len, num_tiles, m,
                            m_bits, m_scales, (const typename G::T *)g, g_ld, err, err_ld, scales,
