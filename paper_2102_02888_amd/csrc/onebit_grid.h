@@ -17,17 +17,13 @@ namespace onebit {
 constexpr int kWave = 64;
 constexpr int kWavesPerBlock = 4;
 constexpr int kBlock = kWave * kWavesPerBlock;
-// The packed worker pass runs one tile per two-wave workgroup, half a tile
-// per wave.
-constexpr int kWorkerWavesPerBlock = 2;
-constexpr int kWorkerBlock = kWave * kWorkerWavesPerBlock;
 
-// The kernels that sum the n gradient rows of each tile (warm-up, the 32-bit
-// comparison step) run 16-wave workgroups over 16 consecutive tiles.
+// The first compression step's row walk runs 16-wave workgroups and gives two
+// waves to each 1024-element block (half a block each): 8 blocks per
+// workgroup.
+constexpr int kWorkerWavesPerBlock = 2;
 constexpr int kRowWaves = 16;
 constexpr int kRowBlock = kWave * kRowWaves;
-// The first compression step's row walk gives two waves to each tile (half a
-// tile each), so its 16-wave workgroups cover 8 tiles.
 constexpr int kWorkerRowTiles = kRowWaves / kWorkerWavesPerBlock;
 
 // Workgroups are dispatched to the chip's 8 XCDs round-robin (block b runs on
@@ -38,16 +34,16 @@ constexpr int kWorkerRowTiles = kRowWaves / kWorkerWavesPerBlock;
 constexpr int kXcds = 8;
 
 // Plans keep the tile count below 2^25, so a grid of one wave per tile stays
-// far below the 2^32 work-item limit.  Kernels over larger pair counts cap
-// their grid at kMaxGridBlocks and stride.  The worker grid (128-thread
-// blocks) may reach 2^24 blocks, 2^31 work-items, so that a BERT-Large-sized
-// pass (n = 32) runs one item per workgroup.  Kernels that give more than 64
-// threads to a tile (the first compression step: 128; the chunk owners'
-// per-tile workgroups: up to 256) are launched over at most kMaxLaunchTiles
-// tiles (or table-sharing workgroups) at a time, at most 2^30 work-items per
-// launch.
+// far below the 2^32 work-item limit.  Kernels over larger counts cap their
+// grid at kMaxGridBlocks and stride, or are launched in pieces: at most
+// kMaxLaunchTiles blocks, tiles or table-sharing workgroups of up to 256
+// threads at a time (2^30 work-items), and at most kMaxPassItems (row, block)
+// items of the worker pass, one workgroup of up to 256 threads each, so that a
+// BERT-Large-sized pass (n = 32) is one launch.
 constexpr int64_t kMaxGridBlocks = (int64_t)1 << 22;
 constexpr int64_t kMaxWorkerGridBlocks = (int64_t)1 << 24;
+constexpr int64_t kMaxPassItems = (int64_t)3 << 22;
+static_assert(kMaxPassItems <= kMaxWorkerGridBlocks, "a piece fits the worker grid");
 constexpr int64_t kMaxLaunchTiles = (int64_t)1 << 22;
 
 // Tiles (or workgroups) of the launch that starts at base, of total.
@@ -93,7 +89,7 @@ ONEBIT_HD inline int32_t server_block_entry(int64_t pos, int64_t count, int64_t 
 ONEBIT_HD inline int64_t server_block_first(int32_t entry) { return entry >> 3; }
 ONEBIT_HD inline int server_block_tiles(int32_t entry) { return entry & 7; }
 
-// Worker pass: items [0, num_items) are cut into kXcds contiguous ranges and
+// Worker pass: items [0, num_items) of a launch are cut into kXcds contiguous ranges and
 // XCD x walks range x with its grid / kXcds blocks; a grid smaller than the
 // item count strides within the range.  Physical block b (all its waves
 // together) takes items first, first + stride, ... below end.

@@ -9,9 +9,8 @@
 namespace onebit {
 
 // A unit of work: up to kTileElems consecutive elements of one segment,
-// starting on a 64-element (one sign word) boundary.  One wavefront owns one
-// tile (one tile of one worker row, in the packed worker pass); the launch
-// shapes are in onebit_grid.h.
+// starting on a 64-element (one sign word) boundary.  Partial sums are kept per
+// tile, and the chunk owners' passes with lookup tables walk tiles.
 struct Tile {
     int64_t start;  // first flat element (multiple of 64)
     int32_t len;    // elements in the tile, 1..kTileElems

@@ -2,22 +2,23 @@
 //
 // Every kernel streams over the flat parameter buffer and, except for the
 // chunk owners' decode-and-average (bound by vector ALU issue), is bound by
-// HBM bandwidth; no MFMA (nothing here is a dense contraction).  Work is cut
-// into tiles of up to 1024 elements that never cross a segment; one
-// wavefront (64 lanes) owns one tile, each lane holding 4 sub-blocks x float4
-// = 16 elements (in the packed worker pass two waves share a tile, 2
-// sub-blocks each), so every global load/store is a 128-bit access and a
-// wave moves 1 KiB per instruction.  A sub-block of 256 elements spans four 16-lane DPP rows, and
-// each row's 64 elements form one LSB-first uint64 sign word (bit b of word w
-// of the tile <=> element 64w+b), assembled with a row-wide OR of the lanes'
-// 4-bit nibbles.
+// HBM bandwidth; no MFMA (nothing here is a dense contraction).  The streaming
+// passes walk blocks of 1024 elements (onebit_internal.h), each wave (64 lanes)
+// holding one or more sub-blocks of 256 elements, a float4 per lane, so every
+// global load/store is a 128-bit access and a wave moves 1 KiB per instruction.
+// The chunk owners' passes with lookup tables walk tiles, up to 1024 elements
+// that never cross a segment, as lists of one owner's tiles.  A sub-block spans
+// four 16-lane DPP rows, and each row's 64 elements form one LSB-first uint64
+// sign word (bit b of word w of a block or tile <=> element 64w+b), assembled
+// with a row-wide OR of the lanes' 4-bit nibbles.
 //
 // Arithmetic contract (shared with the layout/format description in
 // onebit.h): fp32 values, one rounding per operation (built with
 // -ffp-contract=off), correctly rounded sqrt and division, fp64 reductions
 // rounded once to fp32.  Reductions over a segment are deterministic:
 // per-tile partial sums (a fixed lane reduction order) are written to a
-// workspace and summed in a fixed order by a finalize kernel; no atomics.
+// workspace and summed in a fixed order by a finalize kernel, or by the pass
+// that needs the scale; no atomics.
 #include "onebit_internal.h"
 #include <algorithm>
 #include <mutex>
@@ -38,7 +39,7 @@ typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
 // an operand.  Loads are non-temporal (nt); stores are non-temporal at device
 // scope (nt and sc1), which drains the streams of written state to HBM faster
 // than nt alone.  The resource covers 2 GiB from the base, far more than a
-// tile; its fourth word is the gfx9-family buffer format word.
+// block; its fourth word is the gfx9-family buffer format word.
 constexpr int kStreamLoad = 2;        // nt
 constexpr int kStreamStore = 2 | 16;  // nt, sc1
 // Small plans, whose rows stay in the last-level cache from step to step
@@ -200,9 +201,9 @@ __device__ __forceinline__ int64_t xcd_block() { return xcd_block_of(blockIdx.x,
 
 // This wave's number within its workgroup, as a wave-uniform (scalar) value,
 // so that tile indices, tile descriptors and the addresses derived from them
-// stay in scalar registers.  The chunk owners' kernels use it; the streaming
-// kernels keep the plain form, since with the scalar one the compiler spills
-// their scalar registers (their buffer bases are made uniform by stream_rsrc).
+// stay in scalar registers.  Kernels whose waves take different tiles or blocks
+// use it; where a workgroup has one block, the block's number already is
+// scalar.
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 // Error from the compensated form: z - C[z] given z and its segment scale s.
@@ -752,17 +753,13 @@ __global__ __launch_bounds__(kBlock) void k_adam_message(
 // 3.666, 3.645, 3.589, 3.556, 3.542, 3.781 / 3.128, 3.097, 3.041, 3.033,
 // 3.095, 3.704; four at 8, 3, 2 waves 3.727, 3.574, 3.541 / 3.222, 3.038,
 // 3.218.
-// An fp32 momentum (the first compression step) is read once per tile for all
-// local workers instead, by k_worker_rows.
+//
+// An fp32 momentum (the first compression step) is read once per block for all
+// local workers instead, by k_worker_rows, but on small plans.
 // ---------------------------------------------------------------------------
 // Unused dynamic LDS that lets `groups` workgroups of a kernel onto a CU at
 // once (160 KB of LDS, allocated in steps of 512 bytes or less).
 constexpr int idle_lds(int groups) { return 160 * 1024 / groups / 512 * 512; }
-
-// Sub-blocks per wave of the first compression step's row walk.
-constexpr int kWorkerSubBlocks = 2;
-static_assert(kSubBlocks / kWorkerSubBlocks == kWorkerWavesPerBlock,
-              "the row walk gives each wave of a pair part of one tile");
 
 // The packed pass: sub-blocks per wave, waves per workgroup (one block), and
 // the unused LDS that holds the occupancy at 5 waves per SIMD (160 KB of LDS
@@ -771,8 +768,6 @@ template <class G>
 constexpr int kPassSubBlocks = sizeof(typename G::T) == 2 ? 2 : 1;
 template <class G>
 constexpr int kPassWaves = kSubBlocks / kPassSubBlocks<G>;
-// Items of one launch: at most 256 threads each, below 2^32 work-items.
-constexpr int64_t kMaxPassItems = (int64_t)3 << 22;
 template <class G>
 constexpr int kPassIdleLds = sizeof(typename G::T) == 2 ? idle_lds(10) - 512 : 0;
 
@@ -975,10 +970,11 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
 // 4.54, of 4 (one sub-block) 4.68, two workgroups per CU 4.45, the packed pass
 // reading m for every worker 4.80.
 // ---------------------------------------------------------------------------
-constexpr int kWalkSubBlocks = 2;
-constexpr int kWalkWaves = 16;
-constexpr int kWalkParts = kSubBlocks / kWalkSubBlocks;   // waves per block
-constexpr int kWalkBlocks = kWalkWaves / kWalkParts;      // blocks per workgroup
+constexpr int kWalkParts = kWorkerWavesPerBlock;          // waves per block
+constexpr int kWalkSubBlocks = kSubBlocks / kWalkParts;   // sub-blocks per wave
+constexpr int kWalkWaves = kRowWaves;
+constexpr int kWalkBlocks = kWorkerRowTiles;              // blocks per workgroup
+static_assert(kWalkBlocks * kWalkParts == kWalkWaves, "whole blocks");
 
 template <bool WHOLE, class G>
 __device__ __forceinline__ void worker_rows_walk(
