@@ -89,8 +89,31 @@ ONEBIT_HD inline int32_t server_block_entry(int64_t pos, int64_t count, int64_t 
 ONEBIT_HD inline int64_t server_block_first(int32_t entry) { return entry >> 3; }
 ONEBIT_HD inline int server_block_tiles(int32_t entry) { return entry & 7; }
 
-// Worker pass: items [0, num_items) of a launch are cut into kXcds contiguous ranges and
-// XCD x walks range x with its grid / kXcds blocks; a grid smaller than the
+// Exact quotient of an item number below 2^31 by a fixed divisor d < 2^31:
+// (item * mul) >> shift with mul = ceil(2^(31+s) / d), s = ceil(log2 d),
+// shift = 31 + s.  mul * d exceeds 2^(31+s) by less than d <= 2^s, so the
+// error item * (mul * d - 2^(31+s)) / (d * 2^(31+s)) stays below 1/d.
+struct FastDiv {
+    uint64_t mul;
+    uint32_t shift;
+};
+
+ONEBIT_HD inline FastDiv fast_div(int64_t d)
+{
+    uint32_t s = 0;
+    while (((int64_t)1 << s) < d) ++s;
+    const uint64_t one = (uint64_t)1 << (31 + s);
+    return {(one + (uint64_t)d - 1) / (uint64_t)d, 31 + s};
+}
+
+// Quotient of x (below 2^31) by the divisor f was made for.
+ONEBIT_HD inline int64_t fast_quotient(int64_t x, FastDiv f)
+{
+    return (int64_t)(((uint64_t)x * f.mul) >> f.shift);
+}
+
+// Worker pass: items [0, num_items) of a launch are cut into kXcds contiguous
+// ranges and XCD x walks range x with its grid / kXcds blocks; a grid smaller than the
 // item count strides within the range.  Physical block b (all its waves
 // together) takes items first, first + stride, ... below end.
 struct ItemWalk {

@@ -57,23 +57,6 @@ struct DeviceTables {
                                    // (entries of onebit_grid.h's server_block_entry)
 };
 
-// Exact quotient of an item number below 2^31 by a fixed divisor d < 2^31:
-// (item * mul) >> shift with mul = ceil(2^(31+s) / d), s = ceil(log2 d),
-// shift = 31 + s.  mul * d exceeds 2^(31+s) by less than d <= 2^s, so the
-// error item * (mul * d - 2^(31+s)) / (d * 2^(31+s)) stays below 1/d.
-struct FastDiv {
-    uint64_t mul;
-    uint32_t shift;
-};
-
-inline FastDiv fast_div(int64_t d)
-{
-    uint32_t s = 0;
-    while (((int64_t)1 << s) < d) ++s;
-    const uint64_t one = (uint64_t)1 << (31 + s);
-    return {(one + (uint64_t)d - 1) / (uint64_t)d, 31 + s};
-}
-
 // Gradient element types (the values of the ONEBIT_GRAD_* constants).
 constexpr int kGradF32 = 0;
 constexpr int kGradBF16 = 1;

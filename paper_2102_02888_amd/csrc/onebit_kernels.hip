@@ -923,7 +923,7 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     const ItemWalk walk = xcd_item_walk(blockIdx.x, gridDim.x, num_items);
     if (walk.first >= walk.end) return;  // the whole workgroup
     const int64_t item = item_base + walk.first;
-    const int64_t i = (int64_t)(((uint64_t)item * by_blocks.mul) >> by_blocks.shift);
+    const int64_t i = fast_quotient(item, by_blocks);
     const int64_t blk = item - i * num_blocks;
     const int64_t base = blk * kTileElems;
     const int64_t room = padded_len - base;
@@ -2263,7 +2263,8 @@ __device__ __forceinline__ void update_sub(const Lane4 &l, int li, v4f xv, v4f v
 // (half a tile per wave: 0.640 and 1.070 ms), in one A/B process each.  Six
 // workgroups per CU, held by unused LDS, keep about 12 KB in flight per SIMD:
 // one GPU's share of a BERT-Large step (its own worker row, the update) 1.306
-// ms at eight, 1.293 at six, 1.366 at five.
+// ms at eight, 1.293 at six, 1.366 at five in one process; in another 1.321 at
+// eight, 1.320 at six.
 //
 // FORM: the scales are formed here from the chunk owners' partial sums (see
 // wave_scale), which saves the finalize kernel's launch.
@@ -2357,7 +2358,7 @@ __global__ __launch_bounds__(kBlock) void k_materialize(
     const ItemWalk walk = xcd_item_walk(blockIdx.x, gridDim.x, num_items);
     if (walk.first >= walk.end) return;
     const int64_t item = item_base + walk.first;
-    const int64_t r = (int64_t)(((uint64_t)item * by_blocks.mul) >> by_blocks.shift);
+    const int64_t r = fast_quotient(item, by_blocks);
     const int64_t blk = item - r * num_blocks;
     const int64_t base = blk * kTileElems;
     const int64_t room = padded_len - base;

@@ -9,7 +9,7 @@ caller fills `grads` (one row per simulated worker) before each step().
 
 With graph=True the steady compressed step (packed momentum, from the second
 compression step on) is captured once in a HIP graph and replayed: one launch
-instead of five, for models small enough that launch latency matters.  The
+instead of three to six, for models small enough that launch latency matters.  The
 graph holds the state's buffer addresses, so `grads` must be filled in place;
 it is captured again whenever lr, beta1 or eps changes.
 """

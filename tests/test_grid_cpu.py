@@ -23,6 +23,18 @@ def test_every_tile_and_item_is_taken_once(tmp_path):
     assert "grid_check: ok" in r.stdout
 
 
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_every_row_and_block_of_the_worker_pass_is_taken_once(tmp_path):
+    exe = str(tmp_path / "items_check")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-Werror",
+                    "-I" + os.path.join(ROOT, "paper_2102_02888_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "c", "items_check.cpp"), "-o", exe],
+                   check=True, timeout=300)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout[-2000:]
+    assert "items_check: ok" in r.stdout
+
+
 def test_parity_cases_reach_every_partial_tile_shape():
     """The packed worker pass splits each tile between two waves (sub-blocks
     0-1 and 2-3), so a segment's last tile can end inside wave 0's first
