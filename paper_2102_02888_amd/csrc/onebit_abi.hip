@@ -132,13 +132,11 @@ bool server_direct(const onebit_plan_s *p, int32_t begin, int32_t end)
 // to 2^20, n = 8 83.4 / 81.2 / 85.3 / 82.7; 2x10^6, n = 16 83.6 / 83.7 / 85.0 /
 // 84.8; 4x10^6, n = 16 148 / 153 / 157 / 162; 160 tensors up to 2^20, n = 4 183 /
 // 186 / 207 / 209.
-constexpr int64_t kFormMaxSegTiles = 256;
-
 // Worker scales: a tile reads n rows of its segment's partial sums, at most
 // 1,024 on average, and there are at most 8,192 tiles (no lookup tables then).
 bool forms_worker_scales(const onebit_plan_s *p)
 {
-    return p->T > 0 && p->T <= 8192 && p->max_seg_tiles <= kFormMaxSegTiles &&
+    return p->T > 0 && p->T <= 8192 && p->max_seg_tiles <= onebit::kWaveSegTiles &&
            p->n <= onebit::kServerRowBatch && p->n * p->tile_pairs <= 1024 * p->T &&
            !server_uses_tables(p, 0, p->n);
 }
@@ -147,7 +145,7 @@ bool forms_worker_scales(const onebit_plan_s *p)
 // plan is a single round of waves, or a few with short segments.
 bool forms_server_scales(const onebit_plan_s *p)
 {
-    return p->T > 0 && p->max_seg_tiles <= kFormMaxSegTiles &&
+    return p->T > 0 && p->max_seg_tiles <= onebit::kWaveSegTiles &&
            (p->T <= 1200 || (p->T <= 4096 && p->tile_pairs <= 16 * p->T));
 }
 

@@ -44,6 +44,10 @@ struct alignas(16) Segment {
     int32_t pad[3];
 };
 
+// Plans whose segments all have at most this many tiles add a segment's partial
+// sums in the order of a wave (see segment_sum), others in a workgroup's.
+constexpr int kWaveSegTiles = 256;
+
 // Device-side layout tables owned by a plan.
 struct DeviceTables {
     const Tile *tiles;             // [T], in address (segment) order

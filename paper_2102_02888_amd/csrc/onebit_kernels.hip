@@ -555,6 +555,42 @@ __global__ __launch_bounds__(Sh::WAVES *kWave) void k_uncompressed(
 }
 
 // ---------------------------------------------------------------------------
+// The sum of a segment's per-tile partial sums, in one order for every plan
+// whose segments have at most 256 tiles, whichever pass or number of lanes adds
+// them: 64 strided sums, v's being (p[v] + p[v + 64]) + (p[v + 128] + p[v +
+// 192]), then v and v + 32, then v and v + 16, and so on down to v and v + 1.
+// LANES lanes (a power of two) each hold 64 / LANES of the strided sums; MAX is
+// the most tiles there can be, and all loads are issued together.  Every lane
+// gets the sum.  (Absent tiles add 0, which changes no sum of squares.)
+// ---------------------------------------------------------------------------
+template <int LANES, int MAX>
+__device__ __forceinline__ double segment_sum(const double *__restrict__ part, int tiles, int lane)
+{
+    constexpr int J = MAX < kWave ? (MAX + LANES - 1) / LANES : kWave / LANES;
+    constexpr int R = (MAX + kWave - 1) / kWave;
+    static_assert((J & (J - 1)) == 0 && (R == 1 || R == 4), "whole rounds");
+    double p[R][J];
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int t = lane + LANES * j + kWave * k;
+            p[k][j] = t < tiles ? part[t] : 0.0;
+        }
+    double s[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+        s[j] = R == 1 ? p[0][j] : (p[0][j] + p[R > 1][j]) + (p[R / 2][j] + p[R - 1][j]);
+#pragma unroll
+    for (int h = J / 2; h >= 1; h /= 2)
+#pragma unroll
+        for (int j = 0; j < h; ++j) s[j] += s[j + h];
+#pragma unroll
+    for (int off = LANES / 2; off >= 1; off >>= 1) s[0] += __shfl_xor(s[0], off, kWave);
+    return s[0];
+}
+
+// ---------------------------------------------------------------------------
 // Scales formed where they are needed (the fused step on plans whose segments
 // have few tiles): the pass that reads a scale sums its segment's partial sums
 // itself, and the part that holds the segment's first word writes the scale
@@ -1075,46 +1111,52 @@ __global__ __launch_bounds__(kWalkWaves *kWave) void k_worker_rows(
 }
 
 // ---------------------------------------------------------------------------
-// Scale finalize: scale = fp32(sqrt(sum over the segment's tiles / len)),
-// summed in a fixed order (so results do not depend on scheduling); empty
-// segments get 0.  LANES lanes cooperate on one segment of one row, fewer for
+// Scale finalize: scale = fp32(sqrt(sum over the segment's tiles / len)); empty
+// segments get 0.  The order of the sum is the plan's (segment_sum's, or a
+// workgroup's where a segment has more than 256 tiles), so a scale depends
+// neither on scheduling nor on the rows or owners of a call.  LANES lanes
+// cooperate on one segment of one row, fewer for
 // segments of few tiles (launch_finalize): with a wave for each, the 2 million
 // (row, segment) pairs of 2,000 tensors of 64 to 8192 elements with n = 32
 // took 470 us of a 900 us step, which is 422 us with a lane for each; the
 // 5,000-tensor workload's step went from 10.05 to 9.98 ms with 16 lanes.
 // ---------------------------------------------------------------------------
-template <int LANES>
+// The sum by a whole workgroup.
+__device__ __forceinline__ double block_segment_sum(const double *__restrict__ part, int tiles,
+                                                    double *red)
+{
+    const int tid = threadIdx.x;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    int t = tid;
+    for (; t + 3 * kBlock < tiles; t += 4 * kBlock) {
+        s0 += part[t];
+        s1 += part[t + kBlock];
+        s2 += part[t + 2 * kBlock];
+        s3 += part[t + 3 * kBlock];
+    }
+    for (; t < tiles; t += kBlock) s0 += part[t];
+    const double s = wave_sum((s0 + s1) + (s2 + s3));
+    if ((tid & (kWave - 1)) == 0) red[tid / kWave] = s;
+    __syncthreads();
+    return ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+template <int LANES, int MAX>
 __device__ __forceinline__ float finalize_one(const double *__restrict__ part, const Segment &seg,
                                               double *red)
 {
-    const int tid = threadIdx.x % LANES;
-    part += seg.tile;
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
-    int t = tid;
-    for (; t + 3 * LANES < seg.tiles; t += 4 * LANES) {
-        s0 += part[t];
-        s1 += part[t + LANES];
-        s2 += part[t + 2 * LANES];
-        s3 += part[t + 3 * LANES];
-    }
-    for (; t < seg.tiles; t += LANES) s0 += part[t];
-    double s = (s0 + s1) + (s2 + s3);
-#pragma unroll
-    for (int off = (LANES < kWave ? LANES : kWave) / 2; off >= 1; off >>= 1)
-        s += __shfl_xor(s, off, kWave);
-    if (LANES > kWave) {
-        const int wv = tid / kWave;
-        if ((tid & (kWave - 1)) == 0) red[wv] = s;
-        __syncthreads();
-        s = red[0];
-        for (int w = 1; w < LANES / kWave; ++w) s += red[w];
-    }
-    return seg.len > 0 ? (float)__builtin_sqrt(s / (double)seg.len) : 0.0f;
+    double s;
+    if constexpr (LANES > kWave)
+        s = block_segment_sum(part + seg.tile, seg.tiles, red);
+    else
+        s = segment_sum<LANES, MAX>(part + seg.tile, seg.tiles, threadIdx.x % LANES);
+    return seg.len > 0 ? scale_of(s, seg.len) : 0.0f;
 }
 
 // count segments per row; cnt = 0: segment p is the p-th, else (server form)
 // segments k*n + j for j in [jb, jb + cnt) and every tensor k, in that order.
-template <int LANES>
+// No segment has more than MAX tiles (if LANES is at most a wave).
+template <int LANES, int MAX>
 __global__ __launch_bounds__(kBlock) void k_finalize(const Segment *__restrict__ segs,
                                                      uint32_t count, int64_t rows, int n, int jb,
                                                      int cnt, const double *__restrict__ partial,
@@ -1132,7 +1174,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(const Segment *__restrict__
             const uint32_t q = cnt == 0 || cnt == n
                                    ? p
                                    : p / (uint32_t)cnt * (uint32_t)n + jb + p % (uint32_t)cnt;
-            const float s = finalize_one<LANES>(partial + i * part_ld, segs[q], red);
+            const float s = finalize_one<LANES, MAX>(partial + i * part_ld, segs[q], red);
             if (threadIdx.x % LANES == 0) scales[i * scales_ld + q] = s;
             if (LANES > kWave) __syncthreads();  // red is reused by the next segment
         }
@@ -2692,7 +2734,7 @@ hipError_t launch_decode(const DeviceTables &tb, const uint64_t *bits, const flo
     return hipGetLastError();
 }
 
-template <int LANES>
+template <int LANES, int MAX>
 static void launch_finalize_t(const DeviceTables &tb, int64_t num_segments, int64_t rows, int n,
                               int jb, int cnt, const double *partial, int64_t part_ld,
                               float *scales, int64_t scales_ld, hipStream_t s)
@@ -2700,7 +2742,7 @@ static void launch_finalize_t(const DeviceTables &tb, int64_t num_segments, int6
     const int64_t per = kBlock / LANES;
     const dim3 grid((unsigned)std::min((num_segments + per - 1) / per, kMaxGridBlocks),
                     (unsigned)std::min(rows, kMaxGridRows));
-    hipLaunchKernelGGL(k_finalize<LANES>, grid, dim3(kBlock), 0, s, tb.segs,
+    hipLaunchKernelGGL((k_finalize<LANES, MAX>), grid, dim3(kBlock), 0, s, tb.segs,
                        (uint32_t)num_segments, rows, n, jb, cnt, partial, part_ld, scales,
                        scales_ld);
 }
@@ -2711,15 +2753,16 @@ hipError_t launch_finalize(const DeviceTables &tb, int64_t max_seg_tiles, int64_
 {
     if (num_segments <= 0 || rows <= 0) return hipSuccess;
     // A workgroup for segments above 256 tiles (there are few of them, and
-    // their latency counts).  Below that as many lanes as leave a lane at most
-    // 16 partial sums, but a whole wave, with fewer dependent steps, while all
-    // the pairs' waves are on the chip at once anyway.
+    // their latency counts), which is the plan's order of summation too.  Below
+    // that the lanes share one order: as many as leave a lane at most 16
+    // partial sums, but a whole wave, with fewer dependent steps, while all the
+    // pairs' waves are on the chip at once anyway.
     const bool few = num_segments * rows <= 4096;
-    const auto launch = max_seg_tiles > 4 * kWave            ? launch_finalize_t<kBlock>
-                        : max_seg_tiles > 4 && few           ? launch_finalize_t<kWave>
-                        : max_seg_tiles > kWave              ? launch_finalize_t<16>
-                        : max_seg_tiles > 4                  ? launch_finalize_t<8>
-                                                             : launch_finalize_t<1>;
+    const auto launch = max_seg_tiles > kWaveSegTiles ? launch_finalize_t<kBlock, kWaveSegTiles>
+                        : max_seg_tiles > 4 && few       ? launch_finalize_t<kWave, kWaveSegTiles>
+                        : max_seg_tiles > kWave          ? launch_finalize_t<16, kWaveSegTiles>
+                        : max_seg_tiles > 4              ? launch_finalize_t<8, kWave>
+                                                         : launch_finalize_t<1, 4>;
     launch(tb, num_segments, rows, n, jb, cnt, partial, part_ld, scales, scales_ld, s);
     return hipGetLastError();
 }

@@ -1,0 +1,87 @@
+"""One order of every 64-bit sum per plan: the same values give the same scale
+bit for bit whichever call, momentum form, gradient type or lookup-table mode
+computes it.  The values are chosen so that the last bits of a sum of squares
+decide its scale (parity_util.knife_edge); without gradients, momentum and
+earlier scales the compensated values are the error state's own."""
+import numpy as np
+import pytest
+import torch
+
+from parity_util import knife_edge_rows
+
+pytestmark = pytest.mark.gpu
+
+
+def _state(plan, dev, worker=None, server=None, **more):
+    """A state whose next step's compensated values are the given rows."""
+    import paper_2102_02888_amd as ob
+    st = ob.State(plan, dev, **more)
+    st.v.fill_(1.0)
+    if worker is not None:
+        st.worker_err.copy_(worker)
+    if server is not None:
+        st.server_err.copy_(server)
+    return st
+
+
+def _knife(plan, dev, seed, rows=1):
+    return torch.from_numpy(knife_edge_rows(np.random.default_rng(seed), plan, rows)).to(dev)
+
+
+def _compress(st, m=None, rows=None):
+    import paper_2102_02888_amd as ob
+    ob.onebit_worker_compress(st.plan, m, st.grads, st.worker_err, st.worker_bits,
+                              st.worker_scales, 0.9, st.workspace, n_local=rows,
+                              m_bits=st.server_bits, m_scales=st.server_scales)
+
+
+def _reduce(st, begin, end):
+    import paper_2102_02888_amd as ob
+    ob.onebit_server_reduce_compress(st.plan, begin, end, st.worker_bits, st.worker_scales,
+                                     st.server_err, st.server_bits, st.server_scales,
+                                     st.workspace)
+
+
+def _same(a, b, what):
+    bad = int((a.view(torch.int32) != b.view(torch.int32)).sum())
+    assert bad == 0, "%s: %d of %d scales differ" % (what, bad, a.numel())
+
+
+# The segments of one row (or owner) and of all of them lie on both sides of
+# the number below which the finalize kernel gives each segment a wave.
+@pytest.mark.parametrize("each,count,n", [
+    (160_000, 300, 8),       # 20 tiles a segment
+    (560_000, 90, 8),        # 69
+    (4_000_000, 20, 16),     # 245
+    (6000, 1200, 2),         # 3
+])
+def test_worker_scale_does_not_depend_on_the_rows_of_the_call(dev, each, count, n):
+    import paper_2102_02888_amd as ob
+    plan = ob.Plan([each] * count, n)
+    row = _knife(plan, dev, each)
+    got = []
+    for r in (1, n):
+        st = _state(plan, dev, row.expand(r, -1), n_local=r, grad_dtype=torch.bfloat16)
+        _compress(st)
+        torch.cuda.synchronize()
+        for i in range(r):
+            got.append(st.worker_scales[i].clone())
+        del st
+    assert plan.S <= 4096 < plan.S * n
+    for i, s in enumerate(got[1:]):
+        _same(got[0], s, "row %d" % i)
+    plan.close()
+
+
+@pytest.mark.parametrize("each,count,n", [(160_000, 600, 8), (1_000_000, 75, 4), (700_000, 9, 3)])
+def test_server_scale_does_not_depend_on_the_owned_range(dev, each, count, n):
+    import paper_2102_02888_amd as ob
+    plan = ob.Plan([each] * count, n)
+    z = _knife(plan, dev, each)[0]
+    a, b = (_state(plan, dev, server=z, n_local=n, grad_dtype=torch.bfloat16) for _ in range(2))
+    _reduce(a, 0, n)
+    for j in range(n):
+        _reduce(b, j, j + 1)
+    torch.cuda.synchronize()
+    _same(a.server_scales, b.server_scales, "server scales")
+    plan.close()
