@@ -612,46 +612,21 @@ __device__ __forceinline__ void zero_empty(float *__restrict__ scales, int q, co
         for (int e = lane; e < q; e += lanes) scales[e] = 0.f;
 }
 
-// The scale of segment sg from its partial sums, by a whole wave or by each
-// 16-lane row for a segment of its own, in one order: 64 strided sums (v, v +
-// 64, ...), added as v and v + 32, then with v + 16 and v + 48, then over 16.
-// A round of loads covers 256 tiles, issued together.
+// The scale of segment sg (at most kWaveSegTiles tiles), in the finalize
+// kernel's order, by a whole wave or by each 16-lane row for a segment of its
+// own.
 __device__ __forceinline__ float wave_scale(const Segment &sg, const double *__restrict__ partial,
                                             int lane)
 {
-    double s = 0.0;
-    for (int t0 = lane; t0 < sg.tiles; t0 += 4 * kWave) {
-        double p[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            p[k] = t0 + k * kWave < sg.tiles ? partial[sg.tile + t0 + k * kWave] : 0.0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) s += p[k];
-    }
-    s += __shfl_xor(s, 32, kWave);
-    s += __shfl_xor(s, 16, kWave);
-    return scale_of(row_sum(s), sg.len);
+    return scale_of(segment_sum<kWave, kWaveSegTiles>(partial + sg.tile, sg.tiles, lane),
+                    sg.len);
 }
 
 __device__ __forceinline__ float row_scale(const Segment &sg, const double *__restrict__ partial,
                                            int lane)
 {
-    double s[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int t0 = lane & 15; t0 < sg.tiles; t0 += 4 * kWave) {
-        double p[4][4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int t = t0 + k * kWave + 16 * j;
-                p[k][j] = t < sg.tiles ? partial[sg.tile + t] : 0.0;
-            }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s[j] += p[k][j];
-    }
-    return scale_of(row_sum((s[0] + s[2]) + (s[1] + s[3])), sg.len);
+    return scale_of(segment_sum<16, kWaveSegTiles>(partial + sg.tile, sg.tiles, lane & 15),
+                    sg.len);
 }
 
 // ---------------------------------------------------------------------------
@@ -1789,6 +1764,54 @@ __global__ __launch_bounds__(kBlock) void k_server_direct(
                                    partial);
 }
 
+// The sums of a segment's partial sums of n workers, n <= N (rows of part_ld),
+// by one wave, in segment_sum's order: lane L gets worker L / (64 / N)'s (any
+// value where that is n or more).  Up to 64 tiles the lanes of a worker add its
+// tiles, in one, four or more loads each.  Beyond (at most kWaveSegTiles) the
+// wave takes four workers at a time, every lane its strided sum of each; the
+// first two exchanges also leave each 16 lanes with one worker to go on with.
+template <int N>
+__device__ __forceinline__ double worker_segment_sums(const double *__restrict__ part,
+                                                      int64_t part_ld, int n, int tiles, int lane)
+{
+    constexpr int kPer = kWave / N;
+    const int mine = lane / kPer;
+    if (tiles <= kWave) {
+        const double *row = part + min(mine, n - 1) * part_ld;
+        if (tiles <= kPer) return segment_sum<kPer, kPer>(row, tiles, lane % kPer);
+        if (4 * kPer < kWave && tiles <= 4 * kPer)
+            return segment_sum<kPer, 4 * kPer>(row, tiles, lane % kPer);
+        return segment_sum<kPer, kWave>(row, tiles, lane % kPer);
+    }
+    double sum = 0.0;
+#pragma unroll 1
+    for (int r0 = 0; r0 < n; r0 += 4) {
+        double p[4][4], s[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int t = lane + kWave * k;
+                p[r][k] = t < tiles ? part[min(r0 + r, n - 1) * part_ld + t] : 0.0;
+            }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s[r] = (p[r][0] + p[r][1]) + (p[r][2] + p[r][3]);
+#pragma unroll
+        for (int keep = 2, off = kWave / 2; keep >= 1; keep /= 2, off /= 2) {
+            const bool upper = (lane & off) != 0;
+#pragma unroll
+            for (int j = 0; j < keep; ++j) {
+                const double give = upper ? s[j] : s[j + keep];
+                s[j] = (upper ? s[j + keep] : s[j]) + __shfl_xor(give, off, kWave);
+            }
+        }
+        const double four = row_sum(s[0]);  // worker r0 + lane / 16's
+        const double v = N == 4 ? four : __shfl(four, 16 * (mine & 3), kWave);
+        if (mine - r0 >= 0 && mine - r0 < 4) sum = v;
+    }
+    return sum;
+}
+
 // ---------------------------------------------------------------------------
 // Chunk owners' pass for n <= kServerRowBatch, one wave per tile, building
 // the tables itself.  The tile's error-state and sign-word loads are issued
@@ -1805,8 +1828,8 @@ __global__ __launch_bounds__(kBlock) void k_server_direct(
 // stress workload.  Larger G8 is limited by its LDS.
 //
 // FORM (every chunk owned): the tiles are taken in address order, and the
-// workers' scales are formed here from their partial sums, 64 / (n rounded up
-// to a power of two) lanes per worker, which saves the finalize kernel's launch.
+// workers' scales are formed here from their partial sums, which saves the
+// finalize kernel's launch.
 template <int G8, bool FORM>  // groups of 8 workers the LDS tables hold: n <= 8 G8
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G8 == 1 ? 5 : 1))) void k_server_pass(
     const Tile *__restrict__ tiles, const int32_t *__restrict__ chunk_tiles, int64_t tile_begin,
@@ -1844,21 +1867,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(G8 == 1 
     float scl;
     if (FORM) {
         const Segment sg = segs[tile.seg];
-        const int per = n > 1 ? kWave >> (32 - __clz(n - 1)) : kWave;  // lanes per worker
+        const bool four = G8 == 1 && n <= 4;
+        const int per = four ? kWave / 4 : kWave / (8 * G8);  // lanes per worker
         const int r = lane / per;
-        double s = 0.0;
-        if (r < n) {
-            const double *src = wpartial + (int64_t)r * wpart_ld + sg.tile;
-            for (int k0 = lane % per; k0 < sg.tiles; k0 += 8 * per) {
-                double p[8];  // eight loads in flight
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-                    p[k] = k0 + k * per < sg.tiles ? src[k0 + k * per] : 0.0;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) s += p[k];
-            }
-        }
-        for (int off = per >> 1; off >= 1; off >>= 1) s += __shfl_xor(s, off, kWave);
+        const double *src = wpartial + sg.tile;
+        const double s = four ? worker_segment_sums<4>(src, wpart_ld, n, sg.tiles, lane)
+                              : worker_segment_sums<8 * G8>(src, wpart_ld, n, sg.tiles, lane);
         const float sr = scale_of(s, sg.len);
         const bool first = sg.tile == t;
         if (r < n && lane % per == 0) {

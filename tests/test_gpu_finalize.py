@@ -67,8 +67,7 @@ def test_scales_of_every_lane_count(dev, big, small, n):
 def test_fused_step_equals_the_three_calls(dev, numel, n):
     """The fused step, which forms the scales inside its passes on small
     plans, against the separate calls, which finalize them: every output bit
-    for bit but a scale that another order of its 64-bit sum rounds to the
-    next fp32 value (none is expected in so few)."""
+    for bit, as both add a segment's partial sums in one order."""
     import paper_2102_02888_amd as ob
     plan = ob.Plan(numel, n)
     a, b = ob.State(plan, dev), ob.State(plan, dev)

@@ -85,3 +85,35 @@ def test_server_scale_does_not_depend_on_the_owned_range(dev, each, count, n):
     torch.cuda.synchronize()
     _same(a.server_scales, b.server_scales, "server scales")
     plan.close()
+
+
+# Small plans, whose fused step forms both scales, the workers' or the owners'
+# alone in its passes (the separate calls finalize them): segments of up to 16
+# words, of several tiles, of more than 64 and of more than 128.
+@pytest.mark.parametrize("numel,n", [
+    ([1000] * 300 + [0] + [64 * 5] * 100, 2),
+    ([9000] * 110, 7),
+    ([65_000] * 60, 8),
+    ([250_000] * 30, 4),
+    ([1 << 20], 4),
+    ([500_000] * 4, 3),
+    ([150_000] * 6, 16),
+    ([30_000] * 30, 32),
+    ([3000] * 60, 33),
+    ([200_000], 1),
+])
+def test_fused_step_rounds_its_scales_as_the_three_calls(dev, numel, n):
+    import paper_2102_02888_amd as ob
+    plan = ob.Plan(numel, n)
+    for seed, what in ((1, "worker"), (2, "server"), (3, "worker"), (4, "server")):
+        z = _knife(plan, dev, seed, n if what == "worker" else 1)
+        z = {"worker": z} if what == "worker" else {"server": z[0]}
+        a, b = _state(plan, dev, **z), _state(plan, dev, **z)
+        a.compression_steps = 1
+        a.step(1e-3, 0.9, 1e-8)
+        _compress(b)
+        _reduce(b, 0, n)
+        torch.cuda.synchronize()
+        _same(a.worker_scales, b.worker_scales, "worker scales")
+        _same(a.server_scales, b.server_scales, "server scales")
+    plan.close()
