@@ -807,25 +807,46 @@ __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&
     }
 }
 
+// The wave's sum (wave_sum's) of each of SB values per lane, to sums[0 .. SB).
+// Two values share the exchanges: the first one leaves each half of the wave
+// with one value to go on with.
+template <int SB>
+__device__ __forceinline__ void store_wave_sums(const double (&a)[SB], double *sums, int lane)
+{
+    static_assert(SB == 1 || SB == 2, "");
+    if (SB == 1) {
+        const double s = wave_sum(a[0]);
+        if (lane == 0) sums[0] = s;
+        return;
+    }
+    const bool upper = lane >= kWave / 2;
+    double s = (upper ? a[SB - 1] : a[0]) + __shfl_xor(upper ? a[0] : a[SB - 1], kWave / 2, kWave);
+#pragma unroll
+    for (int off = kWave / 4; off >= 1; off >>= 1) s += __shfl_xor(s, off, kWave);
+    if ((lane & (kWave / 2 - 1)) == 0) sums[lane / (kWave / 2)] = s;
+}
+
 // The arithmetic and stores of this wave's sub-blocks of one block of a
 // worker's row: z = (beta1 m + (1 - beta1) g) + delta from the momentum term
 // bm = beta1 m, the gradient and the previous compensated value with its scale
-// sp; the new compensated value and the sign words are stored.  Returns the
-// lane's sum of z^2 (WHOLE), or writes the words' sums to words.
+// sp; the new compensated value and the sign words are stored.  sums (the
+// block's area in LDS) gets this wave's part of the sums of z^2: one per
+// sub-block (WHOLE) or one per word, so that the tiles' sums do not depend on
+// how many sub-blocks a wave takes.
 template <bool WHOLE, int SB, bool CACHED = false>
-__device__ __forceinline__ double worker_compute(const float (&sp)[SB], const int (&valid)[SB],
+__device__ __forceinline__ void worker_compute(const float (&sp)[SB], const int (&valid)[SB],
                                                  const v4f (&bm)[SB], const v4f (&gv)[SB],
                                                  const v4f (&cv)[SB], float *__restrict__ ei,
                                                  uint64_t *__restrict__ bi, int sb0, int lane,
-                                                 int lim, float omb1, double *words)
+                                                 int lim, float omb1, double *sums)
 {
-    double acc = 0.0;
+    double acc[SB];
 #pragma unroll
     for (int b = 0; b < SB; ++b) {
         const int li = (sb0 + b) * (kWave * 4) + 4 * lane;
         v4f zv;
         uint32_t nib = 0;
-        double sub = 0.0;
+        acc[b] = 0.0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             const float d = error_of(cv[b][c], sp[b]);
@@ -835,35 +856,29 @@ __device__ __forceinline__ double worker_compute(const float (&sp)[SB], const in
             zv[c] = z;
             const bool in = WHOLE || c < valid[b];
             const double zd = in ? (double)z : 0.0;
-            sub += zd * zd;
+            acc[b] += zd * zd;
             nib |= (in && z >= 0.f) ? (1u << c) : 0u;
         }
         stb4<WHOLE, CACHED>(ei, li, valid[b], zv);
         const uint64_t out = row_sign_word(nib, lane);
         const int w = 4 * (sb0 + b) + (lane >> 4);
         if ((lane & 15) == 0 && (WHOLE || li < lim)) bi[w] = out;
-        if (WHOLE) {
-            acc += sub;
-        } else {
-            const double row = row_sum(sub);
-            if ((lane & 15) == 0) words[w] = row;
+        if (!WHOLE) {
+            const double row = row_sum(acc[b]);
+            if ((lane & 15) == 0) sums[w] = row;
         }
     }
-    return acc;
+    if (WHOLE) store_wave_sums(acc, sums + sb0, lane);
 }
 
-// The block's partial sums (one per tile) from its waves' sums (WHOLE, waves
-// of them) or its words' sums, by the lanes of one wave.
+// The block's partial sums (one per tile) from its sub-blocks' sums (WHOLE) or
+// its words' sums, by the lanes of one wave.
 template <bool WHOLE>
 __device__ __forceinline__ void block_partials(double *__restrict__ partial, const Block &rec,
-                                               const double *sums, int waves, int lane)
+                                               const double *sums, int lane)
 {
     if (WHOLE) {
-        if (lane == 0) {
-            double sum = sums[0];
-            for (int k = 1; k < waves; ++k) sum += sums[k];
-            partial[rec.tile] = sum;
-        }
+        if (lane == 0) partial[rec.tile] = ((sums[0] + sums[1]) + sums[2]) + sums[3];
     } else if (lane < __popc(rec.starts)) {
         partial[rec.tile + lane] = block_tile_sum(sums, rec.starts, lane);
     }
@@ -903,14 +918,9 @@ __device__ __forceinline__ void worker_block(
 #pragma unroll
         for (int c = 0; c < 4; ++c) bm[b][c] = PACKED ? with_sign(bs, mnib, c) : beta1 * mv[b][c];
     }
-    double acc = worker_compute<WHOLE, SB, CACHED>(sp, valid, bm, gv, cv, ei, bi, sb0, lane, lim,
-                                                   omb1, red);
-    if (WHOLE) {
-        acc = wave_sum(acc);
-        if (lane == 0) red[wv] = acc;
-    }
+    worker_compute<WHOLE, SB, CACHED>(sp, valid, bm, gv, cv, ei, bi, sb0, lane, lim, omb1, red);
     __syncthreads();
-    if (wv == 0) block_partials<WHOLE>(partial, rec, red, kSubBlocks / SB, lane);
+    if (wv == 0) block_partials<WHOLE>(partial, rec, red, lane);
 }
 
 // PACKED: m_{t-1} is the previous step's gathered server message, decoded
@@ -1028,17 +1038,12 @@ __device__ __forceinline__ void worker_rows_walk(
     const auto finish = [&](int64_t i, const v4f(&gv)[SB], const v4f(&cv)[SB],
                             const float(&sp)[SB]) {
         double *sums = red[i & 1][wb];
-        if (active) {
-            double acc = worker_compute<WHOLE, SB>(sp, valid, bm, gv, cv, err + i * err_ld,
-                                                   bits + i * bits_ld, sb0, lane, lim, omb1, sums);
-            if (WHOLE) {
-                acc = wave_sum(acc);
-                if (lane == 0) sums[sb0 / SB] = acc;
-            }
-        }
+        if (active)
+            worker_compute<WHOLE, SB>(sp, valid, bm, gv, cv, err + i * err_ld, bits + i * bits_ld,
+                                      sb0, lane, lim, omb1, sums);
         __syncthreads();  // and the workgroup moves to the next row together
         if (active && sb0 == 0)
-            block_partials<WHOLE>(partial + i * num_tiles, rec, sums, kWalkParts, lane);
+            block_partials<WHOLE>(partial + i * num_tiles, rec, sums, lane);
     };
     for (int i = 0; i < n_local; ++i) {
         v4f ga[SB], ca[SB];
@@ -1724,7 +1729,7 @@ __device__ __forceinline__ void server_direct_block(
         if ((lane & 15) == 0) red[li >> 6] = acc;
     }
     __syncthreads();
-    if (wv == 0) block_partials<WHOLE>(partial, rec, red, kSubBlocks, lane);
+    if (wv == 0) block_partials<WHOLE>(partial, rec, red, lane);
 }
 
 __global__ __launch_bounds__(kBlock) void k_server_direct(

@@ -117,3 +117,24 @@ def test_fused_step_rounds_its_scales_as_the_three_calls(dev, numel, n):
         _same(a.worker_scales, b.worker_scales, "worker scales")
         _same(a.server_scales, b.server_scales, "server scales")
     plan.close()
+
+
+@pytest.mark.parametrize("numel,n", [
+    ([5000] * 800, 2),            # whole and mixed blocks, over 1,024 of them: the row walk
+    ([1024] * 2500, 3),
+    ([300] * 400 + [2000] * 100, 5),   # fewer: the packed pass's grid
+])
+def test_worker_scale_does_not_depend_on_the_momentum_form_or_gradient_type(dev, numel, n):
+    import paper_2102_02888_amd as ob
+    plan = ob.Plan(numel, n)
+    z = _knife(plan, dev, len(numel), n)
+    first = None
+    for dtype in (torch.float32, torch.bfloat16, torch.float16):
+        for fp32_m in (False, True):
+            st = _state(plan, dev, worker=z, grad_dtype=dtype)
+            _compress(st, m=st.m if fp32_m else None)
+            torch.cuda.synchronize()
+            if first is None:
+                first = st.worker_scales
+            _same(first, st.worker_scales, "%s, %s momentum" % (dtype, "fp32" if fp32_m else "packed"))
+    plan.close()
