@@ -1663,9 +1663,42 @@ __device__ __forceinline__ void add_decoded(double (&sum)[4], float s, uint32_t 
         sum[c] += __hiloint2double((int)(hi ^ ((~nib << (31 - c)) & 0x80000000u)), lo);
 }
 
+// The sums of squares of the block's tiles from its lanes' sums (red[t]: thread
+// t's 4 elements), in the order of the passes over tiles, so that a scale does
+// not depend on which pass a call takes.  There lane L of a wave has the
+// elements 4L .. 4L + 3 of each sub-block of its tile: for n <= kServerRowBatch
+// it adds the sub-blocks' sums and the wave adds the lanes'; for more workers
+// each sub-block's wave adds its lanes' and the four sums are added in pairs.
+template <bool WHOLE>
+__device__ __forceinline__ void server_direct_partials(const double (&red)[kBlock],
+                                                       const Block &rec, int lim, int lane, int wv,
+                                                       bool split, double *__restrict__ partial)
+{
+    uint32_t rest = WHOLE ? 1u : rec.starts;
+    for (int j = 0; rest != 0; ++j) {
+        const int w0 = __ffs(rest) - 1;
+        rest &= rest - 1;
+        if ((j & (kWavesPerBlock - 1)) != wv) continue;  // the waves take turns
+        const int words = (WHOLE ? kTileWords : rest ? __ffs(rest) - 1 : lim >> 6) - w0;
+        double a[kSubBlocks];
+#pragma unroll
+        for (int b = 0; b < kSubBlocks; ++b)
+            a[b] = 4 * b + (lane >> 4) < words ? red[16 * (w0 + 4 * b) + lane] : 0.0;
+        double s;
+        if (split && words > 4) {
+#pragma unroll
+            for (int b = 0; b < kSubBlocks; ++b) a[b] = wave_sum_dpp(a[b]);
+            s = (a[0] + a[1]) + (a[2] + a[3]);
+        } else {
+            s = wave_sum_dpp(((a[0] + a[1]) + a[2]) + a[3]);
+        }
+        if (lane == 0) partial[rec.tile + j] = s;
+    }
+}
+
 template <bool WHOLE>
 __device__ __forceinline__ void server_direct_block(
-    double (&red)[kTileWords], const Tile *__restrict__ tiles, const Block &rec, int64_t base,
+    double (&red)[kBlock], const Tile *__restrict__ tiles, const Block &rec, int64_t base,
     int lim, int lane, int wv, v4f cv, int n, const uint8_t *__restrict__ bytes,
     int64_t bytes_ld, uint32_t (&first)[kDirectBatch], const float *__restrict__ wscales,
     int64_t scales_ld, float *__restrict__ serr, float sprev,
@@ -1721,15 +1754,9 @@ __device__ __forceinline__ void server_direct_block(
     stb4<WHOLE>(serr, li, valid, zv);
     const uint64_t word = row_sign_word(nib, lane);
     if ((lane & 15) == 0 && in) sbits[li >> 6] = word;
-    if (WHOLE) {
-        acc = wave_sum_dpp(acc);
-        if (lane == 0) red[wv] = acc;
-    } else {
-        acc = row_sum(acc);
-        if ((lane & 15) == 0) red[li >> 6] = acc;
-    }
+    red[threadIdx.x] = acc;
     __syncthreads();
-    if (wv == 0) block_partials<WHOLE>(partial, rec, red, lane);
+    server_direct_partials<WHOLE>(red, rec, lim, lane, wv, n > kServerRowBatch, partial);
 }
 
 __global__ __launch_bounds__(kBlock) void k_server_direct(
@@ -1738,9 +1765,9 @@ __global__ __launch_bounds__(kBlock) void k_server_direct(
     int64_t bits_ld, const float *__restrict__ wscales, int64_t scales_ld, float *__restrict__ serr, const float *__restrict__ sscales,
     uint64_t *__restrict__ sbits, double *__restrict__ partial)
 {
-    __shared__ double red[kTileWords];
+    __shared__ double red[kBlock];
     const int lane = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x >> 6;
+    const int wv = wave_id();
     const int64_t blk = block_base + xcd_block();
     if (blk >= num_blocks) return;  // the whole workgroup
     const int64_t base = blk * kTileElems;

@@ -138,3 +138,32 @@ def test_worker_scale_does_not_depend_on_the_momentum_form_or_gradient_type(dev,
                 first = st.worker_scales
             _same(first, st.worker_scales, "%s, %s momentum" % (dtype, "fp32" if fp32_m else "packed"))
     plan.close()
+
+
+def _mixed(rng, n, tiles):
+    """Tensor sizes whose chunks are one word to a few blocks long."""
+    out = []
+    while sum(-(-d // (64 * n)) > 0 for d in out) * n < tiles:
+        out.append(int(64 * n * rng.choice([0.5, 1, 1, 2, 2, 3, 4, 5, 7, 12, 20])) + int(rng.integers(0, 60)))
+    return out
+
+
+@pytest.mark.parametrize("n", [2, 7, 8, 32, 33, 64, 130])
+def test_server_scale_does_not_depend_on_the_table_mode_or_owned_range(dev, n):
+    """Plans of many short tiles, which the automatic mode gives the owners'
+    pass over blocks when every chunk is owned."""
+    import paper_2102_02888_amd as ob
+    plan = ob.Plan(_mixed(np.random.default_rng(n), n, 9500), n)
+    assert plan.T > 8192 and plan.T >= 3 * ((plan.D + 1023) // 1024)
+    z = _knife(plan, dev, n)[0]
+    got = {}
+    for mode in (ob.SERVER_TABLES_AUTO, ob.SERVER_TABLES_ON, ob.SERVER_TABLES_OFF, "one by one"):
+        plan.set_server_tables(ob.SERVER_TABLES_AUTO if mode == "one by one" else mode)
+        st = _state(plan, dev, server=z, grad_dtype=torch.bfloat16)
+        for j in range(n) if mode == "one by one" else (None,):
+            _reduce(st, *((0, n) if j is None else (j, j + 1)))
+        torch.cuda.synchronize()
+        got[mode] = st.server_scales
+    for mode, s in got.items():
+        _same(got[ob.SERVER_TABLES_ON], s, str(mode))
+    plan.close()
