@@ -128,8 +128,11 @@ int onebit_plan_get_layout(onebit_plan plan, int64_t *tensor_offset,
  * ONEBIT_SERVER_TABLES_AUTO (the default) uses the workspace when the call's
  * segments average 4 or more tiles and its tiles times its groups of 8
  * workers reach 32768; ON uses it whenever the space is there; OFF never.
- * Results are bit-identical either way; the switch exists to compare the two
- * paths.  Not to be changed while a call on the plan is in flight.
+ * Unless ON, a call over all chunks of a plan of more than 8,192 tiles, three or
+ * more (above 128 workers four or five) per 1,024 elements, uses no tables and
+ * adds the workers one by one.  Results are bit-identical in every mode; the
+ * switch exists to compare the paths.  Not to be changed while a call on the
+ * plan is in flight.
  * Errors: EINVAL (null plan, another mode). */
 #define ONEBIT_SERVER_TABLES_OFF 0
 #define ONEBIT_SERVER_TABLES_AUTO 1

@@ -108,17 +108,26 @@ bool server_uses_tables(const onebit_plan_s *p, int32_t begin, int32_t end)
 }
 
 // Whether the chunk owners' call over [begin, end) adds the workers one by one
-// over blocks instead of giving each tile a wave and lookup tables: with every
-// chunk owned, a third of a block or less per tile on average, and more than
-// 8,192 tiles (smaller plans form the workers' scales in the tables' pass).
-// Step, in us, tables / one by one: 2,000 tensors of 64 to 8192 elements (17
-// tiles a block with n = 32, 4.3 with n = 8) 402 / 350, naive 128 / 119; 640
-// tensors up to 2^16 n = 32 (3.6 a block) 497 / 491; 2,000 up to 2^16 n = 8 (2.1 a
-// block) 413 / 419; one flat buffer of 64 million, n = 8 1154 / 1185.
+// over blocks instead of giving each tile a wave (n > 32: a workgroup) and
+// lookup tables: with every chunk owned, more than 8,192 tiles (smaller plans
+// form the workers' scales in the tables' pass) and many tiles in a block of
+// 1,024 elements.  Its time grows with blocks times workers, the other passes'
+// with tiles times workers and a constant part per tile, the larger the more
+// workers a workgroup builds tables for; far above 128 workers the rows that a
+// block reads no longer stay in the caches.
+// Step, us, tables / one by one: 2,000 tensors of 64 to 8192 elements (8.8 tiles
+// a block with n = 32, 4.2 with n = 8) 402 / 350, naive 128 / 119; 640 tensors up
+// to 2^16 n = 32 (2.9 a block) 497 / 491; 2,000 up to 2^16 n = 8 (1.6 a block)
+// 413 / 419; one flat buffer of 64 million, n = 8 1154 / 1185.
+// Owners' call alone: n = 64, 4.2 tiles a block 210 / 81, 12.2 368 / 59; n = 128, 3.4
+// a block 479 / 325, 16 279 / 57; n = 256, 3.4 a block 541 / 552, 5.4 1287 / 850; n =
+// 512, 4.1 a block 1785 / 1648; n = 1024, 4.2 a block 2067 / 1962; n = 2048, 4.4 a
+// block 2643 / 2798, 16 3369 / 1026.
 bool server_direct(const onebit_plan_s *p, int32_t begin, int32_t end)
 {
+    const int64_t per_block = p->n <= 128 ? 3 : p->n <= 1024 ? 4 : 5;
     return begin == 0 && end == p->n && p->server_tables != ONEBIT_SERVER_TABLES_ON &&
-           p->T > 8192 && p->T >= 3 * p->tb.num_blocks;
+           p->T > 8192 && p->T >= per_block * p->tb.num_blocks;
 }
 
 // On small plans the fused step leaves out the two finalize launches: the chunk

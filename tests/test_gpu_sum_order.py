@@ -144,7 +144,8 @@ def _mixed(rng, n, tiles):
     """Tensor sizes whose chunks are one word to a few blocks long."""
     out = []
     while sum(-(-d // (64 * n)) > 0 for d in out) * n < tiles:
-        out.append(int(64 * n * rng.choice([0.5, 1, 1, 2, 2, 3, 4, 5, 7, 12, 20])) + int(rng.integers(0, 60)))
+        words = [0.5, 1, 1, 2, 2, 3, 4, 5, 7, 12, 20] if n <= 128 else [0.5, 1, 2, 2, 3, 5, 8]
+        out.append(int(64 * n * rng.choice(words)) + int(rng.integers(0, 60)))
     return out
 
 
@@ -153,8 +154,8 @@ def test_server_scale_does_not_depend_on_the_table_mode_or_owned_range(dev, n):
     """Plans of many short tiles, which the automatic mode gives the owners'
     pass over blocks when every chunk is owned."""
     import paper_2102_02888_amd as ob
-    plan = ob.Plan(_mixed(np.random.default_rng(n), n, 9500), n)
-    assert plan.T > 8192 and plan.T >= 3 * ((plan.D + 1023) // 1024)
+    plan = ob.Plan(_mixed(np.random.default_rng(n), n, 9500 if n <= 128 else 12_500), n)
+    assert plan.T > 8192 and plan.T >= (3 if n <= 128 else 4) * ((plan.D + 1023) // 1024)
     z = _knife(plan, dev, n)[0]
     got = {}
     for mode in (ob.SERVER_TABLES_AUTO, ob.SERVER_TABLES_ON, ob.SERVER_TABLES_OFF, "one by one"):
