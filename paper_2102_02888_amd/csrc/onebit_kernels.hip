@@ -42,9 +42,8 @@ typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
 // block; its fourth word is the gfx9-family buffer format word.
 constexpr int kStreamLoad = 2;        // nt
 constexpr int kStreamStore = 2 | 16;  // nt, sc1
-// Small plans, whose rows stay in the last-level cache from step to step
-// (rows_cached): loads and stores without nt.
-constexpr int kCachedLoad = 0;
+// Small plans, whose error rows can stay in the last-level cache from step to
+// step (rows_cached): stores without nt.
 constexpr int kCachedStore = 16;      // sc1
 
 // Resource for a wave-uniform base p (a tile's start in some row: every
@@ -116,11 +115,10 @@ typedef uint16_t v4u16 __attribute__((ext_vector_type(4)));
 typedef _Float16 v4f16 __attribute__((ext_vector_type(4)));
 
 // 16-bit gradient elements li..li+3 as fp32.
-template <class G, bool CACHED>
+template <class G>
 __device__ __forceinline__ v4f ldg4(const typename G::T *__restrict__ p, int li)
 {
-    const v2u32 w = __builtin_amdgcn_raw_buffer_load_b64(stream_rsrc(p), li * 2, 0,
-                                                         CACHED ? kCachedLoad : kStreamLoad);
+    const v2u32 w = __builtin_amdgcn_raw_buffer_load_b64(stream_rsrc(p), li * 2, 0, kStreamLoad);
     v4f r;
     if constexpr (__is_same(typename G::T, uint16_t)) {
         const v4u16 h = __builtin_bit_cast(v4u16, w);
@@ -227,23 +225,22 @@ __device__ __forceinline__ Block load_block(const Block *__restrict__ blocks, in
 
 // Loads elements li..li+3 of the block at p; lim = elements of the block
 // inside the padded length (a multiple of 64).  INSIDE: the whole block is.
-template <bool INSIDE, bool CACHED = false>
+template <bool INSIDE>
 __device__ __forceinline__ v4f ldb4(const float *__restrict__ p, int li, int lim)
 {
     if (INSIDE || li < lim)
         return __builtin_bit_cast(
-            v4f, __builtin_amdgcn_raw_buffer_load_b128(stream_rsrc(p), li * 4, 0,
-                                                       CACHED ? kCachedLoad : kStreamLoad));
+            v4f, __builtin_amdgcn_raw_buffer_load_b128(stream_rsrc(p), li * 4, 0, kStreamLoad));
     return v4f{0.f, 0.f, 0.f, 0.f};
 }
 
-template <bool INSIDE, class G, bool CACHED = false>
+template <bool INSIDE, class G>
 __device__ __forceinline__ v4f ldgb4(const typename G::T *__restrict__ p, int li, int lim)
 {
     if constexpr (sizeof(typename G::T) == 4) {
-        return ldb4<INSIDE, CACHED>((const float *)p, li, lim);
+        return ldb4<INSIDE>((const float *)p, li, lim);
     } else {
-        if (INSIDE || li < lim) return ldg4<G, CACHED>(p, li);
+        if (INSIDE || li < lim) return ldg4<G>(p, li);
         return v4f{0.f, 0.f, 0.f, 0.f};
     }
 }
@@ -784,7 +781,7 @@ constexpr int kPassIdleLds = sizeof(typename G::T) == 2 ? idle_lds(10) - 512 : 0
 
 // A wave's loads of its part of one block: the gradient row, the compensated
 // row and the momentum (sign words, or fp32 values).
-template <bool INSIDE, bool PACKED, class G, int SB, bool CACHED>
+template <bool INSIDE, bool PACKED, class G, int SB>
 __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&mv)[SB],
                                             uint64_t (&word)[SB],
                                             const typename G::T *__restrict__ gi,
@@ -800,10 +797,10 @@ __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&
         if (PACKED) {
             if (INSIDE || li < lim) word[b] = m_bits[li >> 6];
         } else {
-            mv[b] = ldb4<INSIDE, CACHED>(m, li, lim);
+            mv[b] = ldb4<INSIDE>(m, li, lim);
         }
-        gv[b] = ldgb4<INSIDE, G, CACHED>(gi, li, lim);
-        cv[b] = ldb4<INSIDE, CACHED>(ei, li, lim);
+        gv[b] = ldgb4<INSIDE, G>(gi, li, lim);
+        cv[b] = ldb4<INSIDE>(ei, li, lim);
     }
 }
 
@@ -954,10 +951,10 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     v4f gv[SB], cv[SB], mv[SB];
     uint64_t word[SB];
     if (lim == kTileElems)
-        worker_load<true, PACKED, G, SB, CACHED>(gv, cv, mv, word, gi, ei, m + base, m_bits + (base >> 6),
+        worker_load<true, PACKED, G, SB>(gv, cv, mv, word, gi, ei, m + base, m_bits + (base >> 6),
                                          wv * SB, lane, lim);
     else
-        worker_load<false, PACKED, G, SB, CACHED>(gv, cv, mv, word, gi, ei, m + base,
+        worker_load<false, PACKED, G, SB>(gv, cv, mv, word, gi, ei, m + base,
                                           m_bits + (base >> 6), wv * SB, lane, lim);
     const Block rec = load_block(blocks, blk);
     scales += i * scales_ld;
@@ -2633,12 +2630,17 @@ hipError_t launch_warmup(const DeviceTables &tb, float *x, float *m, float *v, c
     return hipGetLastError();
 }
 
-// Whether a call's gradient and error rows stay in the 256 MB last-level cache
-// until the next step: up to a quarter of it.  Non-temporal accesses then only
-// push them out.  Step over three states in turn, fp32, us, streamed / cached:
-// 2^20 elements n = 4 (32 MB) 22.8 / 21.6, 5x10^5 n = 16 (64 MB) 29.9 / 28.0,
-// 10^6 n = 8 31.3 / 29.6, 2x10^6 n = 4 37.8 / 36.3; but 10^6 n = 16 (128 MB)
-// 45.6 / 49.2, 4x10^6 n = 4 59.6 / 63.1.
+// Whether a call's gradient and error rows fit a quarter of the 256 MB
+// last-level cache, so that the error rows that it writes can still be there in
+// the next step: they are then stored without nt.  The loads keep nt, since
+// loads without it lose where other work between two steps has filled the
+// cache.  Step, us, both nt / stores without / both without, (a) back to back, (b)
+// after 128 MB of other writes and new gradients, (c) after 1 GB of other
+// writes: 2^20 elements n = 4 (a) 19.9 / 18.6 / 18.6, (b) 24.6 / 24.1 / 24.0, (c)
+// 26.1 / 26.4 / 30.4; 5x10^5 n = 16 (a) 27.2 / 26.3 / 28.2, (b) 31.5 / 30.7 / 30.9,
+// (c) 33.6 / 33.8 / 40.5; 2x10^6 n = 4 (a) 35.1 / 33.9 / 35.7, (b) 39.8 / 38.4 /
+// 38.8, (c) 42.8 / 44.1 / 50.7; 2^20 n = 8, bf16 (a) 26.6 / 24.5 / 24.3, (b) 31.6 /
+// 30.6 / 30.8, (c) 32.9 / 33.1 / 37.4.
 static bool rows_cached(int64_t items, size_t grad_bytes)
 {
     return items * kTileElems * (int64_t)(grad_bytes + 4) <= (int64_t)64 << 20;
