@@ -2345,11 +2345,8 @@ __device__ __forceinline__ void update_sub(const Lane4 &l, int li, v4f xv, v4f v
 // keeps 2 KB of loads in flight instead of 8 KB (a whole block), which the mix
 // of two read streams and one written stream favours: 0.667 -> 0.619 ms on the
 // BERT-Large shape, 1.112 -> 1.033 ms on the 5,000-tensor stress workload
-// (half a tile per wave: 0.640 and 1.070 ms), in one A/B process each.  Six
-// workgroups per CU, held by unused LDS, keep about 12 KB in flight per SIMD:
-// one GPU's share of a BERT-Large step (its own worker row, the update) 1.306
-// ms at eight, 1.293 at six, 1.366 at five in one process; in another 1.321 at
-// eight, 1.320 at six.
+// (half a tile per wave: 0.640 and 1.070 ms), in one A/B process each.  Large
+// plans run seven workgroups per CU, held by unused LDS (launch_update).
 //
 // FORM: the scales are formed here from the chunk owners' partial sums (see
 // wave_scale), which saves the finalize kernel's launch.
@@ -2892,10 +2889,18 @@ hipError_t launch_update(const DeviceTables &tb, const uint64_t *sbits, float *s
                          const double *partial, float *x, float *m_out, const float *v, float lr,
                          float eps, hipStream_t s)
 {
+    // Seven workgroups per CU above 2^24 elements, where memory bounds the pass
+    // and a little less in flight suits its read and write streams; below, x and
+    // v are mostly in the last-level cache and every wave helps.  Update, us, at
+    // eight / seven / six, in one process on the same buffers: 3x10^6 elements
+    // 6.9 / 6.9 / 7.5, 6x10^6 10.5 / 10.8 / 11.8, 10^7 18.4 / 18.7 / 19.4, 1.4x10^7
+    // 26.2 / 26.5 / 27.0, 1.8x10^7 34.5 / 34.0 / 34.0, BERT-Large 606.4 / 602.5 /
+    // 603.4, 5,000 tensors 1002 / 995 / 1007.
+    const size_t lds = tb.num_blocks > 16384 ? idle_lds(7) : 0;
     const auto kernel = partial ? k_update<true> : k_update<false>;
     for (int64_t base = 0; base < tb.num_blocks; base += kMaxLaunchTiles) {
         const int64_t count = launch_piece(tb.num_blocks, base);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(count, 1)), dim3(kBlock), idle_lds(6),
+        hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(count, 1)), dim3(kBlock), lds,
                            s, tb.tiles, tb.blocks, base, base + count, tb.padded_len, tb.segs,
                            partial, sbits, sscales, x, m_out, v, lr, eps);
     }
