@@ -134,13 +134,17 @@ bool server_direct(const onebit_plan_s *p, int32_t begin, int32_t end)
 // owners' pass forms the workers' scales, and the update the owners', from the
 // partial sums of each tile's segment.  A launch costs about 3.3 us of the host
 // and 2 to 5 us of the GPU; forming costs every tile a few dependent loads and
-// its segment's partial sums again.  Measured (fp32, us a step, with both
-// finalize launches / worker scales formed / owners' formed / both): 10^5
-// elements n = 8 32.4 / 29.3 / 29.6 / 25.9; 2^20, n = 4 32.9 / 28.8 / 28.9 /
-// 26.0; 160 tensors up to 2^16, n = 8 46.8 / 44.5 / 45.8 / 43.3; 40 tensors up
-// to 2^20, n = 8 83.4 / 81.2 / 85.3 / 82.7; 2x10^6, n = 16 83.6 / 83.7 / 85.0 /
-// 84.8; 4x10^6, n = 16 148 / 153 / 157 / 162; 160 tensors up to 2^20, n = 4 183 /
-// 186 / 207 / 209.
+// its segment's partial sums again.  Measured (fp32, us a step, in one process
+// on the same buffers: both finalize launches / workers' scales formed / owners'
+// formed / both): 10^5 elements n = 8 21.5 / 18.7 / 18.5 / 14.7; 60 tensors up to
+// 2^18 n = 4 33.6 / 31.3 / 32.1 / 29.6; 160 up to 2^16 n = 8 48.0 / 45.7 / 46.9 /
+// 44.4; 40 up to 2^20 n = 8 (3,458 tiles) 77.4 / 76.0 / 77.5 / 75.1; 30 up to 2^20
+// n = 16 93.3 / 91.9 / 92.6 / 91.0; 200 up to 2^17 n = 8 (4,717 tiles) 88.7 / 86.4 /
+// 88.2 / 85.9; 1,000 up to 2^14 n = 4 (6,310 tiles) 63.2 / 61.2 / 62.4 / 60.4; one flat
+// buffer of 2x10^6, n = 8 51.5 / 51.5 / 50.9 / 51.0, n = 16 82.3 / 82.4 / 81.5 / 81.4;
+// of 3x10^6, n = 16 (184 tiles a segment) 114.9 / 114.9 / 114.7 / 114.7; of 4x10^6,
+// n = 16 (245 tiles) 147.2 / 147.2 / 148.2 / 148.2.
+
 // Worker scales: a tile reads n rows of its segment's partial sums, at most
 // 1,024 on average, and there are at most 8,192 tiles (no lookup tables then).
 bool forms_worker_scales(const onebit_plan_s *p)
@@ -150,12 +154,13 @@ bool forms_worker_scales(const onebit_plan_s *p)
            !server_uses_tables(p, 0, p->n);
 }
 
-// Owners' scales: each of the update's many short waves waits for them, so the
-// plan is a single round of waves, or a few with short segments.
+// Owners' scales: each of the update's many short waves waits for them.  Up to
+// 3,000 tiles, or as many as the workers' where a tile reads at most 64 partial
+// sums on average.
 bool forms_server_scales(const onebit_plan_s *p)
 {
     return p->T > 0 && p->max_seg_tiles <= onebit::kWaveSegTiles &&
-           (p->T <= 1200 || (p->T <= 4096 && p->tile_pairs <= 16 * p->T));
+           (p->T <= 3000 || (p->T <= 8192 && p->tile_pairs <= 64 * p->T));
 }
 
 int check_plan(const onebit_plan_s *p)
