@@ -986,7 +986,8 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
 // loads issued before the previous row's stores (two rows in flight), 4.21 ms
 // without; one sub-block per wave 4.35, four 4.32, workgroups of 8 waves
 // 4.54, of 4 (one sub-block) 4.68, two workgroups per CU 4.45, the packed pass
-// reading m for every worker 4.80.
+// reading m for every worker 4.80.  The kernel's attribute allocates enough
+// registers that a second workgroup does not fit, whatever the code needs.
 // ---------------------------------------------------------------------------
 constexpr int kWalkParts = kWorkerWavesPerBlock;          // waves per block
 constexpr int kWalkSubBlocks = kSubBlocks / kWalkParts;   // sub-blocks per wave
@@ -1051,7 +1052,8 @@ __device__ __forceinline__ void worker_rows_walk(
 }
 
 template <class G>
-__global__ __launch_bounds__(kWalkWaves *kWave) void k_worker_rows(
+__global__ __launch_bounds__(kWalkWaves *kWave)
+    __attribute__((amdgpu_waves_per_eu(kWalkWaves / 4, kWalkWaves / 4))) void k_worker_rows(
     const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t block_base,
     int64_t num_blocks, int64_t padded_len, int64_t num_tiles, const float *__restrict__ m,
     const typename G::T *__restrict__ g, int64_t g_ld, float *__restrict__ err, int64_t err_ld,
