@@ -320,53 +320,114 @@ def test_update_full_size_exact(ob, dev):
     torch.cuda.empty_cache()
 
 
-def test_first_step_over_two_launch_pieces(ob, dev):
-    """The first compression step's kernel (two waves per tile) is launched
-    over at most 2^22 tiles at a time.  One tensor of 2^22 + 3 tiles (a short
-    last tile), n = 1: the step runs as two launches.  The error state starts
-    at zero, so every element's new compensated value must be the first step's
-    z = fl(beta1 m) + fl((1 - beta1) g) (Algorithm 1's momentum step with a
-    zero error); an element processed twice or not at all would differ.  A
-    plain fp32 torch reference checks all 4.3e9 elements, in chunks; the sign
-    words around the boundary between the launches and the segment's scale
-    are checked too.  (The step's update overwrites m with the decoded server
-    message, so the reference uses a copy of m taken before the step.)  Needs
-    about 125 GB of device memory."""
+@pytest.mark.parametrize("n,dtype", [(2, torch.bfloat16), (1, torch.float32)])
+def test_first_step_over_two_launch_pieces(ob, dev, n, dtype):
+    """The first compression step's row walk (k_worker_rows) is launched over at
+    most 2^22 blocks of 1,024 elements at a time; one row takes the packed
+    pass's grid, one workgroup per (row, block), in one launch.  One tensor of
+    2^22 + 3 blocks (the last one short): two rows run the walk as two launches.
+    The error state starts at zero, so every element's new compensated value
+    must be the first step's z = fl(beta1 m) + fl((1 - beta1) g) (Algorithm 1's
+    momentum step with a zero error); an element processed twice or not at all
+    would differ.  A plain fp32 torch reference checks all 4.3e9 elements of
+    every row, in chunks; the sign words around the boundary between the
+    launches and the segments' scales are checked too.  (The step's update
+    overwrites m with the decoded server message, so the reference uses a copy of
+    m taken before the step.)  Needs about 140 GB of device memory."""
     torch.cuda.empty_cache()
     tiles = (1 << 22) + 3
     d = tiles * 1024 - 100
-    plan = ob.Plan([d], 1)
-    assert plan.T == tiles
-    st = ob.State(plan, dev)
+    plan = ob.Plan([d], n)
+    assert (plan.D + 1023) // 1024 == tiles
+    st = ob.State(plan, dev, grad_dtype=dtype)
     gen = torch.Generator(device=dev)
     gen.manual_seed(2102)
     st.m[:d].normal_(0.0, 1e-3, generator=gen)
-    st.grads[0, :d].normal_(0.0, 1e-2, generator=gen)
+    for i in range(n):
+        st.grads[i, :d].normal_(0.0, 1e-2, generator=gen)
     st.v[:d].uniform_(1e-8, 1e-6, generator=gen)
     beta1, lr, eps = 0.9, 1e-4, 1e-8
     m0 = st.m.clone()
-    st.step(lr, beta1, eps)  # first compression step: fp32 momentum, k_worker_rows
+    st.step(lr, beta1, eps)  # first compression step: fp32 momentum
     torch.cuda.synchronize()
     b1 = torch.tensor(beta1, dtype=torch.float32, device=dev)
     omb1 = torch.tensor(1.0, dtype=torch.float32, device=dev) - b1
     chunk = 1 << 28
-    sq = torch.zeros((), dtype=torch.float64, device=dev)
-    for c0 in range(0, plan.D, chunk):
-        c1 = min(plan.D, c0 + chunk)
-        z = b1 * m0[c0:c1] + omb1 * st.grads[0, c0:c1]
-        got = st.worker_err[0, c0:c1]
-        bad = int((got != z).sum())
-        assert bad == 0, "%d elements of [%d, %d) differ from the first step's z" % (bad, c0, c1)
-        sq += (z.double() ** 2).sum()
-        del z, got
-    # sign words of the tiles on both sides of the boundary between the launches
     t0, t1 = (1 << 22) - 2, (1 << 22) + 2
-    zb = (b1 * m0[t0 * 1024:t1 * 1024] + omb1 * st.grads[0, t0 * 1024:t1 * 1024]).cpu().numpy()
-    want = np.packbits((zb >= 0).reshape(-1, 64)[:, ::-1], axis=1).view(">u8").ravel()
-    got_w = host(st.worker_bits[0, t0 * 16:t1 * 16]).view(np.uint64)
-    np.testing.assert_array_equal(got_w, want.astype(np.uint64))
-    scale = float(np.sqrt(float(sq) / d).astype(np.float32))
-    assert abs(float(st.worker_scales[0, 0]) - scale) <= 1e-6 * scale
+    for i in range(n):
+        for q, (s0, s1) in enumerate(zip(plan.seg_begin.tolist(), plan.seg_end.tolist())):
+            sq = torch.zeros((), dtype=torch.float64, device=dev)
+            for c0 in range(s0, s1, chunk):
+                c1 = min(s1, c0 + chunk)
+                z = b1 * m0[c0:c1] + omb1 * st.grads[i, c0:c1].float()
+                got = st.worker_err[i, c0:c1]
+                bad = int((got != z).sum())
+                assert bad == 0, "row %d: %d elements of [%d, %d) differ from the first step's z" \
+                    % (i, bad, c0, c1)
+                sq += (z.double() ** 2).sum()
+                del z, got
+            scale = float(np.sqrt(float(sq) / (s1 - s0)).astype(np.float32))
+            assert abs(float(st.worker_scales[i, q]) - scale) <= 1e-6 * scale
+        # sign words on both sides of the boundary between the walk's launches
+        zb = (b1 * m0[t0 * 1024:t1 * 1024]
+              + omb1 * st.grads[i, t0 * 1024:t1 * 1024].float()).cpu().numpy()
+        want = np.packbits((zb >= 0).reshape(-1, 64)[:, ::-1], axis=1).view(">u8").ravel()
+        got_w = host(st.worker_bits[i, t0 * 16:t1 * 16]).view(np.uint64)
+        np.testing.assert_array_equal(got_w, want.astype(np.uint64))
     del st, m0
+    plan.close()
+    torch.cuda.empty_cache()
+
+
+def test_packed_worker_pass_over_two_launch_pieces(ob, dev):
+    """The packed worker pass is launched over at most 3 * 2^22 (row, block)
+    items at a time.  The BERT-Large length with 40 rows of bf16 gradients has
+    13.05 million: the second launch begins inside row 38.  The error state
+    starts at zero, so every new compensated value must be z = fl(beta1 m) +
+    fl((1 - beta1) g) with m decoded from the sign words and scales; every
+    element, sign word and scale of the first rows and of those from 37 on is
+    checked against a plain torch reference, and the rest by their sums of
+    squares.  Needs about 90 GB of device memory."""
+    from paper_2102_02888_amd.onebit import paired_rows
+    torch.cuda.empty_cache()
+    d, n = 334_088_192, 40
+    plan = ob.Plan([d], n)
+    D, blocks = plan.D, (plan.D + 1023) // 1024
+    piece = 3 << 22
+    assert piece < n * blocks and 38 * blocks < piece < 39 * blocks
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(40)
+    grads, err = paired_rows(n, D, torch.bfloat16, dev)
+    for i in range(n):
+        grads[i].normal_(0.0, 1e-2, generator=gen)
+    m_bits = torch.randint(-(1 << 62), 1 << 62, (plan.W,), dtype=torch.int64, device=dev,
+                           generator=gen)
+    m_scales = torch.empty(plan.S, device=dev).log_normal_(-7, 0.3, generator=gen)
+    bits = torch.zeros((n, plan.W), dtype=torch.int64, device=dev)
+    scales = torch.zeros((n, plan.S), device=dev)
+    beta1 = 0.9
+    ob.onebit_worker_compress(plan, None, grads, err, bits, scales, beta1, plan.workspace(dev),
+                              m_bits=m_bits, m_scales=m_scales)
+    torch.cuda.synchronize()
+    m = torch.empty(D, device=dev)
+    ob.onebit_decode(plan, m_bits, m_scales, m)
+    b1 = torch.tensor(beta1, dtype=torch.float32, device=dev)
+    omb1 = torch.tensor(1.0, dtype=torch.float32, device=dev) - b1
+    m.mul_(b1)
+    shift = torch.arange(64, device=dev)
+    for i in range(n):
+        full = i in (0, 1, 37, 38, 39)
+        for q, (s0, s1) in enumerate(zip(plan.seg_begin.tolist(), plan.seg_end.tolist())):
+            z = err[i, s0:s1]
+            if full:
+                want = m[s0:s1] + omb1 * grads[i, s0:s1].float()
+                bad = int((z != want).sum())
+                assert bad == 0, "row %d, segment %d: %d elements differ" % (i, q, bad)
+                words = bits[i, s0 // 64:(s1 + 63) // 64]
+                sign = ((words[:, None] >> shift) & 1).view(-1)[:s1 - s0]
+                assert bool((sign == (want >= 0)).all()), "row %d, segment %d: signs" % (i, q)
+            scale = float((z.double() ** 2).mean().sqrt().float())
+            assert abs(float(scales[i, q]) - scale) <= 1e-6 * scale and scale > 0, (i, q)
+    del grads, err, bits, m
     plan.close()
     torch.cuda.empty_cache()
