@@ -19,25 +19,45 @@ def _rms(z, plan):
     return s
 
 
-@pytest.mark.parametrize("big,small,n", [
-    (3000, 50, 2),        # at most 4 tiles: one lane
-    (40_000, 3, 2),       # 20 tiles, few segments: a wave
-    (40_000, 1100, 2),    # 20 tiles, over 4,096 pairs: 8 lanes
-    (150_000, 1100, 2),   # 74 tiles: 16 lanes
-    (600_000, 3, 2),      # 293 tiles: a workgroup
-    (5000, 70, 33),       # n > 32
+def _lanes(plan, segments):
+    """Lanes per segment of a finalize launch over that many (row, segment)
+    pairs, the launch rule's line."""
+    tiles = [-(-int(e) // 1024) - int(b) // 1024 if e > b else 0
+             for b, e in zip(plan.seg_begin, plan.seg_end)]
+    longest = max(tiles)
+    if longest > 256:
+        return 256
+    if longest > 4 and segments <= 4096:
+        return 64
+    return 16 if longest > 64 else 8 if longest > 4 else 1
+
+
+# lanes: of the workers' call, of all owners' call, of one owner's
+@pytest.mark.parametrize("big,small,n,lanes", [
+    (3000, 50, 2, (1, 1, 1)),            # at most 3 tiles
+    (40_000, 3, 2, (64, 64, 64)),        # 21 tiles, few segments
+    (40_000, 2200, 2, (8, 8, 64)),       # 21 tiles, 8,808, 4,404 and 2,202 segments
+    (150_000, 2200, 2, (16, 16, 64)),    # 74 tiles
+    (600_000, 3, 2, (256, 256, 256)),    # 294 tiles
+    (5000, 70, 33, (1, 1, 1)),           # n > 32
 ])
-def test_scales_of_every_lane_count(dev, big, small, n):
+def test_scales_of_every_lane_count(dev, big, small, n, lanes):
+    """Through the separate calls, which always finalize (the fused step forms
+    the scales of small plans in its passes)."""
     import paper_2102_02888_amd as ob
     plan = ob.Plan([100] * (small // 2) + [big, 0] + [300] * (small - small // 2), n)
+    assert lanes == tuple(_lanes(plan, k) for k in (plan.S * n, plan.S, plan.K))
     st = ob.State(plan, dev)
     g = torch.Generator(device=dev)
     g.manual_seed(big + n)
     for t in (st.grads, st.m, st.x):
         t.normal_(generator=g)
-    st.v.fill_(1.0)
-    for _ in range(2):
-        st.step(1e-3, 0.9, 1e-8)
+    for t in (st.worker_scales, st.server_scales):
+        t.fill_(3.0)   # a scale that is not written would show
+    ob.onebit_worker_compress(plan, st.m, st.grads, st.worker_err, st.worker_bits,
+                              st.worker_scales, 0.9, st.workspace)
+    ob.onebit_server_reduce_compress(plan, 0, n, st.worker_bits, st.worker_scales, st.server_err,
+                                     st.server_bits, st.server_scales, st.workspace)
     torch.cuda.synchronize()
     for i in range(n):
         check_scales("worker %d" % i, host(st.worker_scales[i]), _rms(host(st.worker_err[i]), plan))
@@ -58,9 +78,11 @@ def test_scales_of_every_lane_count(dev, big, small, n):
     ([1 << 20], 3),                                   # 342 tiles: neither
     ([0, 0, 100, 0, 5000, 64, 0], 32),                # empty segments before, between, after
     ([300] * 40 + [0] + [4000] * 30, 7),              # mixed blocks, both formed
-    ([2000 * 1024 + 5], 16),                          # 125 tiles, over 1,200: neither owners'
-    ([65_000] * 50, 8),                               # owners' from few tiles a segment
-    ([1_000_000, 70_000], 8),                         # workers' alone
+    ([2000 * 1024 + 5], 16),                          # 125 tiles: owners' alone
+    ([4_000_000], 16),                                # 245 tiles, over 3,000: neither
+    ([65_000] * 50, 8),                               # over 3,000, few tiles a segment: both
+    ([1_000_000, 70_000], 8),                         # 123 tiles: both
+    ([1_000_000] * 4, 4),                             # 245 tiles, over 3,000: workers' alone
     ([129 * 64], 33),                                 # n > 32: owners' alone
     ([1], 1),
 ])
