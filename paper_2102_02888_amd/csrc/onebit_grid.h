@@ -34,16 +34,16 @@ constexpr int kWorkerRowTiles = kRowWaves / kWorkerWavesPerBlock;
 constexpr int kXcds = 8;
 
 // Plans keep the tile count below 2^25, so a grid of one wave per tile stays
-// far below the 2^32 work-item limit.  Kernels over larger counts cap their
-// grid at kMaxGridBlocks and stride, or are launched in pieces: at most
-// kMaxLaunchTiles blocks, tiles or table-sharing workgroups of up to 256
-// threads at a time (2^30 work-items), and at most kMaxPassItems (row, block)
-// items of the worker pass, one workgroup of up to 256 threads each, so that a
+// far below the 2^32 work-item limit.  The finalize kernel caps its grid at
+// kMaxGridBlocks and strides.  All others launch one workgroup (or wave) for each
+// piece of work, in as many launches as it takes: at most kMaxLaunchTiles
+// blocks, tiles or table-sharing workgroups of up to 256 threads at a time (2^30
+// work-items), and at most kMaxPassItems (row, block) items of the worker pass
+// and the explicit errors, one workgroup of up to 256 threads each, so that a
 // BERT-Large-sized pass (n = 32) is one launch.
 constexpr int64_t kMaxGridBlocks = (int64_t)1 << 22;
-constexpr int64_t kMaxWorkerGridBlocks = (int64_t)1 << 24;
 constexpr int64_t kMaxPassItems = (int64_t)3 << 22;
-static_assert(kMaxPassItems <= kMaxWorkerGridBlocks, "a piece fits the worker grid");
+static_assert(kMaxPassItems * kBlock < ((int64_t)1 << 32), "work-items of one launch");
 constexpr int64_t kMaxLaunchTiles = (int64_t)1 << 22;
 
 // Tiles (or workgroups) of the launch that starts at base, of total.
@@ -110,36 +110,6 @@ ONEBIT_HD inline FastDiv fast_div(int64_t d)
 ONEBIT_HD inline int64_t fast_quotient(int64_t x, FastDiv f)
 {
     return (int64_t)(((uint64_t)x * f.mul) >> f.shift);
-}
-
-// Worker pass: items [0, num_items) of a launch are cut into kXcds contiguous
-// ranges and XCD x walks range x with its grid / kXcds blocks; a grid smaller than the
-// item count strides within the range.  Physical block b (all its waves
-// together) takes items first, first + stride, ... below end.
-struct ItemWalk {
-    int64_t first;
-    int64_t end;
-    int64_t stride;
-};
-
-ONEBIT_HD inline ItemWalk xcd_item_walk(int64_t b, int64_t grid, int64_t num_items)
-{
-    const int64_t per_xcd = (num_items + kXcds - 1) / kXcds;
-    const int64_t begin = (b % kXcds) * per_xcd;
-    ItemWalk r;
-    r.first = begin + b / kXcds;
-    r.end = begin + per_xcd < num_items ? begin + per_xcd : num_items;
-    r.stride = grid / kXcds;
-    return r;
-}
-
-// Worker grid: one workgroup per item, at most max_blocks blocks, rounded up
-// to a multiple of kXcds.
-ONEBIT_HD inline int64_t worker_grid(int64_t items, int64_t max_blocks)
-{
-    int64_t blocks = items;
-    if (blocks > max_blocks) blocks = max_blocks;
-    return (blocks + kXcds - 1) / kXcds * kXcds;
 }
 
 }  // namespace onebit

@@ -938,9 +938,9 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x >> 6;
     // each XCD takes one contiguous eighth of the launch's items, one per workgroup
-    const ItemWalk walk = xcd_item_walk(blockIdx.x, gridDim.x, num_items);
-    if (walk.first >= walk.end) return;  // the whole workgroup
-    const int64_t item = item_base + walk.first;
+    const int64_t at = xcd_block();
+    if (at >= num_items) return;  // the whole workgroup
+    const int64_t item = item_base + at;
     const int64_t i = fast_quotient(item, by_blocks);
     const int64_t blk = item - i * num_blocks;
     const int64_t base = blk * kTileElems;
@@ -2439,9 +2439,9 @@ __global__ __launch_bounds__(kBlock) void k_materialize(
     int zero_padding, int64_t item_base, int64_t num_items)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const ItemWalk walk = xcd_item_walk(blockIdx.x, gridDim.x, num_items);
-    if (walk.first >= walk.end) return;
-    const int64_t item = item_base + walk.first;
+    const int64_t at = xcd_block();
+    if (at >= num_items) return;
+    const int64_t item = item_base + at;
     const int64_t r = fast_quotient(item, by_blocks);
     const int64_t blk = item - r * num_blocks;
     const int64_t base = blk * kTileElems;
@@ -2658,7 +2658,7 @@ static void launch_worker_items(const DeviceTables &tb, int64_t num_tiles, const
                             : k_worker_pass<PACKED, G, false>;
     for (int64_t base = 0; base < items; base += kMaxPassItems) {
         const int64_t count = std::min(items - base, kMaxPassItems);
-        hipLaunchKernelGGL(kernel, dim3((unsigned)worker_grid(count, kMaxPassItems)),
+        hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(count, 1)),
                            dim3(kWave * kPassWaves<G>), kPassIdleLds<G>, s, tb.tiles, tb.blocks,
                            tb.num_blocks, fast_div(tb.num_blocks), tb.padded_len, num_tiles, m,
                            m_bits, m_scales, (const typename G::T *)g, g_ld, err, err_ld, scales,
@@ -2916,7 +2916,7 @@ hipError_t launch_materialize(const DeviceTables &tb, int rows, const float *err
     const int64_t items = (int64_t)rows * tb.num_blocks;
     for (int64_t base = 0; base < items; base += kMaxPassItems) {
         const int64_t count = std::min(items - base, kMaxPassItems);
-        hipLaunchKernelGGL(k_materialize, dim3((unsigned)worker_grid(count, kMaxPassItems)),
+        hipLaunchKernelGGL(k_materialize, dim3((unsigned)xcd_grid(count, 1)),
                            dim3(kBlock), 0, s, tb.tiles, tb.blocks, tb.num_blocks,
                            fast_div(tb.num_blocks), tb.padded_len, err, err_ld, scales, scales_ld,
                            out, out_ld, zero_padding, base, count);

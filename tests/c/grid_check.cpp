@@ -1,7 +1,7 @@
 // Enumerates launches of the tile kernels on the host, with the same grid
-// functions the kernels and their launchers use, and checks that every tile
-// (one wave per tile) or worker item (XCD-contiguous walk, possibly strided)
-// is taken by exactly one wave.  Exit status 0 when every case passes.
+// functions the kernels and their launchers use, and checks that every tile,
+// block or (row, block) item is taken by exactly one wave or workgroup.  Exit
+// status 0 when every case passes.
 #include "onebit_grid.h"
 
 #include <cstdio>
@@ -76,27 +76,6 @@ static void check_server_blocks(const std::vector<int64_t> &counts, int64_t base
     }
     for (int64_t t = 0; t < total; ++t)
         if (seen[(size_t)t] != 1) { fail("tile taken other than once", t, seen[(size_t)t]); break; }
-}
-
-// The worker pass: items walked per XCD, one workgroup per item, with a grid
-// capped at max_blocks.
-static void check_worker(int64_t items, int64_t max_blocks)
-{
-    ++cases;
-    const int64_t grid = worker_grid(items, max_blocks);
-    if (grid % kXcds) fail("worker grid not a multiple of the XCD count", items, grid);
-    if (grid > max_blocks + kXcds - 1) fail("worker grid above its cap", items, grid);
-    std::vector<unsigned char> seen((size_t)items, 0);
-    for (int64_t b = 0; b < grid; ++b) {
-        const ItemWalk walk = xcd_item_walk(b, grid, items);
-        if (walk.stride <= 0) { fail("non-positive stride", items, grid); return; }
-        for (int64_t i = walk.first; i < walk.end; i += walk.stride) {
-            if (i < 0 || i >= items) { fail("item out of range", i, items); break; }
-            if (seen[(size_t)i]++) fail("item taken twice", i, items);
-        }
-    }
-    for (int64_t i = 0; i < items; ++i)
-        if (!seen[(size_t)i]) { fail("item not taken", i, items); break; }
 }
 
 // The first compression step's launches: pieces of at most kMaxLaunchTiles
@@ -177,18 +156,12 @@ int main()
         check_server_blocks({9, 5, 1, 2}, (1LL << 25) - 17);
     }
 
-    for (int64_t items = 1; items <= 700; ++items)
-        for (int64_t cap : {1LL, 3LL, 8LL, 9LL, 24LL, 64LL, (long long)kMaxWorkerGridBlocks})
-            check_worker(items, cap);
-    // BERT-Large, n = 32: one item per wave under the real cap, and strided
-    // walks under smaller caps (including the former 2^22-block cap)
-    const int64_t bert = 32LL * 326288;
-    for (int64_t cap : {(long long)kMaxWorkerGridBlocks, (long long)kMaxGridBlocks, 1000003LL, 4096LL})
-        check_worker(bert, cap);
-    // item counts whose eighths are ragged
-    for (int64_t items : {8LL * 1000 + 7, 8LL * 1000 + 1, 123457LL})
-        for (int64_t cap : {5LL, 40LL, 1000LL})
-            check_worker(items, cap);
+    // the worker pass: one workgroup per (row, block) item; BERT-Large, n = 32,
+    // the largest launch, and counts whose eighths are ragged
+    for (int64_t items = 1; items <= 700; ++items) check_tiles(items, 1);
+    for (int64_t items : {32LL * 326288, (long long)kMaxPassItems, 8LL * 1000 + 7, 8LL * 1000 + 1,
+                          123457LL})
+        check_tiles(items, 1);
 
     if (failures) {
         std::printf("grid_check: %d failure(s) in %ld cases\n", failures, cases);

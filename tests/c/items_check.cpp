@@ -26,11 +26,11 @@ static void check_pieces(int64_t rows, int64_t blocks, int64_t piece)
     std::vector<unsigned char> seen((size_t)items, 0);
     for (int64_t base = 0; base < items; base += piece) {
         const int64_t count = items - base < piece ? items - base : piece;
-        const int64_t grid = worker_grid(count, piece);
+        const int64_t grid = xcd_grid(count, 1);
         for (int64_t b = 0; b < grid; ++b) {
-            const ItemWalk walk = xcd_item_walk(b, grid, count);
-            if (walk.first >= walk.end) continue;
-            const int64_t item = base + walk.first;
+            const int64_t at = xcd_block_of(b, grid);
+            if (at >= count) continue;
+            const int64_t item = base + at;
             const int64_t i = fast_quotient(item, by), blk = item - i * blocks;
             if (i < 0 || i >= rows || blk < 0 || blk >= blocks || seen[(size_t)item]++)
                 if (failures++ < 20) std::printf("FAIL item %lld\n", (long long)item);

@@ -1,7 +1,6 @@
 """Host check of the kernels' launch shapes: tests/c/grid_check.cpp includes
 the same grid header as the kernels (paper_2102_02888_amd/csrc/onebit_grid.h)
-and enumerates whole launches, including strided worker walks that no
-workload here is large enough to reach on the GPU."""
+and enumerates whole launches, up to sizes that no GPU test reaches."""
 import os
 import shutil
 import subprocess
@@ -36,10 +35,11 @@ def test_every_row_and_block_of_the_worker_pass_is_taken_once(tmp_path):
 
 
 def test_parity_cases_reach_every_partial_tile_shape():
-    """The packed worker pass splits each tile between two waves (sub-blocks
-    0-1 and 2-3), so a segment's last tile can end inside wave 0's first
-    sub-block (<= 256 elements), inside its second (257-512, wave 1 idle) or
-    in wave 1's half (> 512).  The GPU parity cases must hold all three."""
+    """A wave of the passes over blocks takes one 256-element sub-block of a
+    block, or two of them, so a segment's last tile can end inside the first
+    sub-block, inside the second (the second wave or half of a wave's part) or
+    in the block's second half (the wave pairs' other wave).  The GPU parity
+    cases must hold all three."""
     import oracle
     from test_gpu_parity import CASES
     kinds = set()
