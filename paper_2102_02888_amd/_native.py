@@ -7,7 +7,7 @@ binding fails loudly.  Build it with ``python -m paper_2102_02888_amd.build``
 import ctypes
 import os
 
-from .build import ARGS as ARGS_PATH, LIB as LIB_PATH
+from .build import LIB as LIB_PATH, args_path
 
 _vp = ctypes.c_void_p
 _i64 = ctypes.c_int64
@@ -81,10 +81,11 @@ def args_module():
     """The binding's native argument checks (csrc/binding_args.cpp)."""
     import importlib.machinery
     import importlib.util
-    if not os.path.exists(ARGS_PATH):
-        raise ImportError("onebit_args.so is not built (%s); run "
-                          "`python -m paper_2102_02888_amd.build`" % ARGS_PATH)
-    loader = importlib.machinery.ExtensionFileLoader("onebit_args", ARGS_PATH)
+    path = args_path()
+    if not os.path.exists(path):
+        raise ImportError("the binding's argument checks are not built for this torch and "
+                          "Python (%s); run `python -m paper_2102_02888_amd.build`" % path)
+    loader = importlib.machinery.ExtensionFileLoader("onebit_args", path)
     module = importlib.util.module_from_spec(
         importlib.util.spec_from_loader("onebit_args", loader))
     loader.exec_module(module)

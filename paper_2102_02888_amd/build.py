@@ -1,16 +1,16 @@
 """Builds libonebit.so (the gfx950 HIP kernels and the C ABI) in-tree, the
-binding's native argument checks lib/onebit_args.so, and the HBM streaming
-probe's own library lib/libhbmprobe.so."""
+binding's native argument checks (args_path()), and the HBM streaming probe's
+own library lib/libhbmprobe.so."""
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("onebit_kernels.hip", "onebit_abi.hip")]
 LIB = os.path.join(HERE, "lib", "libonebit.so")
 ARGS_SOURCE = os.path.join(HERE, "csrc", "binding_args.cpp")
-ARGS = os.path.join(HERE, "lib", "onebit_args.so")
 PROBE_SOURCE = os.path.join(HERE, "csrc", "hbm_probe.hip")
 PROBE = os.path.join(HERE, "lib", "libhbmprobe.so")
 
@@ -23,6 +23,15 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I", os.path.join(ROOT, "include"),
 ]
+
+
+def args_path() -> str:
+    """The argument checks' library for this torch and this Python, whose
+    interfaces it is compiled against: both are in its name, so that another
+    torch or Python asks for a build of its own instead of loading this one."""
+    import torch
+    return os.path.join(HERE, "lib", "onebit_args-torch%s%s"
+                        % (torch.__version__, sysconfig.get_config_var("EXT_SUFFIX")))
 
 
 def _compile(compiler, flags, sources, target, verbose, libs=()):
@@ -45,8 +54,6 @@ def _compile(compiler, flags, sources, target, verbose, libs=()):
 
 def _args_flags():
     """Host compiler flags and libraries for an extension against torch."""
-    import sysconfig
-
     import torch
     from torch.utils import cpp_extension
     flags = ["-O2", "-std=c++17", "-fPIC", "-shared",
@@ -60,7 +67,7 @@ def _args_flags():
 def build(verbose: bool = False) -> str:
     _compile("hipcc", HIPCC_FLAGS, SOURCES, LIB, verbose)
     flags, libs = _args_flags()
-    _compile("g++", flags, [ARGS_SOURCE], ARGS, verbose, libs)
+    _compile("g++", flags, [ARGS_SOURCE], args_path(), verbose, libs)
     _compile("hipcc", HIPCC_FLAGS, [PROBE_SOURCE], PROBE, verbose)
     return LIB
 

@@ -1,7 +1,8 @@
 // Argument checks of the Python binding, in native code: the fused step passes
 // 13 tensors, and type, device, layout and size checks of one tensor through
 // Python attributes cost about as much as a kernel launch's third.  Host code
-// only; built against torch's headers into lib/onebit_args.so.
+// only; built against torch's headers, for one torch and Python (build.py's
+// args_path).
 //
 //   pointer(tensor, dtype, cols, rows, cuda) -> int
 //

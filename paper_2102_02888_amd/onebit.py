@@ -22,10 +22,17 @@ __all__ = [
 ]
 
 
+# The current stream's handle without building a Stream object; not part of
+# torch's public interface, so a torch without it takes the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     """HIP stream handle of a torch stream (default: torch's current one)."""
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 

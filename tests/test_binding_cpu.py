@@ -1,4 +1,4 @@
-"""Host-side logic of the Python binding (no GPU): the per-chunk word ranges
+"""Host-side logic of the Python binding (no GPU, but for the last test): the per-chunk word ranges
 that size a chunk owners' call, against brute force, and their per-call cost
 on the 5,000-tensor stress layout; the paired gradient and error rows that
 State allocates."""
@@ -123,3 +123,34 @@ def test_a_failed_check_is_named():
         _ptr(torch.zeros(4, dtype=torch.float64), f, "m")
     with pytest.raises(ValueError, match="m must be a GPU tensor"):
         _ptr(torch.zeros(4), f, "m", 4)
+
+
+def test_argument_checks_are_named_after_the_torch_and_python_they_are_built_for(monkeypatch):
+    import sysconfig
+
+    from paper_2102_02888_amd import _native, build
+    name = build.args_path()
+    assert torch.__version__ in name and name.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(torch, "__version__", "0.0.0+other")
+    assert build.args_path() != name
+    with pytest.raises(ImportError, match="not built for this torch and Python"):
+        _native.args_module()
+
+
+def test_current_stream_without_torchs_private_function(monkeypatch):
+    from paper_2102_02888_amd import onebit
+
+    class Stream:
+        cuda_stream = 1234
+    monkeypatch.setattr(onebit, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", Stream)
+    assert onebit._stream(None) == 1234
+    assert onebit._stream(Stream()) == 1234
+
+
+@pytest.mark.gpu
+def test_current_stream_is_torchs():
+    from paper_2102_02888_amd import onebit
+    for s in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(s):
+            assert onebit._stream(None) == onebit._stream(s) == torch.cuda.current_stream().cuda_stream
