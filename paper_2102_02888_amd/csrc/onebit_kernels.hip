@@ -42,8 +42,9 @@ typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
 // block; its fourth word is the gfx9-family buffer format word.
 constexpr int kStreamLoad = 2;        // nt
 constexpr int kStreamStore = 2 | 16;  // nt, sc1
-// Small plans, whose error rows can stay in the last-level cache from step to
-// step (rows_cached): stores without nt.
+// Small plans, whose rows can stay in the caches (row_caching): stores, and of
+// the smallest ones gradient loads, without nt.
+constexpr int kCachedLoad = 0;
 constexpr int kCachedStore = 16;      // sc1
 
 // Resource for a wave-uniform base p (a tile's start in some row: every
@@ -115,10 +116,10 @@ typedef uint16_t v4u16 __attribute__((ext_vector_type(4)));
 typedef _Float16 v4f16 __attribute__((ext_vector_type(4)));
 
 // 16-bit gradient elements li..li+3 as fp32.
-template <class G>
+template <class G, int POLICY>
 __device__ __forceinline__ v4f ldg4(const typename G::T *__restrict__ p, int li)
 {
-    const v2u32 w = __builtin_amdgcn_raw_buffer_load_b64(stream_rsrc(p), li * 2, 0, kStreamLoad);
+    const v2u32 w = __builtin_amdgcn_raw_buffer_load_b64(stream_rsrc(p), li * 2, 0, POLICY);
     v4f r;
     if constexpr (__is_same(typename G::T, uint16_t)) {
         const v4u16 h = __builtin_bit_cast(v4u16, w);
@@ -225,22 +226,22 @@ __device__ __forceinline__ Block load_block(const Block *__restrict__ blocks, in
 
 // Loads elements li..li+3 of the block at p; lim = elements of the block
 // inside the padded length (a multiple of 64).  INSIDE: the whole block is.
-template <bool INSIDE>
+template <bool INSIDE, int POLICY = kStreamLoad>
 __device__ __forceinline__ v4f ldb4(const float *__restrict__ p, int li, int lim)
 {
     if (INSIDE || li < lim)
         return __builtin_bit_cast(
-            v4f, __builtin_amdgcn_raw_buffer_load_b128(stream_rsrc(p), li * 4, 0, kStreamLoad));
+            v4f, __builtin_amdgcn_raw_buffer_load_b128(stream_rsrc(p), li * 4, 0, POLICY));
     return v4f{0.f, 0.f, 0.f, 0.f};
 }
 
-template <bool INSIDE, class G>
+template <bool INSIDE, class G, int POLICY = kStreamLoad>
 __device__ __forceinline__ v4f ldgb4(const typename G::T *__restrict__ p, int li, int lim)
 {
     if constexpr (sizeof(typename G::T) == 4) {
-        return ldb4<INSIDE>((const float *)p, li, lim);
+        return ldb4<INSIDE, POLICY>((const float *)p, li, lim);
     } else {
-        if (INSIDE || li < lim) return ldg4<G>(p, li);
+        if (INSIDE || li < lim) return ldg4<G, POLICY>(p, li);
         return v4f{0.f, 0.f, 0.f, 0.f};
     }
 }
@@ -781,7 +782,7 @@ constexpr int kPassIdleLds = sizeof(typename G::T) == 2 ? idle_lds(10) - 512 : 0
 
 // A wave's loads of its part of one block: the gradient row, the compensated
 // row and the momentum (sign words, or fp32 values).
-template <bool INSIDE, bool PACKED, class G, int SB>
+template <bool INSIDE, bool PACKED, class G, int SB, int CACHE>
 __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&mv)[SB],
                                             uint64_t (&word)[SB],
                                             const typename G::T *__restrict__ gi,
@@ -799,7 +800,7 @@ __device__ __forceinline__ void worker_load(v4f (&gv)[SB], v4f (&cv)[SB], v4f (&
         } else {
             mv[b] = ldb4<INSIDE>(m, li, lim);
         }
-        gv[b] = ldgb4<INSIDE, G>(gi, li, lim);
+        gv[b] = ldgb4<INSIDE, G, CACHE == 2 ? kCachedLoad : kStreamLoad>(gi, li, lim);
         cv[b] = ldb4<INSIDE>(ei, li, lim);
     }
 }
@@ -922,8 +923,9 @@ __device__ __forceinline__ void worker_block(
 
 // PACKED: m_{t-1} is the previous step's gathered server message, decoded
 // from its sign words and segment scale (+-scale, exactly the fp32 value the
-// update would have stored), so no fp32 momentum buffer is read.
-template <bool PACKED, class G, bool CACHED>
+// update would have stored), so no fp32 momentum buffer is read.  CACHE: see
+// row_caching.
+template <bool PACKED, class G, int CACHE>
 __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     const Tile *__restrict__ tiles, const Block *__restrict__ blocks, int64_t num_blocks,
     FastDiv by_blocks, int64_t padded_len, int64_t num_tiles, const float *__restrict__ m,
@@ -951,11 +953,11 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     v4f gv[SB], cv[SB], mv[SB];
     uint64_t word[SB];
     if (lim == kTileElems)
-        worker_load<true, PACKED, G, SB>(gv, cv, mv, word, gi, ei, m + base, m_bits + (base >> 6),
-                                         wv * SB, lane, lim);
+        worker_load<true, PACKED, G, SB, CACHE>(gv, cv, mv, word, gi, ei, m + base,
+                                                m_bits + (base >> 6), wv * SB, lane, lim);
     else
-        worker_load<false, PACKED, G, SB>(gv, cv, mv, word, gi, ei, m + base,
-                                          m_bits + (base >> 6), wv * SB, lane, lim);
+        worker_load<false, PACKED, G, SB, CACHE>(gv, cv, mv, word, gi, ei, m + base,
+                                                 m_bits + (base >> 6), wv * SB, lane, lim);
     const Block rec = load_block(blocks, blk);
     scales += i * scales_ld;
     // read here, before the branch, so that they travel with the rows
@@ -963,13 +965,13 @@ __global__ __launch_bounds__(kWave *kPassWaves<G>) void k_worker_pass(
     const float ms0 = PACKED ? m_scales[rec.seg] : 0.f;
     uint64_t *bi = bits + i * bits_ld + (base >> 6);
     if (rec.whole)
-        worker_block<true, PACKED, SB, CACHED>(red, tiles, rec, base, lim, lane, wv, mv, word, s0, ms0,
-                                       m_scales, gv, cv, scales, ei, bi, partial + i * num_tiles,
-                                       beta1, omb1);
+        worker_block<true, PACKED, SB, (CACHE > 0)>(red, tiles, rec, base, lim, lane, wv, mv, word,
+                                                    s0, ms0, m_scales, gv, cv, scales, ei, bi,
+                                                    partial + i * num_tiles, beta1, omb1);
     else
-        worker_block<false, PACKED, SB, CACHED>(red, tiles, rec, base, lim, lane, wv, mv, word, s0, ms0,
-                                        m_scales, gv, cv, scales, ei, bi, partial + i * num_tiles,
-                                        beta1, omb1);
+        worker_block<false, PACKED, SB, (CACHE > 0)>(red, tiles, rec, base, lim, lane, wv, mv, word,
+                                                     s0, ms0, m_scales, gv, cv, scales, ei, bi,
+                                                     partial + i * num_tiles, beta1, omb1);
 }
 
 // ---------------------------------------------------------------------------
@@ -2629,20 +2631,28 @@ hipError_t launch_warmup(const DeviceTables &tb, float *x, float *m, float *v, c
     return hipGetLastError();
 }
 
-// Whether a call's gradient and error rows fit a quarter of the 256 MB
-// last-level cache, so that the error rows that it writes can still be there in
-// the next step: they are then stored without nt.  The loads keep nt, since
-// loads without it lose where other work between two steps has filled the
-// cache.  Step, us, both nt / stores without / both without, (a) back to back, (b)
-// after 128 MB of other writes and new gradients, (c) after 1 GB of other
-// writes: 2^20 elements n = 4 (a) 19.9 / 18.6 / 18.6, (b) 24.6 / 24.1 / 24.0, (c)
-// 26.1 / 26.4 / 30.4; 5x10^5 n = 16 (a) 27.2 / 26.3 / 28.2, (b) 31.5 / 30.7 / 30.9,
-// (c) 33.6 / 33.8 / 40.5; 2x10^6 n = 4 (a) 35.1 / 33.9 / 35.7, (b) 39.8 / 38.4 /
-// 38.8, (c) 42.8 / 44.1 / 50.7; 2^20 n = 8, bf16 (a) 26.6 / 24.5 / 24.3, (b) 31.6 /
-// 30.6 / 30.8, (c) 32.9 / 33.1 / 37.4.
-static bool rows_cached(int64_t items, size_t grad_bytes)
+// What a call keeps in the caches.  1: its gradient and error rows fit a quarter
+// of the 256 MB last-level cache, so the error rows that it writes can still be
+// there in the next step and are stored without nt.  2: the gradient rows also
+// fit half of the XCDs' 32 MB of L2 and are loaded without nt.  The error loads
+// keep nt, and larger gradients too: loads without it lose where other work
+// between two steps has filled the cache.
+// Step, us, 0 / 1 / 2 / error loads without nt too, (a) back to back, (b) after
+// 128 MB of other writes and new gradients, (c) after 1 GB of other writes and
+// new gradients, (d) the same with old gradients: 2^20 elements n = 4 (16 MB of
+// gradients) (a) 20.6 / 19.2 / 19.1 / 19.2, (b) 24.4 / 23.4 / 23.6 / 23.2, (c) 25.1
+// / 25.6 / 25.6 / 26.2, (d) 25.9 / 26.3 / 28.9 / 30.3, stepping five states in turn
+// 24.7 / 24.0 / 23.3 / 23.3; 5x10^5 n = 16 (32 MB) (a) 27.3 / 26.2 / 27.7 / 27.7,
+// (b) 31.3 / 30.3 / 30.5 / 30.7, (c) 32.2 / 31.7 / 32.4 / 32.8, (d) 33.3 / 33.6 /
+// 38.9 / 40.3, in turn 32.4 / 31.4 / 33.4 / 31.8; 2x10^6 n = 4 (32 MB) (a) 35.5 /
+// 34.1 / 36.3 / 35.9, (b) 39.2 / 37.9 / 38.0 / 38.2, (d) 42.0 / 42.3 / 47.6 / 49.2.
+// Up to 24 MB of gradients 2 is within 3% of 1 with new gradients, and 3 to 5%
+// ahead in turn; at 32 MB it is 6% behind there.
+static int row_caching(int64_t items, size_t grad_bytes)
 {
-    return items * kTileElems * (int64_t)(grad_bytes + 4) <= (int64_t)64 << 20;
+    const int64_t elems = items * kTileElems;
+    if (elems * (int64_t)(grad_bytes + 4) > (int64_t)64 << 20) return 0;
+    return elems * (int64_t)grad_bytes <= (int64_t)16 << 20 ? 2 : 1;
 }
 
 template <bool PACKED, class G>
@@ -2653,9 +2663,10 @@ static void launch_worker_items(const DeviceTables &tb, int64_t num_tiles, const
                                 double *partial, int n_local, float beta1, hipStream_t s)
 {
     const int64_t items = (int64_t)n_local * tb.num_blocks;
-    const auto kernel = rows_cached(items, sizeof(typename G::T))
-                            ? k_worker_pass<PACKED, G, true>
-                            : k_worker_pass<PACKED, G, false>;
+    const int cache = row_caching(items, sizeof(typename G::T));
+    const auto kernel = cache == 2   ? k_worker_pass<PACKED, G, 2>
+                        : cache == 1 ? k_worker_pass<PACKED, G, 1>
+                                     : k_worker_pass<PACKED, G, 0>;
     for (int64_t base = 0; base < items; base += kMaxPassItems) {
         const int64_t count = std::min(items - base, kMaxPassItems);
         hipLaunchKernelGGL(kernel, dim3((unsigned)xcd_grid(count, 1)),
