@@ -764,7 +764,7 @@ __global__ __launch_bounds__(kBlock) void k_adam_message(
 // 3.218.
 //
 // An fp32 momentum (the first compression step) is read once per block for all
-// local workers instead, by k_worker_rows, but on small plans.
+// local workers instead, by k_worker_rows, where that pays (packed_grid).
 // ---------------------------------------------------------------------------
 // Unused dynamic LDS that lets `groups` workgroups of a kernel onto a CU at
 // once (160 KB of LDS, allocated in steps of 512 bytes or less).
@@ -2677,6 +2677,30 @@ static void launch_worker_items(const DeviceTables &tb, int64_t num_tiles, const
     }
 }
 
+// Whether a call with an fp32 momentum takes the packed pass's grid, which reads
+// m again for every worker (from the caches, on plans of this size), instead of
+// the row walk.  The walk's workgroups of 8 blocks run one to a CU, 2,048 blocks
+// at a time, and step over the rows together, so a last round that is far from
+// full costs as much as a full one: the packed grid wins there in the first two
+// rounds.  Call, us, walk / packed, fp32 gradients unless said: 10^5 elements,
+// 32 rows (a step) 103 / 32; 1,030 blocks n = 8 32.2 / 25.4, bf16 33.0 / 25.0, n = 32
+// 112.9 / 88.0; 1,300 n = 8 34.0 / 31.2; 1,500 n = 8 34.6 / 37.1, bf16 35.5 / 34.3;
+// 2,000 n = 8 40.0 / 48.0; 2,100 n = 8 62.0 / 50.0, n = 32 221 / 179; 2,500 n = 8 63.9 /
+// 58.6; 2,900 n = 8 66.6 / 69.6; 4,000 n = 8 73.6 / 89.5; 4,340 n = 8 95.9 / 97.7, n =
+// 16 181.7 / 186.1.  Two or three rows share m too little for the
+// walk to pay before it runs several rounds: n = 2 2,100 blocks 17.3 / 14.0, 3,500
+// 22.7 / 20.3, 4,500 29.6 / 27.2; n = 3 2,000 19.0 / 17.4, 3,100 28.2 / 28.2, 4,000
+// 32.7 / 35.7.
+static bool packed_grid(int64_t num_blocks, int n_local)
+{
+    constexpr int64_t round = 256 * kWalkBlocks;  // blocks on the chip at once
+    if (n_local == 1) return true;                // no other row to share m with
+    if (n_local == 2 && num_blocks <= 2 * round + round / 4) return true;
+    if (n_local == 3 && num_blocks <= round + round / 2) return true;
+    return num_blocks <= round * 11 / 16 ||
+           (num_blocks > round && num_blocks <= round + round * 3 / 8);
+}
+
 template <class G>
 static void launch_worker_g(const DeviceTables &tb, int64_t num_tiles, const float *m,
                             const uint64_t *m_bits, const float *m_scales, const void *g,
@@ -2689,11 +2713,7 @@ static void launch_worker_g(const DeviceTables &tb, int64_t num_tiles, const flo
                                      scales, scales_ld, bits, bits_ld, partial, n_local, beta1, s);
         return;
     }
-    // One row has no other to share m with; and a small plan's row walk is a
-    // handful of workgroups walking n rows one round trip after another, where
-    // m read again by every worker comes from the caches (32 rows, step in us:
-    // 10^5 elements 103 -> 32, 10^6 137 -> 99; 2x10^6 164 in the walk, 188).
-    if (tb.num_blocks <= 1024 || n_local == 1) {
+    if (packed_grid(tb.num_blocks, n_local)) {
         launch_worker_items<false, G>(tb, num_tiles, m, m_bits, m_scales, g, g_ld, err, err_ld,
                                       scales, scales_ld, bits, bits_ld, partial, n_local, beta1,
                                       s);

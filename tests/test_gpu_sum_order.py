@@ -120,9 +120,11 @@ def test_fused_step_rounds_its_scales_as_the_three_calls(dev, numel, n):
 
 
 @pytest.mark.parametrize("numel,n", [
-    ([5000] * 800, 2),            # whole and mixed blocks, over 1,024 of them: the row walk
-    ([1024] * 2500, 3),
-    ([300] * 400 + [2000] * 100, 5),   # fewer: the packed pass's grid
+    ([5000] * 800, 4),                 # 3,950 blocks, whole and mixed: the row walk
+    ([1024] * 2040, 4),                # 2,040: the row walk
+    ([5000] * 800, 2),                 # two rows: the packed pass's grid
+    ([1024] * 2500, 5),                # 2,500: the packed pass's grid
+    ([300] * 400 + [2000] * 100, 5),   # few: the packed pass's grid
 ])
 def test_worker_scale_does_not_depend_on_the_momentum_form_or_gradient_type(dev, numel, n):
     import paper_2102_02888_amd as ob
@@ -135,8 +137,11 @@ def test_worker_scale_does_not_depend_on_the_momentum_form_or_gradient_type(dev,
             _compress(st, m=st.m if fp32_m else None)
             torch.cuda.synchronize()
             if first is None:
-                first = st.worker_scales
-            _same(first, st.worker_scales, "%s, %s momentum" % (dtype, "fp32" if fp32_m else "packed"))
+                first = st
+            what = "%s, %s momentum" % (dtype, "fp32" if fp32_m else "packed")
+            _same(first.worker_scales, st.worker_scales, what)
+            assert torch.equal(first.worker_bits, st.worker_bits), what
+            assert torch.equal(first.worker_err, st.worker_err), what
     plan.close()
 
 
